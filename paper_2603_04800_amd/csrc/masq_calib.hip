@@ -20,16 +20,38 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "masq.h"
 
 namespace {
 
 using bf16_t = unsigned short;
 
-__device__ __forceinline__ float load_abs(const float* p) { return fabsf(*p); }
-__device__ __forceinline__ float load_abs(const bf16_t* p) {
-    return fabsf(__uint_as_float(static_cast<uint32_t>(*p) << 16));
-}
+typedef int32_t v4i __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef double v4d16 __attribute__((ext_vector_type(4), aligned(16)));   // at any 16-byte address
+
+// 16 bytes of a row as magnitudes: 4 fp32 or 8 bf16 columns.
+template <typename XT> struct Abs16;
+template <> struct Abs16<float> {
+    static constexpr int kCols = 4;
+    static __device__ __forceinline__ void get(v4i raw, float (&v)[4]) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = __uint_as_float(static_cast<uint32_t>(raw[j]) & 0x7FFFFFFFu);
+    }
+};
+template <> struct Abs16<bf16_t> {
+    static constexpr int kCols = 8;
+    static __device__ __forceinline__ void get(v4i raw, float (&v)[8]) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            v[2 * j] = __uint_as_float((static_cast<uint32_t>(raw[j]) << 16) & 0x7FFFFFFFu);
+            v[2 * j + 1] = __uint_as_float(static_cast<uint32_t>(raw[j]) & 0x7FFF0000u);
+        }
+    }
+};
 
 // range [n_mod][K] := 0 (the maxima below are taken with integer atomics on
 // the bits of non-negative floats, which order like the values).
@@ -37,36 +59,77 @@ __global__ __launch_bounds__(256) void k_zero_f32(float* __restrict__ p, int64_t
     for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < n; i += gridDim.x * 256ll) p[i] = 0.f;
 }
 
-// grid (ceil(K / 256), row chunks): thread = column i, rows of its chunk;
-// per-modality maxima in registers, then one atomic max per modality.
-// Tokens whose id is outside [0, n_mod) belong to no modality.
+// grid (ceil(K / (64 C)), row chunks), C columns in a lane's 16 bytes: the
+// four waves of a workgroup take every fourth row of its chunk, kRangeRows
+// rows' loads in flight at once (HBM bound), per-modality maxima in
+// registers; the waves combine in LDS, then one atomic max per column and
+// modality.  Tokens whose id is outside [0, n_mod) belong to no modality.
+constexpr int kRangeRows = 8;
 template <typename XT>
 __global__ __launch_bounds__(256) void k_channel_range(const XT* __restrict__ x,
                                                        const int32_t* __restrict__ mod,
                                                        int64_t T, int K, int n_mod,
                                                        int rows_per_chunk,
                                                        float* __restrict__ range) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= K) return;
+    constexpr int C = Abs16<XT>::kCols;
+    __shared__ float red[3][64][C];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = (blockIdx.x * 64 + lane) * C;
+    const int ic = min(i, K - C);                     // K % 16 == 0: lanes past K repeat the last columns
     const int64_t t0 = static_cast<int64_t>(blockIdx.y) * rows_per_chunk;
     const int64_t t1 = t0 + rows_per_chunk < T ? t0 + rows_per_chunk : T;
-    float m[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int64_t t = t0; t < t1; ++t) {
-        const int mm = mod[t];                                 // uniform across the block
-        const float a = load_abs(x + t * K + i);
+    float m[4][C];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (mm == k) m[k] = fmaxf(m[k], a);
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int c = 0; c < C; ++c) m[k][c] = 0.f;
+    for (int64_t t = t0 + wave; t < t1; t += 4 * kRangeRows) {
+        v4i raw[kRangeRows];
+        int mm[kRangeRows];
+#pragma unroll
+        for (int r = 0; r < kRangeRows; ++r) {        // rows past the chunk repeat row t
+            const int64_t tr = t + 4 * r < t1 ? t + 4 * r : t;
+            raw[r] = *reinterpret_cast<const v4i*>(x + tr * K + ic);
+            mm[r] = __builtin_amdgcn_readfirstlane(mod[tr]);
+        }
+#pragma unroll
+        for (int r = 0; r < kRangeRows; ++r) {
+            float a[C];
+            Abs16<XT>::get(raw[r], a);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (mm[r] == k) {
+#pragma unroll
+                    for (int c = 0; c < C; ++c) m[k][c] = fmaxf(m[k][c], a[c]);
+                }
+        }
     }
-    for (int k = 0; k < n_mod; ++k)
-        if (m[k] > 0.f)
-            atomicMax(reinterpret_cast<int*>(range + static_cast<int64_t>(k) * K + i),
-                      __float_as_int(m[k]));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (k >= n_mod) break;
+        if (wave > 0) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) red[wave - 1][lane][c] = m[k][c];
+        }
+        __syncthreads();
+        if (wave == 0 && i < K) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const float v = fmaxf(fmaxf(m[k][c], red[0][lane][c]), fmaxf(red[1][lane][c], red[2][lane][c]));
+                if (v > 0.f)
+                    atomicMax(reinterpret_cast<int*>(range + static_cast<int64_t>(k) * K + i + c),
+                              __float_as_int(v));
+            }
+        }
+        __syncthreads();
+    }
 }
 
 // One wave per input channel i: w_i = max_j |w_ij| over its row of W
-// [K][N], then s^m_i = fl32(sqrt(max(R, 1e-5) / max(w_i, 1e-5))) in fp64 for
-// every modality and inv = fl32(1 / s) (correctly rounded).
+// [K][N] (16 bytes a lane, four loads in flight: HBM bound), then s^m_i =
+// fl32(sqrt(max(R, 1e-5) / max(w_i, 1e-5))) in fp64 for every modality and
+// inv = fl32(1 / s) (correctly rounded).
 __global__ __launch_bounds__(256) void k_smoothing_factors(const float* __restrict__ range,
                                                            const float* __restrict__ w, int K,
                                                            int N, int n_mod,
@@ -75,9 +138,17 @@ __global__ __launch_bounds__(256) void k_smoothing_factors(const float* __restri
     const int lane = threadIdx.x & 63;
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= K) return;
-    const float* row = w + static_cast<int64_t>(i) * N;
+    const v4f* row = reinterpret_cast<const v4f*>(w + static_cast<int64_t>(i) * N);
+    const int nv = N >> 2;                            // N % 16 == 0
     float a = 0.f;
-    for (int j = lane; j < N; j += 64) a = fmaxf(a, fabsf(row[j]));
+    for (int j = lane; j < nv; j += 4 * 64) {
+        v4f v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = row[j + 64 * q < nv ? j + 64 * q : j];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            a = fmaxf(fmaxf(a, fmaxf(fabsf(v[q].x), fabsf(v[q].y))), fmaxf(fabsf(v[q].z), fabsf(v[q].w)));
+    }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) a = fmaxf(a, __shfl_xor(a, o));
     if (lane < n_mod) {
@@ -89,60 +160,137 @@ __global__ __launch_bounds__(256) void k_smoothing_factors(const float* __restri
     }
 }
 
-// Q(S_t W) for 64 output channels per workgroup (W [K][N] fp32, paper layout;
-// codes written as wq [N][K]).  Pass 1: step d_o = max_i |s_i w_io| / qmax in
-// fp64 (s_i w_io is exact in fp64).  Pass 2: 64 x 64 blocks of codes
-// rint(s_i w_io / d_o) (fp64 division, round half to even), transposed
-// through LDS so both the reads (along o) and the writes (along i) are
-// contiguous.
-__global__ __launch_bounds__(256) void k_quantize_weight(const float* __restrict__ w,
-                                                         const float* __restrict__ s_text,
-                                                         int K, int N, int qmax,
-                                                         int8_t* __restrict__ wq,
-                                                         float* __restrict__ w_scale) {
-    __shared__ double smax[4][64];
-    __shared__ double sdelta[64];
-    __shared__ int8_t tile[64][65];
-    const int tid = threadIdx.x, ol = tid & 63, part = tid >> 6;
-    const int o0 = blockIdx.x * 64;
-    const int o = o0 + ol;
-    double a = 0.0;
-    if (o < N)
-        for (int i = part; i < K; i += 4)
-            a = fmax(a, fabs(static_cast<double>(s_text[i]) * static_cast<double>(w[static_cast<int64_t>(i) * N + o])));
-    smax[part][ol] = a;
+// Q(S_t W) (W [K][N] fp32, paper layout; codes written as wq [N][K]) in three
+// launches, so that the reads of W run on the whole chip whatever N is (one
+// workgroup per 64 channels left 3584 channels 56 workgroups: 0.55 ms for
+// 3584 x 3584, against about 40 us in this form):
+//   k_weight_absmax   step maxima of 64 channels over one of S row chunks,
+//                     max_i |s_i w_io| in fp64 (the product is exact).  The
+//                     chunk's fp64 maximum of channel o is kept in bytes
+//                     [8 c, 8 c + 8) of the row wq[o], which no code has
+//                     reached yet (S <= K / 64, so 8 S <= K bytes).
+//   k_quantize_codes  the codes of the columns past the kept maxima
+//                     (kQwHead); every workgroup combines the chunks' maxima
+//                     of its channels: d_o = max / qmax.
+//   k_quantize_codes (head) the first kQwHead columns, once every other
+//                     column is written: a workgroup reads the maxima of its
+//                     64 channels, then overwrites them.
+constexpr int kQwChunks = 16;
+constexpr int kQwHead = 128;                          // 8 kQwChunks bytes, whole 64-column blocks
+static_assert(8 * kQwChunks <= kQwHead && kQwHead % 64 == 0, "maxima lie in the head columns");
+constexpr int kQwBlocks = 4;                          // 64-column blocks per workgroup, at least
+
+__global__ __launch_bounds__(256) void k_weight_absmax(const float* __restrict__ w,
+                                                       const float* __restrict__ s_text, int K,
+                                                       int N, int rows_per_chunk,
+                                                       int8_t* __restrict__ wq) {
+    __shared__ double red[16][64];
+    const int tid = threadIdx.x, cl = tid & 15, rl = tid >> 4;
+    const int o = blockIdx.x * 64 + 4 * cl;           // N % 16 == 0: whole groups of 4
+    const int oc = min(o, N - 4);
+    const int i0 = blockIdx.y * rows_per_chunk, i1 = min(K, i0 + rows_per_chunk);
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    constexpr int U = 4;
+    for (int i = i0 + rl; i < i1; i += 16 * U) {
+        v4f v[U];
+        float sv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int iu = i + 16 * u < i1 ? i + 16 * u : i;
+            v[u] = *reinterpret_cast<const v4f*>(w + static_cast<int64_t>(iu) * N + oc);
+            sv[u] = s_text[iu];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                a[e] = fmax(a[e], fabs(static_cast<double>(sv[u]) * static_cast<double>(v[u][e])));
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[rl][4 * cl + e] = a[e];
     __syncthreads();
+    if (tid < 64 && blockIdx.x * 64 + tid < N) {
+        double m = red[0][tid];
+#pragma unroll
+        for (int q = 1; q < 16; ++q) m = fmax(m, red[q][tid]);
+        *reinterpret_cast<double*>(wq + static_cast<int64_t>(blockIdx.x * 64 + tid) * K + 8 * blockIdx.y) = m;
+    }
+}
+
+// One code: rint(v / d) clamped to [-qmax, qmax], d > 0, rd = 1 / d.  v rd
+// lies within 2^-51 |v / d| of the correctly rounded quotient, so unless it
+// is that close to a half-way point (or not finite) it rounds to the same
+// integer; the division itself is then never done.
+__device__ __forceinline__ int weight_code(double v, double d, double rd, double qmax) {
+    const double q = v * rd;
+    double r = rint(q);
+    if (!(fabs(q - r) < 0.5 - 1e-9)) r = rint(v / d);
+    return static_cast<int>(fmin(fmax(r, -qmax), qmax));
+}
+
+// Codes of 64 channels (blockIdx.x) and the `per` 64-column blocks from
+// b0 + per blockIdx.y on, below b1, transposed through LDS so that
+// both the reads (along o) and the writes (along i) are contiguous.
+__global__ __launch_bounds__(256) void k_quantize_codes(const float* __restrict__ w,
+                                                        const float* __restrict__ s_text, int K,
+                                                        int N, int qmax, int chunks, int b0, int b1,
+                                                        int per,
+                                                        int8_t* __restrict__ wq,
+                                                        float* __restrict__ w_scale) {
+    constexpr int kPitch = 80;                        // bytes: 16-byte aligned rows
+    __shared__ double sdelta[64];
+    __shared__ __attribute__((aligned(16))) int8_t tile[64 * kPitch];
+    const int tid = threadIdx.x, cl = tid & 15, rl = tid >> 4;
+    const int o0 = blockIdx.x * 64;
     if (tid < 64) {
-        const double m = fmax(fmax(smax[0][tid], smax[1][tid]), fmax(smax[2][tid], smax[3][tid]));
+        const int o = min(o0 + tid, N - 1);
+        const double* mp = reinterpret_cast<const double*>(wq + static_cast<int64_t>(o) * K);
+        double m = mp[0];
+        for (int c = 1; c < chunks; ++c) m = fmax(m, mp[c]);
         const double d = m / qmax;
         sdelta[tid] = d;
-        if (o0 + tid < N) w_scale[o0 + tid] = static_cast<float>(d);
+        if (w_scale != nullptr && o0 + tid < N) w_scale[o0 + tid] = static_cast<float>(d);
     }
     __syncthreads();
-    const double d = sdelta[ol];
-    for (int i0 = 0; i0 < K; i0 += 64) {
-        // read: thread (ol, part) takes rows i0 + part + 4 k of channel o
-        for (int k = 0; k < 16; ++k) {
-            const int il = part + 4 * k, i = i0 + il;
-            int c = 0;
-            if (o < N && i < K && d > 0.0) {
-                const double v = static_cast<double>(s_text[i]) * static_cast<double>(w[static_cast<int64_t>(i) * N + o]);
-                const double r = rint(v / d);
-                c = static_cast<int>(fmin(fmax(r, static_cast<double>(-qmax)), static_cast<double>(qmax)));
+    const int oc = min(o0 + 4 * cl, N - 4);
+    double d[4], rd[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        d[e] = sdelta[oc - o0 + e];
+        rd[e] = 1.0 / d[e];
+    }
+    const double qm = static_cast<double>(qmax);
+    const int first = b0 + per * static_cast<int>(blockIdx.y);
+    for (int blk = first; blk < min(b1, first + per); ++blk) {
+        const int i0 = blk * 64;
+        // thread (cl, rl): rows i0 + 4 rl + k, channels oc ..
+        v4f v[4];
+        float sv[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = min(i0 + 4 * rl + k, K - 1);
+            v[k] = *reinterpret_cast<const v4f*>(w + static_cast<int64_t>(i) * N + oc);
+            sv[k] = s_text[i];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            uint32_t packed = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                int c = 0;
+                if (d[e] > 0.0)
+                    c = weight_code(static_cast<double>(sv[k]) * static_cast<double>(v[k][e]), d[e],
+                                    rd[e], qm);
+                packed |= (static_cast<uint32_t>(c) & 0xFFu) << (8 * k);
             }
-            tile[ol][il] = static_cast<int8_t>(c);
+            *reinterpret_cast<uint32_t*>(tile + (4 * cl + e) * kPitch + 4 * rl) = packed;
         }
         __syncthreads();
-        // write: thread (ol', part) writes 16 consecutive codes of channel o0 + ol' ... as
-        // row (tid / 4) of the block, 16 bytes at 16 (tid % 4)
         {
-            const int orow = tid >> 2, seg = (tid & 3) * 16;
-            const int oo = o0 + orow;
-            if (oo < N) {
-                int8_t* dst = wq + static_cast<int64_t>(oo) * K + i0 + seg;
-                for (int e = 0; e < 16; ++e)
-                    if (i0 + seg + e < K) dst[e] = tile[orow][seg + e];
-            }
+            const int orow = tid >> 2, seg = (tid & 3) * 16;      // K % 16 == 0: whole pieces
+            if (o0 + orow < N && i0 + seg < K)
+                *reinterpret_cast<v4i*>(wq + static_cast<int64_t>(o0 + orow) * K + i0 + seg) =
+                    *reinterpret_cast<const v4i*>(tile + orow * kPitch + seg);
         }
         __syncthreads();
     }
@@ -213,98 +361,161 @@ __global__ __launch_bounds__(256) void k_weight_difference(const float* __restri
 
 // C (i, j) at c[i * crs + j * ccs] = alpha A B (+ beta C), fp64, with A (i,
 // k) at a[i * ars + k * acs] and B (k, j) at b[k * brs + j * bcs], so
-// transposed operands are strides, not copies.  TL x TL tiles (128, or 64
-// when the 128-tiles would not give every CU one), 256 threads of TL/16 x
-// TL/16 outputs (rows ty + 16 u, columns tx + 16 v), k in steps of 16 staged
-// through LDS with the next step's loads in flight.  Every element is summed
-// in increasing k by fused multiply-adds, whatever the tile size; the sum is
-// then multiplied by alpha (exact for alpha = +-1) and beta C added.  With
-// lower, tiles wholly above the diagonal (every j > i) are skipped.
-constexpr int kDgTile = 128;
-constexpr int kDgStep = 16;
-template <int TL>
-__global__ __launch_bounds__(256) void k_dgemm(int64_t M, int64_t N, int64_t K,
+// transposed operands are strides, not copies.  TI x TJ tiles, WI x WJ waves
+// on v_mfma_f64_16x16x4_f64, k in steps of KS staged through two LDS buffers
+// with the next two steps' loads in flight.  The instruction adds its four
+// products in increasing k, each with one rounding (measured: equal to a
+// chain of fma, bit for bit), so every element is the increasing-k chain of
+// fused multiply-adds whatever the tile size; the sum is then multiplied by
+// alpha (exact for alpha = +-1) and beta C added.  With lower, tiles wholly
+// above the diagonal (every j > i) are skipped.
+//
+// Bound by the fp64 rate (78.6 TFLOP/s, shared by the vector and the matrix
+// unit); the vector form of this kernel read one 8-byte LDS operand per four
+// fma and stood at 23-28 TFLOP/s.  LDS rows [i][k] lie KS + 1 doubles apart:
+// 16 rows of one k are served in one 128-byte cycle only if no two of them
+// share an 8-byte slot (KS + 4, two rows a slot: 200 us where this takes
+// 156).  64 x 32 tiles of four waves, several workgroups per CU, hide each
+// other's barriers: measured 156 us for 256 x 3584 x 3584 (64 x 64 of eight
+// waves 158, 128 x 128 452), 135-142 us for 3584 x 3584 x 256 (177, 154),
+// 1.14-1.19 ms for 3072 x 3072 x 3584 (1.26, 1.38), 57 TFLOP/s there; no
+// shape of these favoured a larger tile.
+// v_mfma_f64_16x16x4_f64 layout: lane l holds A(l % 16, l / 16), B(l / 16,
+// l % 16) and C(l / 16 + 4 e, l % 16), e = 0..3.
+constexpr int kDgRows = 64, kDgCols = 32, kDgStep = 16;
+template <int TI, int TJ, int KS, int WI, int WJ>
+__global__ __launch_bounds__(64 * WI * WJ, 2) void k_dgemm(int64_t M, int64_t N, int64_t K,
                                                const double* __restrict__ a, int64_t ars,
                                                int64_t acs, const double* __restrict__ b,
                                                int64_t brs, int64_t bcs, double alpha, double beta,
                                                double* __restrict__ c, int64_t crs, int64_t ccs,
                                                int lower) {
-    constexpr int NU = TL / 16, NQ = TL * kDgStep / 256;     // outputs a row, loads per operand
-    constexpr int LT = TL == 128 ? 7 : 6;                    // log2(TL)
-    __shared__ double as[kDgStep][TL + 1];
-    __shared__ double bs[kDgStep][TL + 1];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int64_t i0 = static_cast<int64_t>(blockIdx.y) * TL;
-    const int64_t j0 = static_cast<int64_t>(blockIdx.x) * TL;
-    if (lower && j0 > i0 + TL - 1) return;                   // block-uniform
-    // staging: element e = tid + 256 q of each TL x 16 operand block; the
-    // fastest-moving index follows the operand's unit-stride direction
+    constexpr int NI = TI / WI / 16, NJ = TJ / WJ / 16;      // 16-wide blocks of a wave's edges
+    constexpr int NT = 64 * WI * WJ;
+    constexpr int NQA = TI * KS / NT, NQB = TJ * KS / NT;    // loads per operand and thread
+    constexpr int kPitch = KS + 1;
+    __shared__ double as[2][TI * kPitch];
+    __shared__ double bs[2][TJ * kPitch];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wi = (wave / WJ) * (TI / WI), wj = (wave % WJ) * (TJ / WJ);
+    const int lr = lane & 15, lk = lane >> 4;
+    const int64_t tiles_j = (N + TJ - 1) / TJ;
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x) / tiles_j * TI;
+    const int64_t j0 = static_cast<int64_t>(blockIdx.x) % tiles_j * TJ;
+    if (lower && j0 > i0 + TI - 1) return;                   // block-uniform
+    // staging: element e = tid + NT q of each operand block;
+    // the fastest-moving index follows the operand's unit-stride direction.
+    // Rows past M (columns past N) repeat the last one: their results are
+    // not stored.  k past K is zero.
     const bool a_k_fast = acs == 1, b_k_fast = bcs != 1;
-    double ra[NQ], rb[NQ];
-    auto load = [&](int64_t k0) __attribute__((always_inline)) {
+    const double *pa[NQA], *pb[NQB];
+    int sa[NQA], sb[NQB], ka[NQA], kb[NQB];                  // LDS places, k within the step
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int e = tid + 256 * q;
-            const int kk = a_k_fast ? (e & 15) : (e >> LT);
-            const int ii = a_k_fast ? (e >> 4) : (e & (TL - 1));
-            const int64_t i = i0 + ii, k = k0 + kk;
-            ra[q] = (i < M && k < K) ? a[i * ars + k * acs] : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int e = tid + 256 * q;
-            const int kk = b_k_fast ? (e & 15) : (e >> LT);
-            const int jj = b_k_fast ? (e >> 4) : (e & (TL - 1));
-            const int64_t j = j0 + jj, k = k0 + kk;
-            rb[q] = (j < N && k < K) ? b[k * brs + j * bcs] : 0.0;
-        }
-    };
-    auto stash = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int e = tid + 256 * q;
-            as[a_k_fast ? (e & 15) : (e >> LT)][a_k_fast ? (e >> 4) : (e & (TL - 1))] = ra[q];
-            bs[b_k_fast ? (e & 15) : (e >> LT)][b_k_fast ? (e >> 4) : (e & (TL - 1))] = rb[q];
-        }
-    };
-    double acc[NU][NU];
-#pragma unroll
-    for (int u = 0; u < NU; ++u)
-#pragma unroll
-        for (int v = 0; v < NU; ++v) acc[u][v] = 0.0;
-    if (K > 0) load(0);
-    for (int64_t k0 = 0; k0 < K; k0 += kDgStep) {
-        __syncthreads();
-        stash();
-        __syncthreads();
-        if (k0 + kDgStep < K) load(k0 + kDgStep);
-#pragma unroll 4
-        for (int kk = 0; kk < kDgStep; ++kk) {
-            double av[NU], bv[NU];
-#pragma unroll
-            for (int u = 0; u < NU; ++u) av[u] = as[kk][ty + 16 * u];
-#pragma unroll
-            for (int v = 0; v < NU; ++v) bv[v] = bs[kk][tx + 16 * v];
-#pragma unroll
-            for (int u = 0; u < NU; ++u)
-#pragma unroll
-                for (int v = 0; v < NU; ++v) acc[u][v] = fma(av[u], bv[v], acc[u][v]);
-        }
+    for (int q = 0; q < NQA; ++q) {
+        const int e = tid + NT * q, ia = a_k_fast ? e / KS : e % TI;
+        ka[q] = a_k_fast ? e % KS : e / TI;
+        sa[q] = ia * kPitch + ka[q];
+        pa[q] = a + (i0 + ia < M ? i0 + ia : M - 1) * ars;
+        if (ka[q] < K) pa[q] += ka[q] * acs;                 // (else never read)
     }
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-        const int64_t i = i0 + ty + 16 * u;
-        if (i >= M) break;
+    for (int q = 0; q < NQB; ++q) {
+        const int e = tid + NT * q, jb = b_k_fast ? e / KS : e % TJ;
+        kb[q] = b_k_fast ? e % KS : e / TJ;
+        sb[q] = jb * kPitch + kb[q];
+        pb[q] = b + (j0 + jb < N ? j0 + jb : N - 1) * bcs;
+        if (kb[q] < K) pb[q] += kb[q] * brs;
+    }
+    // step j's operands through register set j % 2: two steps ahead of use
+    double ra[2][NQA], rb[2][NQB];
+    auto load_whole = [&](auto set, int64_t k0) __attribute__((always_inline)) {
+        constexpr int P = decltype(set)::value;
 #pragma unroll
-        for (int v = 0; v < NU; ++v) {
-            const int64_t j = j0 + tx + 16 * v;
-            if (j < N) {
-                double r = alpha * acc[u][v];
-                if (beta != 0.0) r = r + beta * c[i * crs + j * ccs];
-                c[i * crs + j * ccs] = r;
+        for (int q = 0; q < NQA; ++q) ra[P][q] = pa[q][k0 * acs];
+#pragma unroll
+        for (int q = 0; q < NQB; ++q) rb[P][q] = pb[q][k0 * brs];
+    };
+    auto load = [&](auto set, int64_t k0) __attribute__((always_inline)) {   // any k0 >= 0
+        constexpr int P = decltype(set)::value;
+#pragma unroll
+        for (int q = 0; q < NQA; ++q) ra[P][q] = k0 + ka[q] < K ? pa[q][k0 * acs] : 0.0;
+#pragma unroll
+        for (int q = 0; q < NQB; ++q) rb[P][q] = k0 + kb[q] < K ? pb[q][k0 * brs] : 0.0;
+    };
+    auto stash = [&](auto set) __attribute__((always_inline)) {
+        constexpr int P = decltype(set)::value;
+#pragma unroll
+        for (int q = 0; q < NQA; ++q) as[P][sa[q]] = ra[P][q];
+#pragma unroll
+        for (int q = 0; q < NQB; ++q) bs[P][sb[q]] = rb[P][q];
+    };
+    v4d acc[NI][NJ];
+#pragma unroll
+    for (int u = 0; u < NI; ++u)
+#pragma unroll
+        for (int v = 0; v < NJ; ++v) acc[u][v] = v4d{0.0, 0.0, 0.0, 0.0};
+    using set0 = std::integral_constant<int, 0>;
+    using set1 = std::integral_constant<int, 1>;
+    auto multiply = [&](auto set) __attribute__((always_inline)) {
+        constexpr int P = decltype(set)::value;
+#pragma unroll
+        for (int s = 0; s < KS / 4; ++s) {
+            double av[NI], bv[NJ];
+#pragma unroll
+            for (int u = 0; u < NI; ++u) av[u] = as[P][(wi + 16 * u + lr) * kPitch + 4 * s + lk];
+#pragma unroll
+            for (int v = 0; v < NJ; ++v) bv[v] = bs[P][(wj + 16 * v + lr) * kPitch + 4 * s + lk];
+#pragma unroll
+            for (int u = 0; u < NI; ++u)
+#pragma unroll
+                for (int v = 0; v < NJ; ++v)
+                    acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[v], acc[u][v], 0, 0, 0);
+        }
+    };
+    load(set0{}, 0);
+    load(set1{}, KS);
+    stash(set0{});
+    __syncthreads();
+    // LDS buffer P holds step k0 (k0 / KS even: P = 0); each half stashes the
+    // next step into the other buffer, last read before the previous barrier.
+    // Whole steps only, so that the waits count exactly one step's loads.
+    int64_t k0 = 0;
+    for (; k0 + 4 * KS <= K; k0 += 2 * KS) {
+        load_whole(set0{}, k0 + 2 * KS);
+        multiply(set0{});
+        stash(set1{});
+        __syncthreads();
+        load_whole(set1{}, k0 + 3 * KS);
+        multiply(set1{});
+        stash(set0{});
+        __syncthreads();
+    }
+    for (; k0 < K; k0 += 2 * KS) {
+        load(set0{}, k0 + 2 * KS);
+        multiply(set0{});
+        stash(set1{});
+        __syncthreads();
+        if (k0 + KS >= K) break;
+        load(set1{}, k0 + 3 * KS);
+        multiply(set1{});
+        stash(set0{});
+        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < NI; ++u)
+#pragma unroll
+        for (int v = 0; v < NJ; ++v) {
+            const int64_t j = j0 + wj + 16 * v + lr;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t i = i0 + wi + 16 * u + lk + 4 * e;
+                if (i < M && j < N) {
+                    double r = alpha * acc[u][v][e];
+                    if (beta != 0.0) r = r + beta * c[i * crs + j * ccs];
+                    c[i * crs + j * ccs] = r;
+                }
             }
         }
-    }
 }
 
 // ------------------------------------------------------- MAS optimisation
@@ -315,13 +526,33 @@ __global__ __launch_bounds__(256) void k_dgemm(int64_t M, int64_t N, int64_t K,
 // pass (formed with k_dgemm).
 
 // out [R][C] fp64 = codes [R][C] * scale[r] (exact: 8 x 24 significant bits).
+// With C % 4 == 0 each thread takes 4 codes of a row (VEC: one 4-byte load,
+// two 16-byte stores); grid (chunks of a row's pieces, rows).
+template <bool VEC>
 __global__ __launch_bounds__(256) void k_dequantize_rows(const int8_t* __restrict__ codes,
                                                          const float* __restrict__ scale,
                                                          int64_t R, int64_t C,
                                                          double* __restrict__ out) {
-    const int64_t n = R * C;
-    for (int64_t e = blockIdx.x * 256ll + threadIdx.x; e < n; e += gridDim.x * 256ll)
-        out[e] = static_cast<double>(codes[e]) * static_cast<double>(scale[e / C]);
+    if constexpr (VEC) {
+        const int64_t nv = C >> 2;
+        for (int64_t r = blockIdx.y; r < R; r += gridDim.y) {
+            const double sc = static_cast<double>(scale[r]);
+            const uint32_t* src = reinterpret_cast<const uint32_t*>(codes + r * C);
+            double* dst = out + r * C;
+            for (int64_t v = blockIdx.x * 256ll + threadIdx.x; v < nv; v += gridDim.x * 256ll) {
+                const uint32_t w = src[v];
+                v4d d;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    d[j] = static_cast<double>(static_cast<int8_t>(w >> (8 * j))) * sc;
+                *reinterpret_cast<v4d16*>(dst + 4 * v) = d;
+            }
+        }
+    } else {
+        const int64_t n = R * C;
+        for (int64_t e = blockIdx.x * 256ll + threadIdx.x; e < n; e += gridDim.x * 256ll)
+            out[e] = static_cast<double>(codes[e]) * static_cast<double>(scale[e / C]);
+    }
 }
 
 // g_e = sign(y_e - ref_e) * inv_count; partial[b] = the sum of |y_e - ref_e|
@@ -350,12 +581,23 @@ __global__ __launch_bounds__(256) void k_mae_sign(const double* __restrict__ y,
 }
 
 // loss[0] = (partial[0] + partial[1] + ... + partial[nparts - 1]) / count,
-// in that order (one thread: a few thousand block sums at most).
-__global__ void k_mae_loss(const double* __restrict__ partial, int64_t nparts, double count,
-                           double* __restrict__ loss) {
+// in that order: one wave loads 64 sums at a time, then its first lane adds
+// them (a load per addition would cost a memory round trip each).
+__global__ __launch_bounds__(64) void k_mae_loss(const double* __restrict__ partial, int64_t nparts,
+                                                 double count, double* __restrict__ loss) {
+    __shared__ double buf[64];
+    const int lane = threadIdx.x;
     double s = 0.0;
-    for (int64_t b = 0; b < nparts; ++b) s += partial[b];
-    *loss = s / count;
+    for (int64_t b0 = 0; b0 < nparts; b0 += 64) {
+        buf[lane] = b0 + lane < nparts ? partial[b0 + lane] : 0.0;
+        __syncthreads();
+        if (lane == 0) {
+            const int n = static_cast<int>(nparts - b0 < 64 ? nparts - b0 : 64);
+            for (int q = 0; q < n; ++q) s += buf[q];
+        }
+        __syncthreads();
+    }
+    if (lane == 0) *loss = s / count;
 }
 
 // Adam on theta = ln s (Kingma and Ba 2015), one element a thread, each
@@ -403,30 +645,59 @@ __global__ __launch_bounds__(256) void k_adam_log_init(double* __restrict__ thet
     inv_s[i] = 1.0f / sn;
 }
 
-// colpart[i] = sum_t x[t][i] a[t][i] (thread per column, t in order).
-__global__ __launch_bounds__(256) void k_column_dot(const double* __restrict__ x,
-                                                    const double* __restrict__ a, int64_t T,
-                                                    int64_t K, double* __restrict__ out) {
-    const int64_t i = blockIdx.x * 256ll + threadIdx.x;
+// colpart[i] = sum_t x[t][i] a[t][i] (thread per column, t in order; 16
+// rows' loads in flight, one wave a workgroup so that few columns still
+// spread over the chip).
+__global__ __launch_bounds__(64) void k_column_dot(const double* __restrict__ x,
+                                                   const double* __restrict__ a, int64_t T,
+                                                   int64_t K, double* __restrict__ out) {
+    constexpr int U = 16;
+    const int64_t i = blockIdx.x * 64ll + threadIdx.x;
     if (i >= K) return;
     double acc = 0.0;
-    for (int64_t t = 0; t < T; ++t) acc = fma(x[t * K + i], a[t * K + i], acc);
+    int64_t t = 0;
+    for (; t + U <= T; t += U) {
+        double xv[U], av[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            xv[q] = x[(t + q) * K + i];
+            av[q] = a[(t + q) * K + i];
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) acc = fma(xv[q], av[q], acc);
+    }
+    for (; t < T; ++t) acc = fma(x[t * K + i], a[t * K + i], acc);
     out[i] = acc;
 }
 
-// grad[i] = -colpart[i] / (s_i s_i) + sum_o w[i][o] b[i][o] (a wave per row i).
+// grad[i] = -colpart[i] / (s_i s_i) + sum_o w[i][o] b[i][o] (a wave per row
+// i, lane l summing o = l, l + 64, .. in order; 8 of them in flight).
 __global__ __launch_bounds__(256) void k_mas_grad(const double* __restrict__ colpart,
                                                   const double* __restrict__ w,
                                                   const double* __restrict__ b,
                                                   const float* __restrict__ s, int64_t K,
                                                   int64_t N, double* __restrict__ grad) {
+    constexpr int U = 8;
     const int lane = threadIdx.x & 63;
     const int64_t i = blockIdx.x * 4ll + (threadIdx.x >> 6);
     if (i >= K) return;
+    const double* wr = w + i * N;
+    const double* br = b + i * N;
     double acc = 0.0;
-    for (int64_t o = lane; o < N; o += 64) acc = fma(w[i * N + o], b[i * N + o], acc);
+    int64_t o = lane;
+    for (; o + 64 * (U - 1) < N; o += 64 * U) {
+        double wv[U], bv[U];
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
+        for (int q = 0; q < U; ++q) {
+            wv[q] = wr[o + 64 * q];
+            bv[q] = br[o + 64 * q];
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) acc = fma(wv[q], bv[q], acc);
+    }
+    for (; o < N; o += 64) acc = fma(wr[o], br[o], acc);
+#pragma unroll
+    for (int o2 = 32; o2 >= 1; o2 >>= 1) acc += __shfl_xor(acc, o2);
     if (lane == 0) {
         const double si = static_cast<double>(s[i]);
         grad[i] = -colpart[i] / (si * si) + acc;
@@ -445,15 +716,11 @@ hipError_t launch_dgemm(int64_t m, int64_t n, int64_t k, const double* a, int64_
                         double beta, double* c, int64_t crs, int64_t ccs, bool lower,
                         hipStream_t s) {
     if (m <= 0 || n <= 0) return hipSuccess;
-    const int64_t tiles = ((n + kDgTile - 1) / kDgTile) * ((m + kDgTile - 1) / kDgTile);
-    const int tl = (tiles < 256 && (m + 63) / 64 <= 65535) ? 64 : kDgTile;
-    const dim3 grid(static_cast<unsigned>((n + tl - 1) / tl), static_cast<unsigned>((m + tl - 1) / tl));
-    if (tl == 64)
-        hipLaunchKernelGGL(k_dgemm<64>, grid, dim3(256), 0, s, m, n, k, a, ars, acs, b, brs, bcs,
-                           alpha, beta, c, crs, ccs, lower ? 1 : 0);
-    else
-        hipLaunchKernelGGL(k_dgemm<kDgTile>, grid, dim3(256), 0, s, m, n, k, a, ars, acs, b, brs,
-                           bcs, alpha, beta, c, crs, ccs, lower ? 1 : 0);
+    const int64_t tiles = ((n + kDgCols - 1) / kDgCols) * ((m + kDgRows - 1) / kDgRows);
+    if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;       // (C alone would hold 32 TB)
+    hipLaunchKernelGGL((k_dgemm<kDgRows, kDgCols, kDgStep, 2, 2>), dim3(static_cast<unsigned>(tiles)),
+                       dim3(256), 0, s, m, n, k, a, ars, acs, b, brs, bcs, alpha, beta, c, crs, ccs,
+                       lower ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -477,9 +744,12 @@ masq_status masq_channel_range(const void* x, masq_dtype x_dt, const int32_t* mo
                        dim3(256), 0, s, range, n);
     if (T > 0) {
         const int K = static_cast<int>(c_in);
-        const int64_t col_blocks = (K + 255) / 256;
-        int64_t chunks = (2048 + col_blocks - 1) / col_blocks;          // about 2048 workgroups
-        if (chunks > T) chunks = T;
+        const int cols = 64 * (x_dt == MASQ_BF16 ? Abs16<bf16_t>::kCols : Abs16<float>::kCols);
+        const int64_t col_blocks = (K + cols - 1) / cols;
+        // about 1024 workgroups, and at least a round of loads for each wave
+        int64_t chunks = (1024 + col_blocks - 1) / col_blocks;
+        const int64_t most = (T + 4 * kRangeRows - 1) / (4 * kRangeRows);
+        if (chunks > most) chunks = most;
         const int rows = static_cast<int>((T + chunks - 1) / chunks);
         chunks = (T + rows - 1) / rows;
         const dim3 grid(static_cast<unsigned>(col_blocks), static_cast<unsigned>(chunks));
@@ -519,9 +789,23 @@ masq_status masq_quantize_weight(const float* w, const float* smooth_text, int64
     if (!aligned16(w) || !aligned16(smooth_text) || !aligned16(wq) || !aligned16(w_scale))
         return MASQ_ERR_ALIGN;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_quantize_weight, dim3(static_cast<unsigned>((c_out + 63) / 64)), dim3(256),
-                       0, static_cast<hipStream_t>(stream), w, smooth_text, static_cast<int>(c_in),
-                       static_cast<int>(c_out), (1 << (bits - 1)) - 1, wq, w_scale);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const int K = static_cast<int>(c_in), N = static_cast<int>(c_out), qmax = (1 << (bits - 1)) - 1;
+    const unsigned groups = static_cast<unsigned>((N + 63) / 64);
+    int chunks = K / 64 < kQwChunks ? (K / 64 < 1 ? 1 : K / 64) : kQwChunks;
+    const int rows = (K + chunks - 1) / chunks;
+    chunks = (K + rows - 1) / rows;
+    const int blocks = (K + 63) / 64, head = blocks < kQwHead / 64 ? blocks : kQwHead / 64;
+    hipLaunchKernelGGL(k_weight_absmax, dim3(groups, static_cast<unsigned>(chunks)), dim3(256), 0, s,
+                       w, smooth_text, K, N, rows, wq);
+    const int rest = blocks - head;
+    const int per = rest > kQwBlocks * 65535 ? (rest + 65534) / 65535 : kQwBlocks;
+    if (rest > 0)
+        hipLaunchKernelGGL(k_quantize_codes, dim3(groups, static_cast<unsigned>((rest + per - 1) / per)),
+                           dim3(256), 0, s, w, smooth_text, K, N, qmax, chunks, head, blocks, per, wq,
+                           static_cast<float*>(nullptr));
+    hipLaunchKernelGGL(k_quantize_codes, dim3(groups, 1), dim3(256), 0, s, w, smooth_text, K, N, qmax,
+                       chunks, 0, head, head, wq, w_scale);
     return hipGetLastError() == hipSuccess ? MASQ_OK : MASQ_ERR_HIP;
 }
 
@@ -573,8 +857,8 @@ masq_status masq_dgemm(int64_t m, int64_t n, int64_t k, const double* a, int64_t
                        int64_t a_col_stride, const double* b, int64_t b_row_stride,
                        int64_t b_col_stride, double beta, double* c, int64_t ldc, void* stream) {
     if (m < 0 || n < 0 || k < 0 || a_row_stride < 0 || a_col_stride < 0 || b_row_stride < 0 ||
-        b_col_stride < 0 || (m + kDgTile - 1) / kDgTile > 65535 ||
-        (n + kDgTile - 1) / kDgTile > 0x7fffffffLL || (m > 0 && n > 0 && ldc < n))
+        b_col_stride < 0 || (m + 127) / 128 > 65535 ||
+        (n + 127) / 128 > 0x7fffffffLL || (m > 0 && n > 0 && ldc < n))
         return MASQ_ERR_SHAPE;
     if (m == 0 || n == 0) return MASQ_OK;
     if (!c || (k > 0 && (!a || !b))) return MASQ_ERR_NULL;
@@ -594,10 +878,19 @@ masq_status masq_dequantize_rows(const int8_t* codes, const float* scale, int64_
     if (!codes || !scale || !out) return MASQ_ERR_NULL;
     if (!aligned16(codes) || !aligned16(scale) || !aligned16(out)) return MASQ_ERR_ALIGN;
     (void)hipGetLastError();
-    const int64_t n = rows * cols;
-    const int64_t blocks = (n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192;
-    hipLaunchKernelGGL(k_dequantize_rows, dim3(static_cast<unsigned>(blocks)), dim3(256), 0,
-                       static_cast<hipStream_t>(stream), codes, scale, rows, cols, out);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (cols % 4 == 0) {
+        const int64_t bx = (cols / 4 + 255) / 256;
+        const dim3 grid(static_cast<unsigned>(bx < 64 ? bx : 64),
+                        static_cast<unsigned>(rows < 8192 ? rows : 8192));
+        hipLaunchKernelGGL(k_dequantize_rows<true>, grid, dim3(256), 0, st, codes, scale, rows, cols,
+                           out);
+    } else {
+        const int64_t n = rows * cols;
+        const int64_t blocks = (n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192;
+        hipLaunchKernelGGL(k_dequantize_rows<false>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0,
+                           st, codes, scale, rows, cols, out);
+    }
     return hipGetLastError() == hipSuccess ? MASQ_OK : MASQ_ERR_HIP;
 }
 
@@ -623,7 +916,7 @@ masq_status masq_mae_loss(const double* partial, int64_t count, double* loss, vo
     if (!loss || (count > 0 && !partial)) return MASQ_ERR_NULL;
     if (!aligned8(loss) || (count > 0 && !aligned8(partial))) return MASQ_ERR_ALIGN;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_mae_loss, dim3(1), dim3(1), 0, static_cast<hipStream_t>(stream), partial,
+    hipLaunchKernelGGL(k_mae_loss, dim3(1), dim3(64), 0, static_cast<hipStream_t>(stream), partial,
                        masq_mae_partials(count), count > 0 ? static_cast<double>(count) : 1.0, loss);
     return hipGetLastError() == hipSuccess ? MASQ_OK : MASQ_ERR_HIP;
 }
@@ -668,8 +961,8 @@ masq_status masq_mas_gradient(const double* x, const double* a, const double* w,
         return MASQ_ERR_ALIGN;
     (void)hipGetLastError();
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(k_column_dot, dim3(static_cast<unsigned>((c_in + 255) / 256)), dim3(256), 0,
-                       st, x, a, T, c_in, colpart);
+    hipLaunchKernelGGL(k_column_dot, dim3(static_cast<unsigned>((c_in + 63) / 64)), dim3(64), 0, st, x,
+                       a, T, c_in, colpart);
     hipLaunchKernelGGL(k_mas_grad, dim3(static_cast<unsigned>((c_in + 3) / 4)), dim3(256), 0, st,
                        colpart, w, b, smooth, c_in, c_out, grad);
     return hipGetLastError() == hipSuccess ? MASQ_OK : MASQ_ERR_HIP;

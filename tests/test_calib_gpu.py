@@ -64,6 +64,42 @@ def test_small_calibration_with_invalid_ids_and_empty_modality(ops, act):
     _check(ops, x, mod, w, 4, act)
 
 
+@pytest.mark.parametrize("T,K,N", [(1, 16, 16), (33, 48, 80), (70, 64, 144), (65, 80, 64),
+                                   (129, 128, 272), (100, 144, 48), (257, 1040, 208), (40, 8208, 16)])
+@pytest.mark.parametrize("act", ["f32", "bf16"])
+def test_calibration_at_the_edges_of_its_blocks(ops, T, K, N, act):
+    """Columns around the 64-column code blocks, the two head blocks that are
+    written last, and the 1 to 16 row chunks of the weight maxima; channels
+    around the 64-channel groups; rows around the row rounds of the ranges."""
+    rng = np.random.default_rng(T * 31 + K * 7 + N)
+    mod = rng.integers(0, 3, T).astype(np.int32)
+    x = (rng.standard_normal((T, K)) * rng.uniform(0.1, 30, K)).astype(np.float32)
+    x = bf16_round(x) if act == "bf16" else x
+    w = (rng.standard_normal((K, N)) / np.sqrt(K)).astype(np.float32)
+    w[:, N // 2] = 0.0
+    _check(ops, x, mod, w, 3, act)
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+def test_weight_codes_half_way_between_two_integers(ops, bits):
+    """Steps of exactly 1 and 3 with values exactly half-way (rounded to
+    even) and one part in 2^23 to either side of it."""
+    top = 127 if bits == 8 else 7
+    K, N = 272, 32
+    half = np.arange(-top, top) + 0.5
+    v = np.concatenate([half, half * (1 + 2.0 ** -23), half * (1 - 2.0 ** -23)])[:K - 1]
+    w = np.zeros((K, N), np.float32)
+    w[:v.size] = np.resize(v, v.size)[:, None]
+    w[-1] = top
+    w[:, 1::2] *= 3.0
+    dev = torch.device("cuda:0")
+    one = np.ones(K, np.float32)
+    wq, ws = ops.quantize_weight(torch.from_numpy(w).to(dev), torch.from_numpy(one).to(dev), bits=bits)
+    wq_ref, ws_ref, _ = cal.quantize_weight(w, one, bits)
+    assert np.array_equal(wq.cpu().numpy(), wq_ref)
+    assert np.array_equal(ws.cpu().numpy(), ws_ref)
+
+
 def test_prefill_workload_calibration(ops):
     """The 4096-token prefill layer's X and the 3584 x 18944 float weight."""
     cfg = synth.CONFIGS[1]
@@ -121,6 +157,29 @@ def test_dgemm_within_the_fp64_bound(ops, m, n, k, ta, tb):
     cb = ops.dgemm(at, bt, c=torch.from_numpy(c0.copy()).to(dev), beta=-0.75).cpu().numpy()
     ref = a @ b + (-0.75) * c0
     assert np.all(np.abs(cb - ref) <= _dgemm_bound(a, b) + 2 * _U * np.abs(ref) + 1e-300)
+
+
+@pytest.mark.parametrize("m,n,k", [(64, 64, 32), (65, 63, 33), (63, 65, 31), (192, 320, 4), (16, 2064, 100),
+                                   (1100, 1040, 48), (2049, 2050, 18)])
+@pytest.mark.parametrize("ta,tb", [(False, False), (True, True)])
+def test_dgemm_is_the_increasing_k_chain(ops, m, n, k, ta, tb):
+    """Both tile sizes around their edges and k steps: with operands of few
+    bits every order is exact, and a term that only survives when the sum
+    runs in increasing k (2^60, then -2^60 beside small terms) pins the order."""
+    rng = np.random.default_rng(m + n + k)
+    a = rng.integers(-8, 9, (m, k)).astype(np.float64)
+    b = rng.integers(-8, 9, (k, n)).astype(np.float64)
+    dev = torch.device("cuda:0")
+
+    def put(v, t):
+        return torch.from_numpy(np.ascontiguousarray(v.T)).to(dev).T if t else torch.from_numpy(v).to(dev)
+    assert np.array_equal(ops.dgemm(put(a, ta), put(b, tb)).cpu().numpy(), a @ b)
+    a[:, 0], b[0] = 2.0 ** 30, 2.0 ** 30                    # first: the next k / 2 terms are lost
+    half = k // 2
+    a[:, half], b[half] = -2.0 ** 30, 2.0 ** 30             # cancels it
+    ref = (a[:, half + 1:] @ b[half + 1:]) if k > 2 else a @ b
+    a[:, 1:half] *= 2.0 ** -12                               # below half an ulp of 2^60
+    assert np.array_equal(ops.dgemm(put(a, ta), put(b, tb)).cpu().numpy(), ref)
 
 
 def test_dgemm_degenerate_sizes(ops):
