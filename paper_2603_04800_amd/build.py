@@ -20,7 +20,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIBDIR = os.path.join(PKG, "_lib")
 LIB = os.path.join(LIBDIR, "libmasq.so")
-SOURCES = ("masq_kernels.hip", "masq_api.hip", "masq_calib.hip", "masq_linalg.hip")
+SOURCES = ("masq_kernels.hip", "masq_tile.hip", "masq_api.hip", "masq_calib.hip", "masq_linalg.hip")
 # the benchmark's peak probes, a library of their own (not part of the layer)
 PROBE_SOURCES = ("masq_probe.hip",)
 PROBE_LIB = os.path.join(LIBDIR, "libmasq_probe.so")

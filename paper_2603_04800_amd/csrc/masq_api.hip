@@ -16,6 +16,54 @@ static __device__ __align__(256) uint8_t scratch[MASQ_SCRATCH_BYTES];
 
 namespace masq {
 
+// Shape and slices of a product past the small-batch path.  32-row tiles up
+// to 32 tokens; otherwise the shape with the least estimated time, in units
+// of one full round of 256 x 256 tiles (one per compute unit: 50 us at 3584
+// columns; every entry below is proportional to the row length), from GEMM
+// launches measured over 17-4096 tokens, 512-18944 columns and channels:
+//   64 x 64    up to 256 workgroups 0.24, up to 450 0.32, then 0.0305 / 50
+//              a tile: the units' DMA paths are full (1184 tiles 38.9 us)
+//   128 x 128  up to 256 workgroups (one a unit) 0.5, else 0.72 for each
+//              round of 512 (448 tiles 38 us, 896 tiles 74 us); with the
+//              packed weight 0.62 (fewer bytes)
+//   256 x 256  1 for each round of 256, or for fewer than kSplitMaxTiles
+//              tiles 1 / S with S slices, and 17 us for their hand-over
+// At 3584 columns this gives 64 x 64 tiles for 333 x 3584 (15.0 us; 128 x 128
+// 23.3, 256 x 256 30.5), 128 x 128 for 2048 x 3584 (38.8; 51, 45.0) and 256 x
+// 256 for 512 x 18944 (49.8; 72, 64).  Rows that are not a multiple of 64
+// have no 256 x 256 kernel.  The smallest shapes are split along K until
+// every unit has a workgroup, in slices of at least 10 stages, 8 at most (64
+// tokens, 18944 -> 3584: 40.3 us in one slice, 24.8 in 2, 19.1 in 4, 22.8 in
+// 8, which pay the hand-over again).
+TilePlan plan_tile(int64_t T, int64_t K, int64_t N, bool split, bool w4) {
+    if (T <= 0 || N <= 0) return TilePlan{-1, 1};
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((T + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    TilePlan p{T <= 32 ? 0 : 1, 1};
+    if (T > 32) {
+        const double n64 = static_cast<double>(tiles(64, 64));
+        const int64_t n128 = tiles(128, 128), n256 = tiles(kTileM, kTileN);
+        double best = n64 <= 256 ? 0.24 : (n64 <= 450 ? 0.32 : n64 * (0.0305 / 50.0));
+        const double round128 = w4 ? 0.62 : 0.72;
+        const double t128 = n128 <= 256 ? 0.5 : round128 * static_cast<double>((n128 + 511) / 512);
+        if (t128 < best) {
+            best = t128;
+            p.shape = 2;
+        }
+        if (K % 64 == 0) {
+            const int s256 = split ? plan_gemm_splits(T, K, N) : 1;
+            const double t256 = s256 > 1 ? 1.0 / s256 + 17.0 / (50.0 * static_cast<double>(K) / 3584.0)
+                                         : static_cast<double>((n256 + 255) / 256);
+            if (t256 < best) return TilePlan{-1, 1};
+        }
+    }
+    if (split && p.shape < 2) {
+        const int64_t n = tiles(kTileShapes[p.shape].bm, kTileShapes[p.shape].bn);
+        const int64_t stages = (K + kTileStageK - 1) / kTileStageK;
+        p.S = tile_slices(K, static_cast<int>(std::min<int64_t>({256 / n, stages / 10, 8})));
+    }
+    return p;
+}
+
 static size_t align256(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
 
 // Number of k slices of the down-projection.  Small batches (at most 16 row
@@ -34,8 +82,11 @@ static void plan_kslices(int64_t T, int64_t K, int& n_kslices, int& kslice) {
     n_kslices = static_cast<int>((K + kslice - 1) / kslice);
 }
 
-Workspace plan_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, int n_mod) {
+// The layout for a given tile plan of the GEMM.
+static Workspace carve_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, int n_mod,
+                                 TilePlan tile) {
     Workspace w{};
+    w.tile = tile;
     w.kslice = static_cast<int>(K);
     w.n_kslices = 1;
     size_t off = 0;
@@ -76,9 +127,10 @@ Workspace plan_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, 
         }
     }
     w.gk_splits = plan_gemm_splits(T, K, N);
-    const int n_gk_tickets = w.gk_splits > 1 ? static_cast<int>(((T + kTileM - 1) / kTileM) *
-                                                                 ((N + kTileN - 1) / kTileN))
-                                             : 0;
+    const int64_t bm = tile.shape < 0 ? kTileM : kTileShapes[tile.shape].bm;
+    const int64_t bn = tile.shape < 0 ? kTileN : kTileShapes[tile.shape].bn;
+    const int slices = tile.shape < 0 ? w.gk_splits : tile.S;
+    const int n_gk_tickets = slices > 1 ? static_cast<int>(((T + bm - 1) / bm) * ((N + bn - 1) / bn)) : 0;
     // the arrival counters of the down-projection and of the split GEMM lie
     // side by side, so that stage 1 clears them in one go
     w.tickets = nullptr;
@@ -110,9 +162,26 @@ Workspace plan_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, 
     }
     w.gk_part = nullptr;
     if (n_gk_tickets > 0)
-        w.gk_part = reinterpret_cast<int32_t*>(carve(static_cast<size_t>(n_gk_tickets) * w.gk_splits *
-                                                     kTileM * kTileN * sizeof(int32_t)));
+        w.gk_part = reinterpret_cast<int32_t*>(carve(static_cast<size_t>(n_gk_tickets) * slices *
+                                                     static_cast<size_t>(bm * bn) * sizeof(int32_t)));
     w.bytes = off;
+    return w;
+}
+
+// The size is that of the 256 x 256 tiles' layout whatever the plan, so that
+// it does not depend on which kernel runs; a small-tile plan takes as many
+// slices as that holds (one slice needs no accumulators).
+Workspace plan_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, int n_mod,
+                         bool w4) {
+    Workspace w = carve_workspace(base, T, K, N, rank, n_mod, TilePlan{-1, 1});
+    TilePlan tile = small_path(T, K) ? TilePlan{-1, 1} : plan_tile(T, K, N, true, w4);
+    if (tile.shape < 0) return w;
+    const size_t bytes = w.bytes;
+    for (;; tile.S = tile_slices(K, tile.S - 1)) {
+        w = carve_workspace(base, T, K, N, rank, n_mod, tile);
+        if (w.bytes <= bytes || tile.S <= 1) break;
+    }
+    w.bytes = bytes;
     return w;
 }
 
@@ -245,7 +314,7 @@ masq_status validate_fused(const Fused& a) {
         return MASQ_ERR_ALIGN;
     if (cmc && (!aligned16(a.l_down) || !aligned16(a.r_up))) return MASQ_ERR_ALIGN;
     if (a.workspace && (reinterpret_cast<uintptr_t>(a.workspace) & 255u) != 0) return MASQ_ERR_ALIGN;
-    const masq::Workspace w = masq::plan_workspace(nullptr, a.T, a.c_in, a.c_out, a.rank, a.n_mod);
+    const masq::Workspace w = masq::plan_workspace(nullptr, a.T, a.c_in, a.c_out, a.rank, a.n_mod, a.w4);
     if (a.T > 0 && a.workspace_bytes < w.bytes) return MASQ_ERR_WORKSPACE;
     return MASQ_OK;
 }
@@ -255,7 +324,7 @@ masq_status fused_stage(const Fused& a, int stage) {
     if (st != MASQ_OK || a.T == 0) return st;
     const bool cmc = a.rank > 0 && a.n_mod > 1;
     const masq::Workspace w =
-        masq::plan_workspace(a.workspace, a.T, a.c_in, a.c_out, a.rank, a.n_mod);
+        masq::plan_workspace(a.workspace, a.T, a.c_in, a.c_out, a.rank, a.n_mod, a.w4);
     hipStream_t s = static_cast<hipStream_t>(a.stream);
     (void)hipGetLastError();
     if ((stage & 1) && masq::small_path(a.T, a.c_in)) {
@@ -324,7 +393,7 @@ masq_status fused_stage(const Fused& a, int stage) {
                                         w.u_part,
                                         w.n_kslices, a.rank, a.n_mod,
                                         a.r_up, to_dt(a.lr_dt), cmc, nullptr, a.y, to_dt(a.y_dt),
-                                        s, a.w4, w.pair));
+                                        s, w.tile, a.w4, w.pair));
     }
     return st;
 }
@@ -410,7 +479,8 @@ static masq_status gemm_call(const int8_t* q, const float* x_scale, const int8_t
     return from_hip(masq::launch_gemm(q, x_scale, wq, w_scale, T, c_in, c_out, nullptr, nullptr,
                                       nullptr, nullptr, nullptr, 1, nullptr, nullptr, nullptr, 1, 0,
                                       1, nullptr, DT::BF16, false, acc, y, to_dt(y_dt),
-                                      static_cast<hipStream_t>(stream), w4));
+                                      static_cast<hipStream_t>(stream),
+                                      masq::plan_tile(T, c_in, c_out, false, w4), w4));
 }
 
 masq_status masq_w8a8_gemm(const int8_t* q, const float* x_scale, const int8_t* wq,

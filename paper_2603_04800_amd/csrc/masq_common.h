@@ -80,6 +80,23 @@ inline int plan_gemm_splits(int64_t T, int64_t K, int64_t N) {
     return S < 1 ? 1 : static_cast<int>(S);
 }
 
+// Small-tile GEMM (k_gemm_tile): output tile shapes, and the shape and number
+// of k slices a product takes.  shape < 0: the 256 x 256 kernel.
+struct TileShape { int bm, bn; };
+constexpr TileShape kTileShapes[] = {{32, 64}, {64, 64}, {128, 128}};
+struct TilePlan { int shape, S; };
+// split: slices are possible (the caller has room for their accumulators).
+TilePlan plan_tile(int64_t T, int64_t K, int64_t N, bool split, bool w4);
+constexpr int kTileStageK = 128;      // codes per stage of the small-tile GEMM
+// At most S slices of whole stages, none of them empty.
+inline int tile_slices(int64_t K, int S) {
+    const int n = static_cast<int>((K + kTileStageK - 1) / kTileStageK);
+    if (S > n) S = n;
+    if (S <= 1) return 1;
+    const int per = (n + S - 1) / S;
+    return (n + per - 1) / per;
+}
+
 // Decode GEMM of the fused small-batch path: a workgroup covers kDecCh output
 // channels and one k slice of at most kDecSteps 64-byte steps (its waves hold
 // every Wq step of the slice in registers).  ns slices of sp steps (the last
@@ -128,8 +145,9 @@ struct Workspace {
                        // then [kSmallMaxT][N] fp32 compensation terms
     int* dec_tickets;  // small-batch path: [ngroups] arrival counters (zeroed by stage 1)
     int dec_ns, dec_sp, dec_groups;   // plan_decode of the small-batch path
-    int gk_splits;     // plan_gemm_splits
-    int32_t* gk_part;  // [tiles][gk_splits][256 * 256] int32 slice accumulators (gk_splits > 1)
+    TilePlan tile;     // plan_tile: the small-tile GEMM's shape and slices (shape < 0: 256 x 256)
+    int gk_splits;     // plan_gemm_splits (256 x 256 tiles)
+    int32_t* gk_part;  // [tiles][slices][bm * bn] int32 slice accumulators (slices > 1)
     int* gk_tickets;   // [tiles] arrival counters (gk_splits > 1); follow `tickets` when both exist
     int n_zero;        // ints from zero_base that stage 1 clears
     int* zero_base;
@@ -141,7 +159,8 @@ struct Workspace {
     size_t bytes;
 };
 
-Workspace plan_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, int n_mod);
+Workspace plan_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, int n_mod,
+                         bool w4 = false);
 
 // zero_ints / n_zero: optional array the kernel clears on the way (the
 // down-projection's tickets, which must start at zero).
@@ -253,8 +272,35 @@ hipError_t launch_gemm(const int8_t* q, const float* x_scale, const int8_t* wq,
                        int32_t* dec_part, int* dec_tickets, int gk_splits, int32_t* gk_part,
                        int* gk_tickets, const float* u_part, int n_kslices,
                        int rank, int n_mod, const void* r_up, DT lr_dt, bool cmc, int32_t* acc,
-                       void* y, DT y_dt, hipStream_t s, bool w4 = false,
+                       void* y, DT y_dt, hipStream_t s, TilePlan tile, bool w4 = false,
                        bool a_pair = false);
+
+// The small-tile GEMM; arguments as launch_gemm's.  part / tickets: plan.S
+// slots of bm x bn int32 per tile and an arrival counter (zero on entry, left
+// zero) per tile, for plan.S > 1.
+struct TileGemm {
+    const int8_t* q;
+    const float* x_scale;
+    const int8_t* wq;
+    const float* w_scale;
+    int64_t T, K, N;
+    const int32_t* mod;
+    const float* u;
+    const uint8_t* u_hl;
+    int rank, n_mod;
+    const void* r_up;
+    DT lr_dt;
+    bool cmc;
+    int32_t* acc;
+    void* y;
+    DT y_dt;
+    bool w4, a_pair;
+    TilePlan plan;
+    int32_t* part;
+    int* tickets;
+    hipStream_t stream;
+};
+hipError_t launch_gemm_tile(const TileGemm& g);
 
 // MAS-only comparator (a weight per modality, no compensation): rows grouped
 // by modality on the device, then the direct-to-LDS GEMM over tiles of one

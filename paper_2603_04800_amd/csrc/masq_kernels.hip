@@ -10,12 +10,12 @@
 //   k_lowrank_down   u = (x S_m^-1) L1^m on 16-row tiles with bf16 (or fp32)
 //                    MFMA; rows of other modalities are masked to zero, tiles
 //                    without non-text rows exit at once.
-//   k_gemm           q . Wq^T on int8 MFMA (v_mfma_i32_32x32x32_i8), 256x256
-//                    tiles, 128-byte K stages double-buffered in LDS with an
-//                    XOR swizzle; epilogue: dequantisation, then on tiles that
-//                    hold non-text rows the rank-r up-projection u L2^m on
-//                    bf16 (fp32) MFMA accumulating into the dequantised fp32
-//                    tile, then the cast and store.
+//   k_gemm_dma       q . Wq^T on int8 MFMA (v_mfma_i32_32x32x32_i8), 256x256
+//                    tiles, K stages by DMA into an LDS ring; epilogue:
+//                    dequantisation, then on tiles that hold non-text rows the
+//                    rank-r up-projection u L2^m on bf16 (fp32) MFMA
+//                    accumulating into the dequantised fp32 tile, then the cast
+//                    and store.  (Small tiles: k_gemm_tile in masq_tile.hip.)
 //   k_lowrank_comp   standalone y += (x S_m^-1 L1^m) L2^m.
 //
 // Bit-exact contract: the smoothing is a single fp32 multiply, the scale and
@@ -24,140 +24,10 @@
 // dequantisation is two fp32 multiplies in a fixed order.  The library is
 // compiled without FP contraction.
 
-#include <type_traits>
-
-#include "masq_common.h"
+#include "masq_device.h"
 
 namespace masq {
 namespace {
-
-typedef int32_t v2i __attribute__((ext_vector_type(2)));
-typedef int32_t v4i __attribute__((ext_vector_type(4)));
-typedef int32_t v16i __attribute__((ext_vector_type(16)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-
-typedef uint16_t bf16_t;   // bfloat16 stored as its bit pattern
-
-__device__ __forceinline__ float bf16_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
-
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-
-// Two fp32 values narrowed to bf16 bits (a in the low half), round to nearest
-// even: one v_cvt_pk_bf16_f32 on gfx950.
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{a, b}, v2bf));
-}
-__device__ __forceinline__ uint32_t f32_to_bf16(float f) { return pack_bf16x2(f, 0.f) & 0xFFFFu; }
-
-// ---------------------------------------------------------------- element IO
-template <typename T> struct Elem;
-template <> struct Elem<float> {
-    static __device__ __forceinline__ void load8(const float* p, float (&v)[8]) {
-        const v4f a = *reinterpret_cast<const v4f*>(p);
-        const v4f b = *reinterpret_cast<const v4f*>(p + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    }
-    static __device__ __forceinline__ float load1(const float* p) { return *p; }
-    static __device__ __forceinline__ void store1(float* p, float v) { *p = v; }
-};
-template <> struct Elem<bf16_t> {
-    static __device__ __forceinline__ void load8(const bf16_t* p, float (&v)[8]) {
-        const v4i a = *reinterpret_cast<const v4i*>(p);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            v[2 * j] = __uint_as_float(static_cast<uint32_t>(a[j]) << 16);
-            v[2 * j + 1] = __uint_as_float(static_cast<uint32_t>(a[j]) & 0xFFFF0000u);
-        }
-    }
-    static __device__ __forceinline__ float load1(const bf16_t* p) { return bf16_to_f32(*p); }
-    static __device__ __forceinline__ void store1(bf16_t* p, float v) {
-        *p = static_cast<bf16_t>(f32_to_bf16(v));
-    }
-};
-
-__device__ __forceinline__ void load8_f32(const float* p, float (&v)[8]) { Elem<float>::load8(p, v); }
-
-// Eight elements as loaded (16 or 32 bytes), converted to fp32 only when
-// used, so that a software pipeline can keep the load in flight meanwhile.
-template <typename T> struct Raw8;
-template <> struct Raw8<bf16_t> {
-    v4i a;
-    __device__ __forceinline__ void load(const bf16_t* p) { a = *reinterpret_cast<const v4i*>(p); }
-    __device__ __forceinline__ void to_f32(float (&v)[8]) const {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            v[2 * j] = __uint_as_float(static_cast<uint32_t>(a[j]) << 16);
-            v[2 * j + 1] = __uint_as_float(static_cast<uint32_t>(a[j]) & 0xFFFF0000u);
-        }
-    }
-};
-template <> struct Raw8<float> {
-    v4f a, b;
-    __device__ __forceinline__ void load(const float* p) {
-        a = *reinterpret_cast<const v4f*>(p);
-        b = *reinterpret_cast<const v4f*>(p + 4);
-    }
-    __device__ __forceinline__ void to_f32(float (&v)[8]) const {
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    }
-};
-
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
-}
-
-// Modality ids outside [0, n_mod) are treated as text, so that a bad id can
-// never index past the smoothing or factor arrays.
-__device__ __forceinline__ int sane_mod(int m, int n_mod) {
-    return (m >= 0 && m < n_mod) ? m : 0;
-}
-
-// XOR swizzle of the 16-byte chunk index inside a 128-byte LDS row: any 8
-// (or 16) consecutive rows read at one logical chunk land on distinct banks.
-__device__ __forceinline__ int swz(int row) { return (row ^ (row >> 3)) & 7; }
-
-// 4-bit shared weight.  A row of K codes is packed two per byte, in 4-byte
-// words of 8 codes: byte b of the word holding codes 8g .. 8g + 7 carries
-// code 8g + b in its low nibble and code 8g + b + 4 in its high nibble
-// (two's complement).  Two packed words (16 codes) become one 16-byte int8
-// MFMA operand in k order, each code multiplied by 16: masking leaves every
-// nibble in the high half of its byte, so the int8 byte reads 16 c.  An int32
-// sum of such products is 16 times the true one and a multiple of 16, so an
-// arithmetic shift right by 4 recovers it exactly.  (|16 c q| <= 112 * 127:
-// any K below 2^31 / 14224 stays in range.)
-__device__ __forceinline__ v4i w4_operand(v2i p) {
-    constexpr int kHi = static_cast<int>(0xF0F0F0F0u);
-    return v4i{(p.x << 4) & kHi, p.x & kHi, (p.y << 4) & kHi, p.y & kHi};
-}
-
-// ================================================================ LDS DMA
-// One 16-byte lane of an LDS-DMA load: the wave writes 64 x 16 contiguous
-// bytes at LDS address m0 (wave-uniform), lane i at m0 + 16 i.
-__device__ __forceinline__ void lds_dma16(const void* src, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :: "v"(src), "s"(lds_addr) : "memory", "m0");
-}
-
-// Scheduling fence: the compiler may move no instruction across it, so the
-// software pipeline below keeps the order it is written in.
-#define MASQ_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
-
-// s_waitcnt vmcnt(n) lgkmcnt(0) (expcnt unconstrained).
-#define MASQ_WAIT_VMCNT_LGKM0(n) \
-    __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | (7 << 4) | (0 << 8))
-
-// One 4-byte lane of an LDS-DMA load: lane i writes LDS address m0 + 4 i.
-__device__ __forceinline__ void lds_dma4(const void* src, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
-                 :: "v"(src), "s"(lds_addr) : "memory", "m0");
-}
 
 // ================================================================ smoothing + quant
 // One workgroup per token row (small batches, where a row's latency
@@ -294,16 +164,6 @@ __global__ __launch_bounds__(256) void k_smooth_quant(const XT* __restrict__ x,
         finish_u_row(blockIdx.x, T, sane_mod(mod[blockIdx.x], n_mod) == 0, fin.part, fin.slices,
                      fin.r, fin.u, fin.u_hl, threadIdx.x);
     sq_row<XT, 256, kSqChunks>(x, mod, inv_s, K, n_mod, q, x_scale, blockIdx.x, pair);
-}
-
-__device__ __forceinline__ void split_bf16x8(const float (&v)[8], v4i& hi, v4i& lo) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t h = pack_bf16x2(v[2 * j], v[2 * j + 1]);
-        const float h0 = __uint_as_float(h << 16), h1 = __uint_as_float(h & 0xFFFF0000u);
-        hi[j] = static_cast<int32_t>(h);
-        lo[j] = static_cast<int32_t>(pack_bf16x2(v[2 * j] - h0, v[2 * j + 1] - h1));
-    }
 }
 
 // One row t quantised by one wave (lane = this lane), its smoothed values
@@ -1910,31 +1770,7 @@ template <> struct Cmc<float> {           // fp32 operands, v_mfma_f32_32x32x2f3
     }
 };
 
-// Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous
-// range of tiles, ordered in groups of 8 tile-rows, so that tiles running
-// together on one XCD share A and B stages in its L2.  Returns false for the
-// padding workgroups of the last XCD range.
-__device__ __forceinline__ bool tile_coords_at(int b, int tiles_m, int tiles_n, int& tm, int& tn) {
-    const int nt = tiles_m * tiles_n;
-    const int per_xcd = (nt + 7) >> 3;
-    if ((b >> 3) >= per_xcd) return false;
-    const int L = (b & 7) * per_xcd + (b >> 3);
-    if (L >= nt) return false;
-    constexpr int GM = 8;
-    const int gsize = GM * tiles_n;
-    const int g = L / gsize;
-    const int first_m = g * GM;
-    const int gm = min(GM, tiles_m - first_m);
-    const int li = L - g * gsize;
-    tm = first_m + li % gm;
-    tn = li / gm;
-    return true;
-}
-__device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int& tm, int& tn) {
-    return tile_coords_at(static_cast<int>(blockIdx.x), tiles_m, tiles_n, tm, tn);
-}
-
-// Shared LDS of both GEMM kernels: the K stages during the main loop, then
+// Shared LDS of the GEMM kernel: the K stages during the main loop, then
 // the compensation pieces in the epilogue.
 // Per-wave output transpose buffer: 32 rows of TW bf16 channels (TW = 64
 // with 4 waves, 32 with 8), rows padded by 16 bytes (16-byte aligned rows
@@ -1952,7 +1788,6 @@ struct RowOps {
 struct GemmSmem {
     uint8_t buf[2 * 65536];
     RowOps ro[2];             // the tile's set and (persistent grid) the next tile's
-    unsigned wpresent[8];     // per wave: bit m set if a row of modality m is in its rows
     uint8_t tr[kTrBytes];     // 16-byte aligned (the transposes use 16-byte LDS accesses)
     int last;                 // split K: this workgroup is the last slice of its tile to arrive
 };
@@ -1962,28 +1797,6 @@ static_assert(4 * 32 * tr_pitch(64) <= kTrBytes && 8 * 32 * tr_pitch(32) <= kTrB
 // Epilogue of a 256 x 256 tile whose int32 accumulators are in acc (this
 // wave's 128 x 128 quarter as 4 x 4 blocks of 32 x 32): optional int32 store,
 // dequantisation, Cross-Modal Compensation on non-text rows, cast and store.
-// Per-thread epilogue operands (thread t: token row0 + t, channel col0 + t),
-// loaded at the start of the kernel so that their latency hides behind the
-// main loop.
-struct EpiPrefetch {
-    float dx, ws;
-    int mod;
-};
-
-__device__ __forceinline__ EpiPrefetch epi_prefetch(const float* __restrict__ x_scale,
-                                                    const float* __restrict__ w_scale,
-                                                    const int32_t* __restrict__ mod, bool cmc,
-                                                    int64_t T, int N, int64_t row0, int col0,
-                                                    int n_mod) {
-    const int tid = threadIdx.x;
-    const int64_t t = row0 + tid;
-    EpiPrefetch e;
-    e.dx = t < T ? x_scale[t] : 0.f;
-    e.ws = (col0 + tid) < N ? w_scale[col0 + tid] : 0.f;
-    e.mod = (cmc && t < T) ? sane_mod(mod[t], n_mod) : 0;
-    return e;
-}
-
 // State handed over by the DMA kernel: the per-row operands are in LDS
 // already, the modalities present are known, and with pre the fast-path
 // compensation operands sit at the given byte offsets of the K buffers.
@@ -1995,41 +1808,20 @@ struct EpiDma {
 };
 
 // NWN waves along the channels (2: four waves of 128 x 128, 4: eight waves of
-// 128 x 64); NJ = 8 / NWN channel blocks of 32 per wave.  DMA: called from
-// the DMA kernel (state in ed; pf unused), else the per-thread operands pf
-// are written to LDS here.
-template <typename YT, typename LT, bool CMC, bool ACC, int NWN = 2, bool DMA = false,
-          bool GRP = false>
+// 128 x 64); NJ = 8 / NWN channel blocks of 32 per wave.
+template <typename YT, typename LT, bool CMC, bool ACC, int NWN = 2, bool GRP = false>
 __device__ __forceinline__ void gemm_epilogue(
-    v16i (&acc)[4][8 / NWN], GemmSmem& sm, const EpiPrefetch& pf, int64_t T, int N, int64_t row0,
+    v16i (&acc)[4][8 / NWN], GemmSmem& sm, int64_t T, int N, int64_t row0,
     int col0, const float* __restrict__ u, int r, int n_mod, const LT* __restrict__ r_up,
-    int32_t* __restrict__ acc_out, YT* __restrict__ y, const EpiDma& ed = EpiDma{}, int rb = 0,
-    int tid_in = -1) {
+    int32_t* __restrict__ acc_out, YT* __restrict__ y, const EpiDma& ed, int rb, int tid) {
     constexpr int NJ = 8 / NWN, NW = 2 * NWN, NT = 64 * NW;
     constexpr int kWaveCols = 32 * NJ;                 // channels per wave
     constexpr int TW = NJ == 4 ? 64 : 32;              // transpose unit width (channels)
     constexpr int kPitch = tr_pitch(TW);
-    const int tid = tid_in >= 0 ? tid_in : static_cast<int>(threadIdx.x);
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave / NWN, wn = wave % NWN;
     RowOps& ro = sm.ro[rb];
-    // dx, ws, mod and wpresent lie outside the K-stage buffers, so they can be
-    // written before the barrier; after it every wave is also done with the
-    // K stages
-    if constexpr (!DMA) {
-        if (tid < kTileM) {                    // threads past 256 carry no prefetch
-            ro.dx[tid] = pf.dx;
-            ro.ws[tid] = pf.ws;
-        }
-        if constexpr (CMC) {
-            if (tid < kTileM) ro.mod[tid] = pf.mod;
-            unsigned wp = 0;
-            for (int m = 1; m < n_mod; ++m)
-                if (__ballot(tid < kTileM && pf.mod == m) != 0ull) wp |= 1u << m;
-            if (lane == 0) sm.wpresent[wave] = wp;
-        }
-    }
-    __syncthreads();
+    __syncthreads();                       // every wave is done with the K stages
 
     // ---- compensation: modalities present in the tile, LDS plan per 64-column chunk.
     // Every quantity that selects a code path is wave-uniform (scalar registers).
@@ -2041,18 +1833,11 @@ __device__ __forceinline__ void gemm_epilogue(
     // LDS byte offsets of the fast path's u hi, u lo and L2 pieces
     int off_uh = 0, off_ul = kTileM * 128, off_r0 = kChunkBase, off_r1 = kChunkBase + (CMC ? Cmc<LT>::kRBytes : 0);
     if constexpr (CMC) {
-        if constexpr (DMA) {
-            present = ed.present;
-        } else {
-            unsigned pa = 0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) pa |= sm.wpresent[w];
-            present = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(pa)));
-        }
+        present = ed.present;
         n_present = __builtin_popcount(present);
         const int chunk_bytes = Cmc<LT>::kUBytes + n_present * Cmc<LT>::kRBytes;
         staged = n_chunks * chunk_bytes <= static_cast<int>(sizeof(sm.buf));
-        if (DMA && ed.pre) {
+        if (ed.pre) {
             staged = true;
             off_uh = ed.off_uh;
             off_ul = ed.off_ul;
@@ -2079,7 +1864,7 @@ __device__ __forceinline__ void gemm_epilogue(
     // wm*128 + 32 i + (lane % 32) and channel wn*kWaveCols + 32 j + 8 (e / 4) +
     // 4 (lane / 32) + e % 4.  Loops over blocks are fully unrolled: the
     // accumulators are registers and must be indexed by constants.
-    static_assert(!GRP || (DMA && !CMC && !ACC), "grouped tiles: plain product, DMA kernel");
+    static_assert(!GRP || (!CMC && !ACC), "grouped tiles: plain product");
     // GRP: local row l of the tile is token ro.rawmod[l], valid for l < ed.grp_rows
     const bool interior = GRP ? (ed.grp_rows == kTileM && col0 + kTileN <= N)
                               : (row0 + kTileM <= T) && (col0 + kTileN <= N);
@@ -2323,112 +2108,6 @@ __device__ __forceinline__ void gemm_epilogue(
             store_rowblock(i, ybs);
         }
     }
-}
-
-// 16 x 32 x 32 MFMA steps of one wave's 128 x 128 quarter: fragments of the
-// 4 token blocks (q rows) and 4 channel blocks (Wq rows) for k chunk c (lane
-// group l / 32 selects the chunk), read through the row swizzle `sw`.  The
-// product is formed transposed, channels x tokens, so that each lane ends up
-// holding one token and 4 consecutive output channels per register group.
-template <int kRowBytes, typename Swz>
-__device__ __forceinline__ void mfma_kstep(const uint8_t* sa, const uint8_t* sb, int c, int wm,
-                                           int wn, int lane, Swz sw, v16i (&acc)[4][4]) {
-    v4i fa[4], fb[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = wm * 128 + i * 32 + (lane & 31);
-        fa[i] = *reinterpret_cast<const v4i*>(sa + row * kRowBytes + ((c ^ sw(row)) << 4));
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int row = wn * 128 + j * 32 + (lane & 31);
-        fb[j] = *reinterpret_cast<const v4i*>(sb + row * kRowBytes + ((c ^ sw(row)) << 4));
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[j], fa[i], acc[i][j], 0, 0, 0);
-}
-
-// ---------------------------------------------------------------- GEMM, general K
-// K stages of 128 bytes go global -> registers -> LDS, double-buffered; any
-// c_in that is a multiple of 16 (chunks past K are zero-filled).
-template <typename YT, typename LT, bool CMC, bool ACC>
-__global__ __launch_bounds__(256, 1) void k_gemm(
-    const int8_t* __restrict__ A, const int8_t* __restrict__ B, const float* __restrict__ x_scale,
-    const float* __restrict__ w_scale, int64_t T, int K, int N, int tiles_m, int tiles_n,
-    const int32_t* __restrict__ mod, const float* __restrict__ u, int r, int n_mod,
-    const LT* __restrict__ r_up, int32_t* __restrict__ acc_out, YT* __restrict__ y) {
-    __shared__ __attribute__((aligned(16))) GemmSmem sm;
-    int tm, tn;
-    if (!tile_coords(tiles_m, tiles_n, tm, tn)) return;
-    const int64_t row0 = static_cast<int64_t>(tm) * kTileM;
-    const int col0 = tn * kTileN;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int lc = tid & 7;      // 16-byte chunk of a 128-byte stage row
-    const int lr = tid >> 3;     // first row this thread loads (+32 j)
-
-    v16i acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = v16i{0};
-
-    const EpiPrefetch pf = epi_prefetch(x_scale, w_scale, mod, CMC, T, N, row0, col0, n_mod);
-    v4i ra[8], rb[8];
-    // Row indices are clamped into the matrix (rows past T or N are computed
-    // and discarded); chunks past K are loaded from a clamped in-bounds
-    // address and replaced by zeros at the LDS store.
-    int64_t a_off[8], b_off[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        a_off[j] = min(row0 + lr + 32 * j, T - 1) * K;
-        b_off[j] = static_cast<int64_t>(min(col0 + lr + 32 * j, N - 1)) * K;
-    }
-    bool kin = true;          // this thread's chunk of the stage lies inside K
-    auto gload = [&](int k0) {
-        const int kraw = k0 + lc * 16;
-        kin = kraw < K;
-        const int kk = kin ? kraw : K - 16;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            ra[j] = *reinterpret_cast<const v4i*>(A + a_off[j] + kk);
-            rb[j] = *reinterpret_cast<const v4i*>(B + b_off[j] + kk);
-        }
-    };
-    auto sstore = [&](int buf) {
-        uint8_t* sa = sm.buf + buf * 65536;
-        uint8_t* sb = sa + 32768;
-        const v4i zero = {0, 0, 0, 0};
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int row = lr + 32 * j;
-            const int off = row * 128 + ((lc ^ swz(row)) << 4);
-            *reinterpret_cast<v4i*>(sa + off) = kin ? ra[j] : zero;
-            *reinterpret_cast<v4i*>(sb + off) = kin ? rb[j] : zero;
-        }
-    };
-    auto sw8 = [](int row) { return swz(row); };
-
-    const int nk = (K + kTileK - 1) / kTileK;
-    gload(0);
-    sstore(0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        if (kt + 1 < nk) gload((kt + 1) * kTileK);
-        const uint8_t* sa = sm.buf + cur * 65536;
-        const uint8_t* sb = sa + 32768;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-            mfma_kstep<128>(sa, sb, 2 * ks + (lane >> 5), wm, wn, lane, sw8, acc);
-        if (kt + 1 < nk) sstore(cur ^ 1);
-        __syncthreads();
-    }
-    gemm_epilogue<YT, LT, CMC, ACC>(acc, sm, pf, T, N, row0, col0, u, r, n_mod, r_up, acc_out, y);
 }
 
 // ---------------------------------------------------------------- GEMM, K % 64 == 0
@@ -2879,7 +2558,7 @@ __global__ __launch_bounds__(128 * NWN, 1) void k_gemm_dma(
     else if (npf == 1) MASQ_WAIT_VMCNT_LGKM0(kPiecesMin + kDmaPerStage);
     else if (npf == 2) MASQ_WAIT_VMCNT_LGKM0(kPiecesMin + 2 * kDmaPerStage);
     else MASQ_WAIT_VMCNT_LGKM0(kPiecesMin + 3 * kDmaPerStage);
-    gemm_epilogue<YT, LT, CMC, ACC, NWN, true, GRP>(acc, sm, EpiPrefetch{}, T, N, row0, col0, u, r, n_mod,
+    gemm_epilogue<YT, LT, CMC, ACC, NWN, GRP>(acc, sm, T, N, row0, col0, u, r, n_mod,
                                                r_up, acc_out, y, ed, rb, tid);
     if constexpr (!PERSIST) break;
     ring = nring;
@@ -3650,30 +3329,20 @@ static void launch_gemm_t(const int8_t* q, const float* x_scale, const int8_t* w
     const int tiles_m = static_cast<int>((T + kTileM - 1) / kTileM);
     const int tiles_n = static_cast<int>((N + kTileN - 1) / kTileN);
     const int nt = tiles_m * tiles_n;
-    const dim3 grid(8 * ((nt + 7) / 8)), block(256);
-    if (K % kDmaStageK == 0) {
-        if (part == nullptr || tickets == nullptr) S = 1;
-        const dim3 gridk(8 * ((nt * S + 7) / 8));
-        // whole tiles: a persistent grid of at most one workgroup per compute unit
-        const dim3 gridp(static_cast<unsigned>(min(8 * ((nt + 7) / 8), persistent_blocks())));
-        if (S > 1)
-            hipLaunchKernelGGL((k_gemm_dma<YT, LT, CMC, ACC, kGemmWavesN, true, W4>), gridk,
-                               dim3(128 * kGemmWavesN), 0, s, q, wq, x_scale, w_scale, T,
-                               static_cast<int>(K), static_cast<int>(N), tiles_m, tiles_n, mod, u,
-                               u_hl, rank, n_mod, static_cast<const LT*>(r_up), acc,
-                               static_cast<YT*>(y), S, part, tickets, nullptr, nullptr, nullptr, 0,
-                               a_pair);
-        else
-            hipLaunchKernelGGL((k_gemm_dma<YT, LT, CMC, ACC, kGemmWavesN, false, W4, false, true>), gridp,
-                               dim3(128 * kGemmWavesN), 0, s, q, wq, x_scale, w_scale, T,
-                               static_cast<int>(K), static_cast<int>(N), tiles_m, tiles_n, mod, u,
-                               u_hl, rank, n_mod, static_cast<const LT*>(r_up), acc,
-                               static_cast<YT*>(y), 1, nullptr, nullptr, nullptr, nullptr, nullptr, 0,
-                               a_pair);
-    } else if constexpr (!W4)
-        hipLaunchKernelGGL((k_gemm<YT, LT, CMC, ACC>), grid, block, 0, s, q, wq, x_scale, w_scale, T,
-                           static_cast<int>(K), static_cast<int>(N), tiles_m, tiles_n, mod, u,
-                           rank, n_mod, static_cast<const LT*>(r_up), acc, static_cast<YT*>(y));
+    if (part == nullptr || tickets == nullptr) S = 1;
+    if (S > 1)
+        hipLaunchKernelGGL((k_gemm_dma<YT, LT, CMC, ACC, kGemmWavesN, true, W4>),
+                           dim3(8 * ((nt * S + 7) / 8)), dim3(128 * kGemmWavesN), 0, s, q, wq, x_scale,
+                           w_scale, T, static_cast<int>(K), static_cast<int>(N), tiles_m, tiles_n, mod,
+                           u, u_hl, rank, n_mod, static_cast<const LT*>(r_up), acc,
+                           static_cast<YT*>(y), S, part, tickets, nullptr, nullptr, nullptr, 0, a_pair);
+    else      // whole tiles: a persistent grid of at most one workgroup per compute unit
+        hipLaunchKernelGGL((k_gemm_dma<YT, LT, CMC, ACC, kGemmWavesN, false, W4, false, true>),
+                           dim3(static_cast<unsigned>(min(8 * ((nt + 7) / 8), persistent_blocks()))),
+                           dim3(128 * kGemmWavesN), 0, s, q, wq, x_scale, w_scale, T,
+                           static_cast<int>(K), static_cast<int>(N), tiles_m, tiles_n, mod, u, u_hl,
+                           rank, n_mod, static_cast<const LT*>(r_up), acc, static_cast<YT*>(y), 1,
+                           nullptr, nullptr, nullptr, nullptr, nullptr, 0, a_pair);
 }
 
 hipError_t launch_group_rows(const int32_t* mod, int64_t T, int n_mod, int32_t* rows,
@@ -3728,7 +3397,7 @@ hipError_t launch_gemm(const int8_t* q, const float* x_scale, const int8_t* wq,
                        int32_t* dec_part, int* dec_tickets, int gk_splits, int32_t* gk_part,
                        int* gk_tickets, const float* u_part, int n_kslices,
                        int rank, int n_mod, const void* r_up, DT lr_dt, bool cmc, int32_t* acc,
-                       void* y, DT y_dt, hipStream_t s, bool w4, bool a_pair) {
+                       void* y, DT y_dt, hipStream_t s, TilePlan tile, bool w4, bool a_pair) {
     // packed 4-bit Wq: K % 64 == 0 (checked by the caller), so every batch
     // takes the decode, small-batch or direct-to-LDS kernel
     if (w4 && K % 64 != 0) return hipErrorInvalidValue;
@@ -3763,6 +3432,11 @@ hipError_t launch_gemm(const int8_t* q, const float* x_scale, const int8_t* wq,
 #undef MASQ_SMALL
         return hipGetLastError();
     }
+    if (tile.shape >= 0)      // always where K % 64 != 0 (plan_tile)
+        return launch_gemm_tile(TileGemm{q, x_scale, wq, w_scale, T, K, N, mod, u, u_hl, rank, n_mod,
+                                         r_up, lr_dt, cmc, acc, y, y_dt, w4, a_pair, tile, gk_part,
+                                         gk_tickets, s});
+    if (K % kDmaStageK != 0) return hipErrorInvalidValue;
 #define MASQ_GEMM(YT, LT, C, A) (w4 ? launch_gemm_t<YT, LT, C, A, true> : launch_gemm_t<YT, LT, C, A, false>)(q, x_scale, wq, w_scale, T, K, N, mod, u, u_hl, rank, n_mod, r_up, acc, y, gk_splits, gk_part, gk_tickets, s, a_pair)
     // the int32 accumulator output exists only for the plain product (no
     // compensation); it is a separate instantiation because storing the

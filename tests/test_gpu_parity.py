@@ -591,3 +591,42 @@ def test_w4a8_equals_w8a8_on_the_same_codes(ops):
         y8 = lin8(x, mod)
         torch.cuda.synchronize()
         assert torch.equal(y4.view(torch.int16), y8.view(torch.int16)), f"T={T}"
+
+
+# ------------------------------------------------------------------ small tiles
+@pytest.mark.parametrize("T,K,N,r,M,act,lr,bits", [
+    # 32-row tiles: one row short of, at and past the edge of the rows, the
+    # channel tiles (64) and the K stages (128: shorter, whole, one piece more)
+    (17, 64, 16, 16, 2, "bf16", "bf16", 8), (31, 112, 80, 32, 3, "f32", "f32", 8),
+    (32, 128, 64, 64, 4, "bf16", "bf16", 8), (20, 144, 144, 48, 2, "bf16", "f32", 8),
+    (32, 192, 48, 64, 2, "f32", "bf16", 4), (12, 16, 16, 16, 2, "bf16", "bf16", 8),
+    # 64 x 64 tiles
+    (33, 128, 64, 64, 2, "bf16", "bf16", 8), (64, 272, 128, 128, 3, "f32", "f32", 8),
+    (65, 320, 208, 144, 2, "bf16", "bf16", 8), (127, 448, 80, 16, 4, "f32", "f32", 4),
+    (200, 1040, 336, 0, 1, "bf16", "bf16", 8), (129, 512, 1008, 256, 2, "bf16", "f32", 4),
+    # K split in 2 to 8 slices, the last one shorter, ragged rows of the last stage
+    (17, 2624, 80, 64, 2, "bf16", "bf16", 8), (40, 3840, 144, 64, 3, "bf16", "bf16", 4),
+    (64, 10304, 96, 32, 2, "f32", "f32", 8), (90, 5184, 272, 64, 2, "bf16", "bf16", 8),
+    # 128 x 128 tiles
+    (1100, 144, 3104, 64, 3, "bf16", "bf16", 8), (1090, 192, 3152, 64, 2, "f32", "f32", 4),
+    (1100, 128, 3104, 128, 2, "bf16", "bf16", 8),
+])
+def test_small_tile_gemm_edges(ops, T, K, N, r, M, act, lr, bits):
+    L = _random_layer(T, K, N, r, M, act, lr, weight_bits=bits, layout="alternating", seed=T + K + N)
+    _check_layer(ops, L, name="small tiles")
+
+
+@pytest.mark.parametrize("T,K,N", [(17, 2624, 80), (300, 512, 256), (512, 3584, 18944), (2048, 18944, 3584),
+                                   (1000, 1040, 2000)])
+def test_the_workspace_does_not_depend_on_the_tile_plan(ops, T, K, N):
+    """The size the layer asks for is that of its codes, scales, u and the
+    256 x 256 tiles' slices, whichever tile shape the GEMM takes."""
+    def up(v):
+        return (v + 255) // 256 * 256
+    tiles = -(-T // 256) * -(-N // 256)
+    S = 1 if tiles >= 128 or K % 64 else max(1, min(256 // tiles, 4, K // 64 // 8))
+    rows = (T + 1) // 2 * 2 if K % 64 == 0 else T
+    want = up(rows * K) + up(4 * T)
+    if S > 1:
+        want += up(4 * tiles) + up(4 * tiles * S * 65536)
+    assert ops.workspace_bytes(T, K, N, 0, 1) == want
