@@ -266,6 +266,10 @@ __global__ __launch_bounds__(256) void k_smooth_quant_rows(const XT* __restrict_
 // sums are added across waves in LDS in a fixed order.  Rows whose modality
 // is not m contribute zeros.  MFMA operand layout: lane l holds row/column
 // (l % 16) and the k group (l / 16); A and B use the same k assignment.
+// The instructions of a round stand in one block of code: column blocks past
+// the group's and steps past the range multiply zeros (or repeat a column
+// block whose result is dropped).  A branch between an MFMA and the next
+// read of its result has been compiled without the wait that the read needs.
 template <typename XT, typename LT> struct DownK;
 
 // bf16 factors: the smoothed row enters as two bf16 terms, hi = bf16(xs) and
@@ -274,21 +278,27 @@ template <typename XT, typename LT> struct DownK;
 template <typename XT> struct DownK<XT, bf16_t> {
     static constexpr int kStep = 32;
     static constexpr int kUnroll = 4;
+    template <int RG>
     static __device__ __forceinline__ void run(const XT* x, const float* inv_s_m,
                                                const bf16_t* ld_m, int64_t row0, int64_t T,
                                                int K, int kb, int ke, int c0, int ncb,
-                                               const int* smod, int m, v4f (&acc)[4], int lane) {
+                                               const int* smod, int m, v4f (&acc)[RG][4], int lane) {
         const int ar = lane & 15, kg = lane >> 4;
-        const int64_t t = row0 + ar;
-        const bool live = (t < T) && (smod[ar] == m);
-        const XT* xrow = x + (live ? t : row0) * static_cast<int64_t>(K);
+        bool live[RG];
+        const XT* xrow[RG];
+#pragma unroll
+        for (int g = 0; g < RG; ++g) {
+            const int64_t t = row0 + 16 * g + ar;
+            live[g] = t < T && smod[16 * g + ar] == m;
+            xrow[g] = x + (live[g] ? t : row0) * static_cast<int64_t>(K);
+        }
         const bf16_t* lrow[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             lrow[j] = ld_m + static_cast<int64_t>(c0 + 16 * min(j, ncb - 1) + ar) * K;
         const v4i zero = {0, 0, 0, 0};
         for (int k0 = kb; k0 < ke; k0 += kStep * kUnroll) {
-            float xv[kUnroll][8], sv[kUnroll][8];
+            float xv[kUnroll][RG][8], sv[kUnroll][8];
             v4i bv[kUnroll][4];
             bool ok[kUnroll];
 #pragma unroll
@@ -296,71 +306,116 @@ template <typename XT> struct DownK<XT, bf16_t> {
                 const int k = k0 + kStep * u + 8 * kg;
                 ok[u] = k < ke;
                 const int kc = ok[u] ? k : ke - 8;
-                Elem<XT>::load8(xrow + kc, xv[u]);
+#pragma unroll
+                for (int g = 0; g < RG; ++g) Elem<XT>::load8(xrow[g] + kc, xv[u][g]);
                 load8_f32(inv_s_m + kc, sv[u]);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) bv[u][j] = *reinterpret_cast<const v4i*>(lrow[j] + kc);
             }
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
-                if (k0 + kStep * u >= ke) break;
-                float xs[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) xs[e] = xv[u][e] * sv[u][e];
-                v4i hi, lo;
-                split_bf16x8(xs, hi, lo);
-                const bool use = live && ok[u];
-                hi = use ? hi : zero;
-                lo = use ? lo : zero;
+                for (int g = 0; g < RG; ++g) {
+                    float xs[8];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (j >= ncb) break;
-                    const v4i b = ok[u] ? bv[u][j] : zero;
-                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(v8bf, hi), __builtin_bit_cast(v8bf, b), acc[j], 0, 0, 0);
-                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(v8bf, lo), __builtin_bit_cast(v8bf, b), acc[j], 0, 0, 0);
+                    for (int e = 0; e < 8; ++e) xs[e] = xv[u][g][e] * sv[u][e];
+                    v4i hi, lo;
+                    split_bf16x8(xs, hi, lo);
+                    const bool use = live[g] && ok[u];
+                    hi = use ? hi : zero;
+                    lo = use ? lo : zero;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const v4i b = ok[u] ? bv[u][j] : zero;
+                        acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(v8bf, hi), __builtin_bit_cast(v8bf, b), acc[g][j], 0, 0, 0);
+                        acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(v8bf, lo), __builtin_bit_cast(v8bf, b), acc[g][j], 0, 0, 0);
+                    }
                 }
             }
         }
     }
 };
 
-template <typename XT> struct DownK<XT, float> {   // fp32 factors: fp32 MFMA
-    static constexpr int kStep = 4;
+// Four elements as fp32 (16-byte aligned rows of a multiple of 16 elements).
+__device__ __forceinline__ v4f load4(const float* p) { return *reinterpret_cast<const v4f*>(p); }
+__device__ __forceinline__ v4f load4(const bf16_t* p) {
+    const v2i a = *reinterpret_cast<const v2i*>(p);
+    return v4f{__uint_as_float(static_cast<uint32_t>(a.x) << 16),
+               __uint_as_float(static_cast<uint32_t>(a.x) & 0xFFFF0000u),
+               __uint_as_float(static_cast<uint32_t>(a.y) << 16),
+               __uint_as_float(static_cast<uint32_t>(a.y) & 0xFFFF0000u)};
+}
+
+// fp32 factors: fp32 MFMA, 16 k in four instructions.  Lane group kg holds
+// columns 4 kg .. 4 kg + 3 of the 16 (one 16-byte load a row) and instruction
+// e takes each group's column e: any assignment serves as long as both
+// operands share it.  (One column a lane and instruction, loaded 4 bytes at a
+// time, took 9.6 us for 64 non-text rows of 512; latency bound.)
+template <typename XT> struct DownK<XT, float> {
+    static constexpr int kStep = 16;
+    static constexpr int kUnroll = 4;
+    template <int RG>
     static __device__ __forceinline__ void run(const XT* x, const float* inv_s_m,
                                                const float* ld_m, int64_t row0, int64_t T, int K,
                                                int kb, int ke, int c0, int ncb, const int* smod,
-                                               int m, v4f (&acc)[4], int lane) {
+                                               int m, v4f (&acc)[RG][4], int lane) {
         const int ar = lane & 15, kg = lane >> 4;
-        const int64_t t = row0 + ar;
-        const bool live = (t < T) && (smod[ar] == m);
-        const XT* xrow = x + (live ? t : row0) * static_cast<int64_t>(K);
-        for (int k0 = kb; k0 < ke; k0 += kStep) {
-            const int k = k0 + kg;
-            const bool ok = k < ke;
-            const int kc = ok ? k : ke - 1;
-            const float xs = Elem<XT>::load1(xrow + kc) * inv_s_m[kc];
-            const float a = (live && ok) ? xs : 0.f;
+        bool live[RG];
+        const XT* xrow[RG];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (j >= ncb) break;
-                const float b = ok ? ld_m[static_cast<int64_t>(c0 + 16 * j + ar) * K + kc] : 0.f;
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[j], 0, 0, 0);
+        for (int g = 0; g < RG; ++g) {
+            const int64_t t = row0 + 16 * g + ar;
+            live[g] = t < T && smod[16 * g + ar] == m;
+            xrow[g] = x + (live[g] ? t : row0) * static_cast<int64_t>(K);
+        }
+        const float* lrow[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            lrow[j] = ld_m + static_cast<int64_t>(c0 + 16 * min(j, ncb - 1) + ar) * K;
+        for (int k0 = kb; k0 < ke; k0 += kStep * kUnroll) {       // kb, ke: multiples of 16
+            v4f xv[kUnroll][RG], sv[kUnroll], bv[kUnroll][4];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {                   // all loads first
+                const int k = min(k0 + kStep * u, ke - kStep) + 4 * kg;
+                sv[u] = load4(inv_s_m + k);
+#pragma unroll
+                for (int g = 0; g < RG; ++g) xv[u][g] = load4(xrow[g] + k);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) bv[u][j] = load4(lrow[j] + k);
+            }
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                const bool in = k0 + kStep * u < ke;
+#pragma unroll
+                for (int g = 0; g < RG; ++g)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float xs = xv[u][g][e] * sv[u][e];
+                        const float a = live[g] && in ? xs : 0.f;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[u][j][e], acc[g][j], 0, 0, 0);
+                    }
             }
         }
     }
 };
 
-// The 16 x rc block of u (rank columns c0..c0+rc) over k in [kb, ke), summed
-// over the modalities present, written as red-reduced fp32 to out(row, col).
-template <int NW, typename XT, typename LT, typename Out>
+// The 16 RG x rc block of u (rank columns c0..c0+rc) over k in [kb, ke),
+// summed over the modalities present, written as red-reduced fp32 to
+// out(row, col).
+template <int NW, int RG, typename XT, typename LT, typename Out>
 __device__ __forceinline__ void down_group(const XT* x, const float* inv_s, const LT* l_down,
                                            int64_t row0, int64_t T, int K, int r, int n_mod,
                                            int kb, int ke, int c0, const int* smod,
-                                           unsigned present, float (*red)[kRowsDown][64],
+                                           unsigned present, float (*red)[kRowsDown * RG][64],
                                            Out out) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // wave-uniform k range (scalar registers), so that the loops branch on
+    // it: MFMA instructions ignore EXEC and must not sit under a lane mask
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rc = min(64, r - c0);
     const int ncb = rc >> 4;
     constexpr int step = DownK<XT, LT>::kStep;
@@ -368,23 +423,28 @@ __device__ __forceinline__ void down_group(const XT* x, const float* inv_s, cons
     const int q = ((span + NW * step - 1) / (NW * step)) * step;  // k per wave, step-aligned
     const int wkb = min(ke, kb + wave * q);
     const int wke = min(ke, wkb + q);
-    v4f acc[4];
+    v4f acc[RG][4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int g = 0; g < RG; ++g)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[g][j] = v4f{0.f, 0.f, 0.f, 0.f};
     for (int m = 1; m < n_mod; ++m) {
         if (!(present & (1u << m))) continue;
-        DownK<XT, LT>::run(x, inv_s + static_cast<int64_t>(m) * K,
-                           l_down + static_cast<int64_t>(m - 1) * r * K, row0, T, K, wkb, wke,
-                           c0, ncb, smod, m, acc, lane);
+        DownK<XT, LT>::template run<RG>(x, inv_s + static_cast<int64_t>(m) * K,
+                                        l_down + static_cast<int64_t>(m - 1) * r * K, row0, T, K, wkb,
+                                        wke, c0, ncb, smod, m, acc, lane);
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if (j >= ncb) break;
+    for (int g = 0; g < RG; ++g)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) red[wave][4 * (lane >> 4) + i][16 * j + (lane & 15)] = acc[j][i];
-    }
+        for (int j = 0; j < 4; ++j) {
+            if (j >= ncb) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                red[wave][16 * g + 4 * (lane >> 4) + i][16 * j + (lane & 15)] = acc[g][j][i];
+        }
     __syncthreads();
-    for (int idx = tid; idx < kRowsDown * rc; idx += 64 * NW) {
+    for (int idx = tid; idx < kRowsDown * RG * rc; idx += 64 * NW) {
         const int row = idx / rc, col = idx - row * rc;
         float v = red[0][row][col];
 #pragma unroll
@@ -394,10 +454,11 @@ __device__ __forceinline__ void down_group(const XT* x, const float* inv_s, cons
     __syncthreads();
 }
 
+template <int ROWS = kRowsDown>
 __device__ __forceinline__ unsigned tile_presence(const int* smod) {
     unsigned present = 0;
 #pragma unroll
-    for (int i = 0; i < kRowsDown; ++i)
+    for (int i = 0; i < ROWS; ++i)
         if (smod[i] > 0) present |= 1u << smod[i];
     return present;
 }
@@ -434,7 +495,7 @@ __device__ __forceinline__ void down_tile_in(const XT* __restrict__ x, const int
     if (!present) return;                                            // uniform per tile
     float* out = n_kslices > 1 ? u_part + static_cast<int64_t>(s) * T * r : u;
     for (int c0 = 0; c0 < r; c0 += 64)
-        down_group<NW, XT, LT>(x, inv_s, l_down, row0, T, K, r, n_mod, kb, ke, c0, smod, present,
+        down_group<NW, 1, XT, LT>(x, inv_s, l_down, row0, T, K, r, n_mod, kb, ke, c0, smod, present,
                                red, [&](int row, int col, float v) {
                                    const int64_t t = row0 + row;
                                    if (t < T) out[t * r + col] = v;
@@ -1514,38 +1575,89 @@ __global__ __launch_bounds__(64 * kFrWaves) void k_stage1_fr(
 }
 
 // ================================================================ standalone CMC
+// y += (x S_m^-1 L1^m) L2^m on the non-text rows.  Grid (32-row tiles, groups
+// of `per` 32-channel blocks): a workgroup forms its tile's u in LDS (8 waves
+// splitting K), then each wave takes every eighth channel block of its group
+// on v_mfma_f32_32x32x2_f32, u and L2 in fp32 (bf16 factors widened exactly).
+// There is no scratch to hand u over in, so every group forms it again; that
+// costs its L1 reads (r K factors a workgroup, from L2) and buys a full chip
+// where T / 32 tiles would leave most of it idle.  One lane a channel and
+// scalar fma, 16 rows a workgroup: 2081 us for 1000 x 1040 -> 2000, rank 128
+// in fp32, and 4.6 ms for 8192 x 3584 -> 3584, rank 64 in bf16; in this form
+// 42 and 147 us.
+constexpr int kCompRows = 32;
+constexpr int kCompWaves = 8;
+constexpr int kCompPad = 4;             // floats after a u row: rows start on different banks
+
+// Rank columns k .. k + 7 of a channel's L2 row.
+__device__ __forceinline__ void load8_any(const float* p, float (&v)[8]) { load8_f32(p, v); }
+__device__ __forceinline__ void load8_any(const bf16_t* p, float (&v)[8]) { Elem<bf16_t>::load8(p, v); }
+
 template <typename XT, typename LT, typename YT>
-__global__ __launch_bounds__(256) void k_lowrank_comp(const XT* __restrict__ x,
+__global__ __launch_bounds__(64 * kCompWaves) void k_lowrank_comp(const XT* __restrict__ x,
                                                       const int32_t* __restrict__ mod,
                                                       const float* __restrict__ inv_s,
                                                       const LT* __restrict__ l_down,
                                                       const LT* __restrict__ r_up, int64_t T,
-                                                      int K, int N, int r, int n_mod,
+                                                      int K, int N, int r, int n_mod, int per,
                                                       YT* __restrict__ y) {
-    __shared__ int smod[kRowsDown];
-    __shared__ float red[4][kRowsDown][64];
-    __shared__ float su[kRowsDown][kMaxRank];
-    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kRowsDown;
-    if (threadIdx.x < kRowsDown) {
-        const int64_t t = row0 + threadIdx.x;
-        smod[threadIdx.x] = t < T ? sane_mod(mod[t], n_mod) : 0;
-    }
+    __shared__ int smod[kCompRows];
+    __shared__ float red[kCompWaves][kCompRows][64];
+    __shared__ __attribute__((aligned(16))) float su[kCompRows * (kMaxRank + kCompPad)];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kCompRows;
+    if (tid < kCompRows) smod[tid] = row0 + tid < T ? sane_mod(mod[row0 + tid], n_mod) : 0;
     __syncthreads();
-    const unsigned present = tile_presence(smod);
+    const unsigned present = tile_presence<kCompRows>(smod);
     if (!present) return;
+    const int pitch = r + kCompPad;
     for (int c0 = 0; c0 < r; c0 += 64)
-        down_group<4, XT, LT>(x, inv_s, l_down, row0, T, K, r, n_mod, 0, K, c0, smod, present, red,
-                              [&](int row, int col, float v) { su[row][col] = v; });
-    for (int o = threadIdx.x; o < N; o += 256) {
-        for (int i = 0; i < kRowsDown; ++i) {
-            const int m = smod[i];
-            const int64_t t = row0 + i;
-            if (t >= T || m == 0) continue;
-            const LT* rr = r_up + (static_cast<int64_t>(m - 1) * N + o) * r;
-            float c = 0.f;
-            for (int k = 0; k < r; ++k) c = fmaf(su[i][k], Elem<LT>::load1(rr + k), c);
-            YT* yp = y + t * N + o;
-            Elem<YT>::store1(yp, Elem<YT>::load1(yp) + c);
+        down_group<kCompWaves, 2, XT, LT>(x, inv_s, l_down, row0, T, K, r, n_mod, 0, K, c0, smod,
+                                          present, red,
+                                          [&](int row, int col, float v) { su[row * pitch + col] = v; });
+    const int tl = lane & 31, kg = lane >> 5;
+    const int md = smod[tl];
+    const int64_t t = row0 + tl;
+    const int nb = (N + 31) / 32;
+    const int b1 = min(nb, (static_cast<int>(blockIdx.y) + 1) * per);
+    for (int b = static_cast<int>(blockIdx.y) * per + wave; b < b1; b += kCompWaves) {
+        const int chan = min(32 * b + tl, N - 1);
+        v16f acc = v16f{0.f};
+        for (int m = 1; m < n_mod; ++m) {
+            if (!__builtin_amdgcn_readfirstlane(static_cast<int>(present >> m) & 1)) continue;
+            const bool live = md == m;
+            const LT* rr = r_up + (static_cast<int64_t>(m - 1) * N + chan) * r + 8 * kg;
+            const float* ur = su + tl * pitch + 8 * kg;
+            for (int k0 = 0; k0 < r; k0 += 64) {            // r % 16 == 0
+                float rv[4][8];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) load8_any(rr + min(k0 + 16 * q, r - 16), rv[q]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const bool use = live && k0 + 16 * q < r;     // (no branch: see DownK)
+                    float uv[8];
+                    load8_f32(ur + min(k0 + 16 * q, r - 16), uv);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(rv[q][e], use ? uv[e] : 0.f, acc, 0, 0, 0);
+                }
+            }
+        }
+        // lane: token tl, channels 32 b + 8 g + 4 kg + e in acc[4 g + e]
+        if (t < T && md > 0) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int ch = 32 * b + 8 * g + 4 * kg;
+                if (ch >= N) continue;                       // N % 16 == 0
+                YT* yp = y + t * N + ch;
+                const v4f v = load4(yp) + v4f{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+                if constexpr (sizeof(YT) == 2)
+                    *reinterpret_cast<v2i*>(yp) = v2i{static_cast<int32_t>(pack_bf16x2(v.x, v.y)),
+                                                      static_cast<int32_t>(pack_bf16x2(v.z, v.w))};
+                else
+                    *reinterpret_cast<v4f*>(yp) = v;
+            }
         }
     }
 }
@@ -3464,11 +3576,16 @@ template <typename XT, typename LT, typename YT>
 static void launch_comp_t(const void* x, const int32_t* mod, const float* inv_s, const void* ld,
                           const void* ru, int64_t T, int64_t K, int64_t N, int rank, int n_mod,
                           void* y, hipStream_t s) {
-    const dim3 grid(static_cast<unsigned>((T + kRowsDown - 1) / kRowsDown)), block(256);
-    hipLaunchKernelGGL((k_lowrank_comp<XT, LT, YT>), grid, block, 0, s,
+    // channel groups: about 512 workgroups in all, at least a block for each wave
+    const int64_t tiles = (T + kCompRows - 1) / kCompRows, nb = (N + 31) / 32;
+    int64_t groups = (512 + tiles - 1) / tiles;
+    if (groups > (nb + kCompWaves - 1) / kCompWaves) groups = (nb + kCompWaves - 1) / kCompWaves;
+    const int per = static_cast<int>((nb + groups - 1) / groups);
+    const dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>((nb + per - 1) / per));
+    hipLaunchKernelGGL((k_lowrank_comp<XT, LT, YT>), grid, dim3(64 * kCompWaves), 0, s,
                        static_cast<const XT*>(x), mod, inv_s, static_cast<const LT*>(ld),
                        static_cast<const LT*>(ru), T, static_cast<int>(K), static_cast<int>(N),
-                       rank, n_mod, static_cast<YT*>(y));
+                       rank, n_mod, per, static_cast<YT*>(y));
 }
 
 hipError_t launch_lowrank_comp(const void* x, DT x_dt, const int32_t* mod, const float* inv_s,

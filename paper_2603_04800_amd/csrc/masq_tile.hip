@@ -40,12 +40,14 @@ template <> struct CompBlocks<bf16_t> {
                                                const bool (&live)[MI], const int (&chan)[NJ], int lane) {
         const int kg = lane >> 5;
         const v4i zero = {0, 0, 0, 0};
-        auto mac = [&](const v4i (&hi)[MI], const v4i (&lo)[MI], const v4i (&b)[NJ])
+        // (in: the step lies within r; a step past it multiplies zeros, without
+        // a branch between the MFMAs)
+        auto mac = [&](const v4i (&hi)[MI], const v4i (&lo)[MI], const v4i (&b)[NJ], bool in)
                        __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
-                const v8bf h = __builtin_bit_cast(v8bf, live[i] ? hi[i] : zero);
-                const v8bf l = __builtin_bit_cast(v8bf, live[i] ? lo[i] : zero);
+                const v8bf h = __builtin_bit_cast(v8bf, live[i] && in ? hi[i] : zero);
+                const v8bf l = __builtin_bit_cast(v8bf, live[i] && in ? lo[i] : zero);
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     const v8bf bj = __builtin_bit_cast(v8bf, b[j]);
@@ -71,8 +73,7 @@ template <> struct CompBlocks<bf16_t> {
                     b[ks][j] = *reinterpret_cast<const v4i*>(rm + static_cast<int64_t>(chan[j]) * r + k);
             }
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-                if (ks < nks) mac(hi[ks], lo[ks], b[ks]);
+            for (int ks = 0; ks < 4; ++ks) mac(hi[ks], lo[ks], b[ks], ks < nks);
             return;
         }
         for (int k0 = 0; k0 < r; k0 += 32) {                // r % 16 == 0: two steps a round
@@ -90,8 +91,8 @@ template <> struct CompBlocks<bf16_t> {
                 for (int j = 0; j < NJ; ++j)
                     b[ks][j] = *reinterpret_cast<const v4i*>(rm + static_cast<int64_t>(chan[j]) * r + k);
             }
-            mac(hi[0], lo[0], b[0]);
-            if (k0 + 16 < r) mac(hi[1], lo[1], b[1]);
+            mac(hi[0], lo[0], b[0], true);
+            mac(hi[1], lo[1], b[1], k0 + 16 < r);
         }
     }
 };
@@ -242,13 +243,12 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void k_gemm_tile(
         const v4i zero = {0, 0, 0, 0};
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-            if (2 * ks >= valid) break;                     // uniform
             v4i fa[MI], fb[NJ];
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
                 const int row = wm * (BM / WM) + 32 * i + (lane & 31);
                 fa[i] = *reinterpret_cast<const v4i*>(sa + row * kTsK + (((2 * ks + h) ^ ts_swz(row)) << 4));
-                if (2 * ks + 1 >= valid) fa[i] = h ? zero : fa[i];
+                if (valid < 8) fa[i] = 2 * ks + h < valid ? fa[i] : zero;
             }
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {

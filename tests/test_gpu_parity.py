@@ -630,3 +630,28 @@ def test_the_workspace_does_not_depend_on_the_tile_plan(ops, T, K, N):
     if S > 1:
         want += up(4 * tiles) + up(4 * tiles * S * 65536)
     assert ops.workspace_bytes(T, K, N, 0, 1) == want
+
+
+@pytest.mark.parametrize("T,K,N,r,M,act,lr", [
+    (1, 16, 16, 16, 2, "f32", "f32"), (31, 48, 48, 48, 3, "bf16", "f32"), (32, 112, 272, 80, 2, "f32", "bf16"),
+    (33, 144, 32, 256, 4, "bf16", "bf16"), (65, 1040, 2064, 64, 3, "f32", "f32"), (700, 256, 304, 16, 2, "bf16", "bf16"),
+])
+@pytest.mark.parametrize("y_dtype", [torch.float32, torch.bfloat16])
+def test_standalone_compensation_edges(ops, T, K, N, r, M, act, lr, y_dtype):
+    """Row tiles of 32, channel blocks of 32 (whole and half), k ranges of the
+    eight waves that are empty, partial and whole, every rank remainder: each
+    output within the oracle's bar, text rows (NaN here) never read or written."""
+    L = _random_layer(T, K, N, r, M, act, lr, seed=T + K + r)
+    dev = torch.device("cuda")
+    x = torch.from_numpy(L["x"]).to(dev, torch.bfloat16 if act == "bf16" else torch.float32)
+    mod = torch.from_numpy(L["modality"]).to(dev)
+    lt = torch.bfloat16 if lr == "bf16" else torch.float32
+    y0 = torch.from_numpy(np.random.default_rng(1).standard_normal((T, N)).astype(np.float32)).to(dev, y_dtype)
+    y0[mod == 0] = float("nan")
+    y = ops.lowrank_comp(x, mod, torch.from_numpy(L["inv_smooth"]).to(dev), torch.from_numpy(L["l_down"]).to(dev, lt),
+                         torch.from_numpy(L["r_up"]).to(dev, lt), y0.clone())
+    text = L["modality"] == 0
+    assert bool(torch.isnan(y[mod == 0]).all())
+    ref = oinf.lowrank_comp(L["x"], L["modality"], L["inv_smooth"], L["l_down"], L["r_up"], _np(y0))
+    if (~text).any():
+        assert oinf.relerr(_np(y)[~text], ref[~text]) <= (_tol(act, lr) if y_dtype == torch.float32 else 1e-2)
