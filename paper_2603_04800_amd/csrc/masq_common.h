@@ -104,6 +104,8 @@ inline int tile_slices(int64_t K, int S) {
 constexpr int kDecSteps = 40;
 constexpr int kDecCh = 64;
 constexpr int kDecMaxSlices = 8;    // longer rows (K > 8 * 40 * 64) take the single-pass GEMM
+constexpr int kDecShort = 28;       // slices this short take the kernel of three workgroups per CU
+constexpr int kDecCmcBytesShort = 24576;
 constexpr int kDecCmcBytes = 32768;  // LDS for the compensation operands of a k-slice workgroup
 inline void plan_decode(int64_t K, int64_t N, int& ns, int& sp, int& ngroups) {
     const int64_t nsteps = K / 64;

@@ -2832,19 +2832,24 @@ __global__ __launch_bounds__(256) void k_gemm_small(
 // unpacked into the MFMA operand in registers).
 // only_mod >= 0 (the MAS-only comparator, one launch per modality's weight):
 // only the outputs of tokens of that modality are stored.
-template <typename YT, typename LT, bool W4>
-__global__ __launch_bounds__(256, 2) void k_gemm_decode(
+// DS: the Wq steps a wave holds (sp <= DS); fewer registers and less LDS let
+// three workgroups share a CU (DS <= kDecShort) instead of two.  3584 columns
+// are two slices of 28 steps: with 40 steps held the 592 workgroups of 18944
+// channels took two rounds and 12 of each wave's 40 loads were repeats.
+template <typename YT, typename LT, bool W4, int DS>
+__global__ __launch_bounds__(256, DS <= kDecShort ? 3 : 2) void k_gemm_decode(
     const int8_t* __restrict__ A, const int8_t* __restrict__ B, const float* __restrict__ x_scale,
     const float* __restrict__ w_scale, int T, int K, int N, int ns, int sp,
     const int32_t* __restrict__ mod, const float* __restrict__ u,
     const float* __restrict__ u_part, int n_kslices, int r, int n_mod,
     const LT* __restrict__ r_up, int32_t* __restrict__ part, int* __restrict__ tickets,
     YT* __restrict__ y, int only_mod) {
-    __shared__ __attribute__((aligned(16))) uint8_t sq[kDecSteps * 1024];
+    constexpr int kCmcBytes = DS <= kDecShort ? kDecCmcBytesShort : kDecCmcBytes;
+    __shared__ __attribute__((aligned(16))) uint8_t sq[DS * 1024];
     // compensation operands (u partials of the token share, then L2 rows of
     // the group's channels) or, when they do not fit, the u rows of the batch
-    __shared__ __attribute__((aligned(16))) uint8_t scm[kDecCmcBytes];
-    static_assert(sizeof(float) * kSmallMaxT * kMaxRank <= kDecCmcBytes, "u rows fit scm");
+    __shared__ __attribute__((aligned(16))) uint8_t scm[kCmcBytes];
+    static_assert(sizeof(float) * kSmallMaxT * kMaxRank <= kCmcBytes, "u rows fit scm");
     auto& su = *reinterpret_cast<float (*)[kSmallMaxT][kMaxRank]>(scm);
     __shared__ int s_last;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -2877,7 +2882,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_decode(
     const int up_bytes = ((up_pieces * 16 + 1023) >> 10) << 10;
     const int rrow = r * static_cast<int>(sizeof(LT));              // bytes of one L2 row
     const int rp_pieces = cmc ? (n_mod - 1) * kDecCh * (rrow >> 4) : 0;
-    const bool early = cmc && nts <= 4 && up_bytes + rp_pieces * 16 <= kDecCmcBytes;
+    const bool early = cmc && nts <= 4 && up_bytes + rp_pieces * 16 <= kCmcBytes;
     const uint32_t scm0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(scm));
     int tmod = 0;                                   // modality of the thread's share output
     if (early) {
@@ -2904,20 +2909,20 @@ __global__ __launch_bounds__(256, 2) void k_gemm_decode(
     // used; a wave past N reads the last channel block and stores nothing)
     using BRaw = std::conditional_t<W4, v2i, v4i>;
     constexpr int kStepB = W4 ? 32 : 64;                           // Wq bytes per row and step
-    BRaw fb[kDecSteps];
+    BRaw fb[DS];
     {
         const int64_t pitch = W4 ? K / 2 : K;                      // bytes per Wq row
         const int8_t* bp = B + (min(cb, N - 16) + (lane & 15)) * pitch +
                            static_cast<int64_t>(st0) * kStepB + (kStepB / 4) * (lane >> 4);
         asm volatile("" ::: "memory");
 #pragma unroll
-        for (int j = 0; j < kDecSteps; ++j)
+        for (int j = 0; j < DS; ++j)
             fb[j] = *reinterpret_cast<const BRaw*>(bp + kStepB * min(j, S - 1));
         asm volatile("" ::: "memory");
     }
-    // this wave's q loads are the ones older than its kDecSteps Wq loads;
+    // this wave's q loads are the ones older than its DS Wq loads;
     // the barrier publishes every wave's share
-    MASQ_WAIT_VMCNT_LGKM0(kDecSteps);
+    MASQ_WAIT_VMCNT_LGKM0(DS);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     // while Wq streams in: u rows of the share (slice partials added in
@@ -2957,7 +2962,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_decode(
         const uint8_t* rd = sq + rt * 64 + (((lane >> 4) ^ swz4(rt)) << 4);
         const v4i zero = {0, 0, 0, 0};
 #pragma unroll
-        for (int j = 0; j < kDecSteps; ++j) {
+        for (int j = 0; j < DS; ++j) {
             // steps past S multiply zeros (MFMA does not branch on lanes)
             v4i fa = *reinterpret_cast<const v4i*>(rd + min(j, S - 1) * 1024);
             fa = j < S ? fa : zero;
@@ -3010,7 +3015,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_decode(
     // kRStage bytes) and the u rows of the batch; or, when the slices have
     // formed the compensation terms, those terms.
     constexpr int kOut = kSmallMaxT * kDecCh / 256;
-    constexpr int kRStage = 16384;
+    constexpr int kRStage = DS * 1024 < 16384 ? DS * 1024 : 16384;
     constexpr int kRPieces = kRStage / 16 / 256;                       // per thread
     int pv[kOut][kDecMaxSlices], mv[kOut], om[kOut];
     float dxv[kOut], dwv[kOut], cv[kOut];
@@ -3389,10 +3394,15 @@ static void launch_gemm_decode_t(const int8_t* q, const float* x_scale, const in
                                  int only_mod = -1) {
     int ns, sp, ngroups;
     plan_decode(K, N, ns, sp, ngroups);
-    hipLaunchKernelGGL((k_gemm_decode<YT, LT, W4>), dim3(static_cast<unsigned>(ngroups * ns)), dim3(256),
-                       0, s, q, wq, x_scale, w_scale, static_cast<int>(T), static_cast<int>(K),
-                       static_cast<int>(N), ns, sp, mod, u, u_part, n_kslices, rank, n_mod,
-                       static_cast<const LT*>(r_up), part, tickets, static_cast<YT*>(y), only_mod);
+#define MASQ_DECODE(DS)                                                                            \
+    hipLaunchKernelGGL((k_gemm_decode<YT, LT, W4, DS>), dim3(static_cast<unsigned>(ngroups * ns)), \
+                       dim3(256), 0, s, q, wq, x_scale, w_scale, static_cast<int>(T),              \
+                       static_cast<int>(K), static_cast<int>(N), ns, sp, mod, u, u_part,           \
+                       n_kslices, rank, n_mod, static_cast<const LT*>(r_up), part, tickets,        \
+                       static_cast<YT*>(y), only_mod)
+    if (sp <= kDecShort) MASQ_DECODE(kDecShort);
+    else MASQ_DECODE(kDecSteps);
+#undef MASQ_DECODE
 }
 
 hipError_t launch_gemm_decode_mas(const int8_t* q, const float* x_scale, const int8_t* wq,

@@ -655,3 +655,15 @@ def test_standalone_compensation_edges(ops, T, K, N, r, M, act, lr, y_dtype):
     ref = oinf.lowrank_comp(L["x"], L["modality"], L["inv_smooth"], L["l_down"], L["r_up"], _np(y0))
     if (~text).any():
         assert oinf.relerr(_np(y)[~text], ref[~text]) <= (_tol(act, lr) if y_dtype == torch.float32 else 1e-2)
+
+
+@pytest.mark.parametrize("T,K,N,r,M,lr,bits", [
+    # slices of 28 steps and fewer (three workgroups a CU), 29 and more
+    (1, 64, 16, 16, 2, "bf16", 8), (16, 1792, 144, 64, 2, "bf16", 8), (7, 1856, 80, 32, 3, "bf16", 4),
+    (16, 3584, 208, 64, 4, "f32", 8), (1, 3584, 1040, 64, 2, "bf16", 4), (13, 2688, 64, 128, 2, "bf16", 8),
+    # operands past the smaller compensation buffer: u added by the last slice
+    (16, 3584, 96, 256, 2, "f32", 8), (16, 14336, 80, 64, 4, "bf16", 8),
+])
+def test_decode_gemm_step_counts(ops, T, K, N, r, M, lr, bits):
+    L = _random_layer(T, K, N, r, M, "bf16", lr, weight_bits=bits, seed=T + K)
+    _check_layer(ops, L, name="decode steps")
