@@ -188,6 +188,16 @@ hipError_t launch_lowrank_down(const void* x, DT x_dt, const int32_t* mod, const
                                const void* l_down, DT lr_dt, int64_t T, int64_t K, int rank,
                                int n_mod, const Workspace& w, hipStream_t s);
 
+// Quantisation and the down-projection in one launch: one k slice of u a
+// tile (no arrival counters, which the launch itself would have to clear).
+constexpr int64_t kQuantDownMaxK = 4096;
+inline bool quant_down_ok(const Workspace& w, int64_t K) {
+    return w.n_kslices == 1 && K <= kQuantDownMaxK;
+}
+hipError_t launch_quant_down(const void* x, DT x_dt, const int32_t* mod, const float* inv_s,
+                             const void* l_down, DT lr_dt, int64_t T, int64_t K, int rank, int n_mod,
+                             const Workspace& w, hipStream_t s);
+
 // Stage 1 in one kernel for bf16 factors and rank <= 64 (fused_stage1_ok):
 // smoothing, quantisation and the down-projection, reading each row once.
 inline bool fused_stage1_ok(int64_t T, int64_t K, int rank, DT lr_dt) {

@@ -667,3 +667,14 @@ def test_standalone_compensation_edges(ops, T, K, N, r, M, act, lr, y_dtype):
 def test_decode_gemm_step_counts(ops, T, K, N, r, M, lr, bits):
     L = _random_layer(T, K, N, r, M, "bf16", lr, weight_bits=bits, seed=T + K)
     _check_layer(ops, L, name="decode steps")
+
+
+@pytest.mark.parametrize("T,K,N,r,M,act,lr", [
+    # one launch for codes and u: rows around 8 a workgroup and 16 a tile,
+    # columns up to what a wave holds (4096) and past it (4112: two launches)
+    (17, 512, 32, 16, 2, "f32", "f32"), (23, 16, 48, 80, 3, "bf16", "f32"), (257, 1040, 64, 128, 4, "bf16", "bf16"),
+    (263, 4096, 80, 96, 2, "f32", "f32"), (264, 4096, 32, 128, 2, "bf16", "bf16"), (272, 4112, 32, 16, 2, "f32", "f32"),
+])
+def test_quantisation_and_down_projection_in_one_launch(ops, T, K, N, r, M, act, lr):
+    L = _random_layer(T, K, N, r, M, act, lr, zero_rows=(T // 2,), seed=T + K)
+    _check_layer(ops, L, name="one launch")
