@@ -42,7 +42,8 @@ if ROOT not in sys.path:
 
 INT8_PEAK_TOPS = 5000.0      # MI355X dense int8 MFMA
 HBM_PEAK_GBS = 8000.0        # MI355X HBM3E
-KERNEL_SOURCES = ("paper_2603_04800_amd/csrc/masq_kernels.hip",)
+KERNEL_SOURCES = ("paper_2603_04800_amd/csrc/masq_kernels.hip",
+                  "paper_2603_04800_amd/csrc/masq_tile.hip")
 
 
 def log(msg):
@@ -523,14 +524,14 @@ def cpu_baseline(layers, min_seconds=10.0, max_runs=64):
 
 def gemm_kernel_label(layers) -> str:
     """Name of the stage-2 kernel(s) the layers dispatch to: batches of at
-    most 16 tokens with K % 64 == 0 take the k-sliced decode kernel (K up to
-    8 slices of 40 64-byte steps; longer rows the single-pass one), other
-    K % 64 == 0 shapes the LDS-DMA tile kernel, the rest the general-K one."""
+    most 16 tokens with K % 64 == 0 stream the weight (k_gemm_stream), larger
+    ones take the 256 x 256 or the small-tile kernel, whichever the library's
+    plan estimates faster."""
     names = []
     for L in layers:
         T, K = L["x"].shape
-        n = (("k_gemm_decode" if K <= 8 * 40 * 64 else "k_gemm_small") if T <= 16 and K % 64 == 0
-             else "k_gemm_dma" if K % 64 == 0 else "k_gemm")
+        n = "k_gemm_stream" if T <= 16 and K % 64 == 0 else \
+            "k_gemm_dma / k_gemm_tile" if K % 64 == 0 else "k_gemm_tile"
         if n not in names:
             names.append(n)
     return " + ".join(names) + " (stage 2: int8 GEMM + dequant + compensation)"

@@ -97,22 +97,26 @@ inline int tile_slices(int64_t K, int S) {
     return (n + per - 1) / per;
 }
 
-// Decode GEMM of the fused small-batch path: a workgroup covers kDecCh output
-// channels and one k slice of at most kDecSteps 64-byte steps (its waves hold
-// every Wq step of the slice in registers).  ns slices of sp steps (the last
-// may be shorter, none is empty), ngroups channel groups.
+// Decode GEMM of the fused small-batch path (k_gemm_stream): channel groups of
+// kDecCh, and the k slices its workspace holds room for: ns slices of sp
+// 64-byte steps, sp <= kDecSteps.
 constexpr int kDecSteps = 40;
 constexpr int kDecCh = 64;
-constexpr int kDecMaxSlices = 8;    // longer rows (K > 8 * 40 * 64) take the single-pass GEMM
-constexpr int kDecShort = 28;       // slices this short take the kernel of three workgroups per CU
-constexpr int kDecCmcBytesShort = 24576;
-constexpr int kDecCmcBytes = 32768;  // LDS for the compensation operands of a k-slice workgroup
+constexpr int kDecMaxSlices = 8;    // at most this many are used
 inline void plan_decode(int64_t K, int64_t N, int& ns, int& sp, int& ngroups) {
     const int64_t nsteps = K / 64;
     const int64_t ns0 = (nsteps + kDecSteps - 1) / kDecSteps;
     sp = static_cast<int>((nsteps + ns0 - 1) / ns0);
     ns = static_cast<int>((nsteps + sp - 1) / sp);
     ngroups = static_cast<int>((N + kDecCh - 1) / kDecCh);
+}
+// Slices the decode GEMM takes of the `most` that the workspace holds: none
+// for 256 channel groups and more, else up to about 448 workgroups.
+inline int stream_slices(int64_t K, int groups, int most) {
+    int S = groups >= 256 ? 1 : 448 / groups;
+    if (S > most) S = most;
+    if (S > kDecMaxSlices) S = kDecMaxSlices;
+    return tile_slices(K, S);
 }
 constexpr int64_t kRowsPerWaveMinT = 256;   // batches this large quantise one row per wave
 
@@ -313,6 +317,30 @@ struct TileGemm {
     hipStream_t stream;
 };
 hipError_t launch_gemm_tile(const TileGemm& g);
+
+// The decode GEMM (small_path): u (null without compensation) holds u_slices
+// partials [T][rank]; part: the decode workspace's [slices + 1][kSmallMaxT][N],
+// tickets: a counter per 64 channels (zero on entry, left zero).
+struct StreamGemm {
+    const int8_t* q;
+    const float* x_scale;
+    const int8_t* wq;
+    const float* w_scale;
+    int64_t T, K, N;
+    const int32_t* mod;
+    const float* u;
+    int u_slices, rank, n_mod;
+    const void* r_up;
+    DT lr_dt;
+    void* y;
+    DT y_dt;
+    bool w4;
+    int32_t* part;
+    int* tickets;
+    int only_mod;
+    hipStream_t stream;
+};
+hipError_t launch_gemm_stream(const StreamGemm& g);
 
 // MAS-only comparator (a weight per modality, no compensation): rows grouped
 // by modality on the device, then the direct-to-LDS GEMM over tiles of one

@@ -26,6 +26,7 @@
 
 #include "masq_device.h"
 
+
 namespace masq {
 namespace {
 
@@ -168,32 +169,37 @@ __global__ __launch_bounds__(256) void k_smooth_quant(const XT* __restrict__ x,
 
 // One row t quantised by one wave (lane = this lane), its smoothed values
 // kept in registers between the absmax and the codes for rows of up to
-// 64 * 8 * NC elements; longer rows stream their remainder twice.
-template <typename XT, int NC>
+// 64 * 8 * NC elements; longer rows stream their remainder twice.  The row's
+// NC loads are in flight together, issued before anything that waits for the
+// modality id (lanes past the row's end repeat its last piece); `between`
+// runs while they are.
+template <typename XT, int NC, typename Between>
 __device__ __forceinline__ void quant_row_wave(const XT* __restrict__ x, const int32_t* __restrict__ mod,
                                                const float* __restrict__ inv_s, int K, int n_mod,
                                                int8_t* __restrict__ q, float* __restrict__ x_scale,
-                                               int64_t t, bool pair, int lane) {
-    const int m = sane_mod(mod[t], n_mod);
+                                               int64_t t, bool pair, int lane, Between between) {
     const XT* xr = x + t * static_cast<int64_t>(K);
+    const int nv = K >> 3;
+    Raw8<XT> raw[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) raw[c].load(xr + 8 * min(lane + 64 * c, nv - 1));
+    const int m = sane_mod(mod[t], n_mod);
     const float* sr = inv_s + static_cast<int64_t>(m) * K;
     int8_t* qr = q + code_row(t, K, pair);
-    const int nv = K >> 3;
+    between(m);
 
     float xs[NC][8];
     float amax = 0.f;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        const int v = lane + 64 * c;
-        if (v < nv) {
-            float xv[8], sv[8];
-            Elem<XT>::load8(xr + 8 * v, xv);
-            load8_f32(sr + 8 * v, sv);
+    for (int c = 0; c < NC; ++c) load8_f32(sr + 8 * min(lane + 64 * c, nv - 1), xs[c]);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                xs[c][j] = xv[j] * sv[j];
-                amax = fmaxf(amax, fabsf(xs[c][j]));
-            }
+    for (int c = 0; c < NC; ++c) {
+        float xv[8];
+        raw[c].to_f32(xv);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {                 // (repeats do not change the maximum)
+            xs[c][j] = xv[j] * xs[c][j];
+            amax = fmaxf(amax, fabsf(xs[c][j]));
         }
     }
     for (int v = lane + 64 * NC; v < nv; v += 64) {
@@ -254,9 +260,10 @@ __global__ __launch_bounds__(256) void k_smooth_quant_rows(const XT* __restrict_
     const int lane = threadIdx.x & 63;
     const int64_t t = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (t >= T) return;
-    if (fin.part != nullptr)
-        finish_u_row(t, T, sane_mod(mod[t], n_mod) == 0, fin.part, fin.slices, fin.r, fin.u, fin.u_hl, lane);
-    quant_row_wave<XT, NC>(x, mod, inv_s, K, n_mod, q, x_scale, t, pair, lane);
+    quant_row_wave<XT, NC>(x, mod, inv_s, K, n_mod, q, x_scale, t, pair, lane, [&](int m) {
+        if (fin.part != nullptr)
+            finish_u_row(t, T, m == 0, fin.part, fin.slices, fin.r, fin.u, fin.u_hl, lane);
+    });
 }
 
 // ================================================================ down-projection
@@ -578,7 +585,8 @@ __global__ __launch_bounds__(64 * kDownWaves) void k_quant_down(
     if (b == 0)
         for (int i = threadIdx.x; i < n_zero; i += 64 * kDownWaves) zero_ints[i] = 0;
     const int64_t t = b * kDownWaves + (threadIdx.x >> 6);
-    if (t < T) quant_row_wave<XT, 8>(x, mod, inv_s, K, n_mod, q, x_scale, t, pair, threadIdx.x & 63);
+    if (t < T)
+        quant_row_wave<XT, 8>(x, mod, inv_s, K, n_mod, q, x_scale, t, pair, threadIdx.x & 63, [](int) {});
 }
 
 // Down-projection of large batches (bf16 factors, rank <= 64): u = (x S_m^-1)
@@ -1608,7 +1616,7 @@ __global__ __launch_bounds__(64 * kFrWaves) void k_stage1_fr(
 // where T / 32 tiles would leave most of it idle.  One lane a channel and
 // scalar fma, 16 rows a workgroup: 2081 us for 1000 x 1040 -> 2000, rank 128
 // in fp32, and 4.6 ms for 8192 x 3584 -> 3584, rank 64 in bf16; in this form
-// 42 and 147 us.
+// 43 and 135 us (16-row tiles, twice the L1 reads: 68 and 224 us).
 constexpr int kCompRows = 32;
 constexpr int kCompWaves = 8;
 constexpr int kCompPad = 4;             // floats after a u row: rows start on different banks
@@ -2832,330 +2840,6 @@ __global__ __launch_bounds__(256) void k_gemm_small(
     small_output<YT, LT>(su, a, t, ch, N, x_scale, w_scale, mod, u != nullptr, r, n_mod, r_up, y);
 }
 
-// ---------------------------------------------------------------- decode GEMM
-// The fused layer's small-batch GEMM.  At most 16 tokens make the layer a
-// stream of Wq from HBM, so the kernel is shaped to keep as many Wq bytes in
-// flight as it can: a workgroup covers kDecCh output channels (16 per wave)
-// and one k slice of sp <= kDecSteps 64-byte steps, and each wave issues all
-// of its slice's Wq loads at once into registers.  The slice of q goes to
-// LDS by DMA queued ahead of those loads (vector-memory loads complete in
-// issue order, so waiting for q does not wait for Wq).  The int32 partial
-// sums of each slice go to the workspace; the last workgroup of a channel
-// group to arrive adds the slices in slice order and finishes the outputs
-// like the single-pass kernel (dequantisation, compensation, store).
-// The compensation term of the group's outputs is computed off that tail
-// when its operands fit in LDS: workgroup (g, s) takes the tokens t with
-// t % ns == s.  The u partials of those tokens and the L2 rows of the
-// group's channels are queued by DMA with the q slice, ahead of the Wq
-// loads, so they have landed long before Wq has; the workgroup adds the
-// partials (slice order), forms (x S^-1 L1) L2 for its tokens while its Wq
-// loads are still in flight (each thread sums over the rank in 8-column
-// chunks, starting at a lane-dependent chunk), and hands the fp32 terms over
-// beside the int32 partials.  The last workgroup then only adds.
-// W4: Wq holds packed 4-bit codes (K / 2 bytes a row, 8 bytes a lane a step,
-// unpacked into the MFMA operand in registers).
-// only_mod >= 0 (the MAS-only comparator, one launch per modality's weight):
-// only the outputs of tokens of that modality are stored.
-// DS: the Wq steps a wave holds (sp <= DS); fewer registers and less LDS let
-// three workgroups share a CU (DS <= kDecShort) instead of two.  3584 columns
-// are two slices of 28 steps: with 40 steps held the 592 workgroups of 18944
-// channels took two rounds and 12 of each wave's 40 loads were repeats.
-template <typename YT, typename LT, bool W4, int DS>
-__global__ __launch_bounds__(256, DS <= kDecShort ? 3 : 2) void k_gemm_decode(
-    const int8_t* __restrict__ A, const int8_t* __restrict__ B, const float* __restrict__ x_scale,
-    const float* __restrict__ w_scale, int T, int K, int N, int ns, int sp,
-    const int32_t* __restrict__ mod, const float* __restrict__ u,
-    const float* __restrict__ u_part, int n_kslices, int r, int n_mod,
-    const LT* __restrict__ r_up, int32_t* __restrict__ part, int* __restrict__ tickets,
-    YT* __restrict__ y, int only_mod) {
-    constexpr int kCmcBytes = DS <= kDecShort ? kDecCmcBytesShort : kDecCmcBytes;
-    __shared__ __attribute__((aligned(16))) uint8_t sq[DS * 1024];
-    // compensation operands (u partials of the token share, then L2 rows of
-    // the group's channels) or, when they do not fit, the u rows of the batch
-    __shared__ __attribute__((aligned(16))) uint8_t scm[kCmcBytes];
-    static_assert(sizeof(float) * kSmallMaxT * kMaxRank <= kCmcBytes, "u rows fit scm");
-    auto& su = *reinterpret_cast<float (*)[kSmallMaxT][kMaxRank]>(scm);
-    __shared__ int s_last;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = blockIdx.x / ns, sl = blockIdx.x - g * ns;        // channel group, k slice
-    const int st0 = sl * sp;
-    const int S = min(sp, (K >> 6) - st0);                         // steps of this slice, >= 1
-    const int cb = g * kDecCh + 16 * wave;                         // the wave's first channel
-    const bool active = cb < N;
-
-    // q slice into LDS: step j as 16 rows x 64 bytes, row t's piece p at
-    // position p ^ swz4(t); rows past T repeat row T - 1 (results discarded)
-    const uint32_t sq0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(sq));
-    {
-        const int t = lane >> 2, p = (lane & 3) ^ swz4(lane >> 2);
-        const int8_t* qa = A + static_cast<int64_t>(min(t, T - 1)) * K +
-                           static_cast<int64_t>(st0) * 64 + 16 * p;
-        for (int j = wave; j < S; j += 4) lds_dma16(qa + 64 * j, sq0 + j * 1024);
-    }
-    // compensation operands of the token share, when they fit: the u slice
-    // partials as rows [slice][share token][r] fp32, then the L2 rows
-    // [modality - 1][channel of the group][r]; both padded to whole 1 KB
-    // DMA blocks (a block's pieces past the end repeat the last piece)
-    const bool cmc = u != nullptr;
-    const int uslices = (u_part != nullptr && n_kslices > 1) ? n_kslices : 1;
-    const float* usrc = uslices > 1 ? u_part : u;
-    const int nts = (T + ns - 1) / ns;                              // share tokens, at most
-    const int own = sl < T ? (T - sl + ns - 1) / ns : 0;            // this workgroup's
-    const int up_pieces = uslices * nts * (r >> 2);                 // 16-byte pieces
-    const int up_bytes = ((up_pieces * 16 + 1023) >> 10) << 10;
-    const int rrow = r * static_cast<int>(sizeof(LT));              // bytes of one L2 row
-    const int rp_pieces = cmc ? (n_mod - 1) * kDecCh * (rrow >> 4) : 0;
-    const bool early = cmc && nts <= 4 && up_bytes + rp_pieces * 16 <= kCmcBytes;
-    const uint32_t scm0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(scm));
-    int tmod = 0;                                   // modality of the thread's share output
-    if (early) {
-        const int ti = tid >> 6;
-        if (ti < own) tmod = sane_mod(mod[sl + ti * ns], n_mod);
-        const int upr = r >> 2;                                     // pieces per u row
-        for (int i = wave; i * 64 < up_pieces; i += 4) {
-            const int pc = min(i * 64 + lane, up_pieces - 1);
-            const int row = pc / upr, c = pc - row * upr;
-            const int s = row / nts, tt = min(sl + (row - s * nts) * ns, T - 1);
-            lds_dma16(usrc + (static_cast<int64_t>(s) * T + tt) * r + 4 * c, scm0 + i * 1024);
-        }
-        const int rpr = rrow >> 4;                                  // pieces per L2 row
-        for (int i = wave; i * 64 < rp_pieces; i += 4) {
-            const int pc = i * 64 + lane;                           // rp_pieces % 64 == 0
-            const int row = pc / rpr, c = pc - row * rpr;
-            const int mm = row / kDecCh, ch = min(g * kDecCh + (row - mm * kDecCh), N - 1);
-            lds_dma16(reinterpret_cast<const uint8_t*>(r_up + (static_cast<int64_t>(mm) * N + ch) * r) +
-                          16 * c,
-                      scm0 + up_bytes + i * 1024);
-        }
-    }
-    // every Wq step of the slice (steps past S repeat step S - 1 and are not
-    // used; a wave past N reads the last channel block and stores nothing)
-    using BRaw = std::conditional_t<W4, v2i, v4i>;
-    constexpr int kStepB = W4 ? 32 : 64;                           // Wq bytes per row and step
-    BRaw fb[DS];
-    {
-        const int64_t pitch = W4 ? K / 2 : K;                      // bytes per Wq row
-        const int8_t* bp = B + (min(cb, N - 16) + (lane & 15)) * pitch +
-                           static_cast<int64_t>(st0) * kStepB + (kStepB / 4) * (lane >> 4);
-        asm volatile("" ::: "memory");
-#pragma unroll
-        for (int j = 0; j < DS; ++j)
-            fb[j] = *reinterpret_cast<const BRaw*>(bp + kStepB * min(j, S - 1));
-        asm volatile("" ::: "memory");
-    }
-    // this wave's q loads are the ones older than its DS Wq loads;
-    // the barrier publishes every wave's share
-    MASQ_WAIT_VMCNT_LGKM0(DS);
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    // while Wq streams in: u rows of the share (slice partials added in
-    // slice order, into slice 0's rows), then one compensation term per
-    // thread (share token tid / 64, channel tid % 64), k in order
-    float cterm = 0.f;
-    if (early) {
-        float* up = reinterpret_cast<float*>(scm);
-        const int stride = nts * r;                                 // floats per slice
-        for (int idx = 4 * tid; idx < stride; idx += 4 * 256) {
-            v4f v = *reinterpret_cast<const v4f*>(up + idx);
-            for (int s = 1; s < uslices; ++s) v = v + *reinterpret_cast<const v4f*>(up + s * stride + idx);
-            *reinterpret_cast<v4f*>(up + idx) = v;
-        }
-        __syncthreads();
-        if (tmod > 0) {
-            // lane l starts at 8-column chunk l % (r / 8) of its L2 row (the
-            // rows lie 128 or 256 bytes apart, so reading the chunks in the
-            // same order would put every lane on the same banks)
-            const float* ur = up + (tid >> 6) * r;
-            const LT* rr = reinterpret_cast<const LT*>(scm + up_bytes +
-                                                       ((tmod - 1) * kDecCh + (tid & 63)) * rrow);
-            const int nch = r >> 3;
-            for (int j = 0; j < nch; ++j) {
-                const int k0 = 8 * ((j + lane) % nch);
-                float rv[8];
-                Elem<LT>::load8(rr + k0, rv);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) cterm = fmaf(ur[k0 + k], rv[k], cterm);
-            }
-        }
-    }
-    MASQ_SCHED_FENCE();
-    v4i acc = {0, 0, 0, 0};
-    {
-        const int rt = lane & 15;
-        const uint8_t* rd = sq + rt * 64 + (((lane >> 4) ^ swz4(rt)) << 4);
-        const v4i zero = {0, 0, 0, 0};
-#pragma unroll
-        for (int j = 0; j < DS; ++j) {
-            // steps past S multiply zeros (MFMA does not branch on lanes)
-            v4i fa = *reinterpret_cast<const v4i*>(rd + min(j, S - 1) * 1024);
-            fa = j < S ? fa : zero;
-            if constexpr (W4)
-                acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, w4_operand(fb[j]), acc, 0, 0, 0);
-            else
-                acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, fb[j], acc, 0, 0, 0);
-        }
-        if constexpr (W4) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] >>= 4;               // exact: 16 x the sum
-        }
-    }
-    // Hand-over of the partials without cache maintenance: they are written
-    // and read only by agent-scope atomic accesses, which the XCD-local L2
-    // does not hold back, and every store has completed (vmcnt 0) before the
-    // workgroup's arrival is counted.  (A device-scope fence would write
-    // back the whole L2 of the XCD, once per workgroup.)
-    // acc[e]: token 4 (lane / 16) + e, channel cb + lane % 16
-    if (active) {
-        int32_t* pp = part + static_cast<int64_t>(sl) * kSmallMaxT * N + cb + (lane & 15);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int t = 4 * (lane >> 4) + e;
-            if (t < T)
-                __hip_atomic_store(pp + static_cast<int64_t>(t) * N, acc[e], __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-    // the share's compensation terms: fp32 bits in slot ns of the partials
-    if (tmod > 0 && g * kDecCh + (tid & 63) < N)
-        __hip_atomic_store(part + static_cast<int64_t>(ns) * kSmallMaxT * N +
-                               static_cast<int64_t>(sl + (tid >> 6) * ns) * N + g * kDecCh + (tid & 63),
-                           __float_as_int(cterm), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    MASQ_WAIT_VMCNT_LGKM0(0);
-    __syncthreads();
-    if (tid == 0)
-        s_last = __hip_atomic_fetch_add(&tickets[g], 1, __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT) == ns - 1;
-    __syncthreads();
-    if (!s_last) return;
-    if (tid == 0)                       // ready for the next launch
-        __hip_atomic_store(&tickets[g], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-
-    // Everything the outputs need is loaded before any of it is used: the
-    // slice partials of the thread's outputs (slices past ns re-read slice
-    // ns - 1 and are not added), their scales and modality ids, the L2 rows
-    // of the group's channels for every non-text modality (into the q
-    // buffer, free now, slot (m - 1) kDecCh + o, when they fit in
-    // kRStage bytes) and the u rows of the batch; or, when the slices have
-    // formed the compensation terms, those terms.
-    constexpr int kOut = kSmallMaxT * kDecCh / 256;
-    constexpr int kRStage = DS * 1024 < 16384 ? DS * 1024 : 16384;
-    constexpr int kRPieces = kRStage / 16 / 256;                       // per thread
-    int pv[kOut][kDecMaxSlices], mv[kOut], om[kOut];
-    float dxv[kOut], dwv[kOut], cv[kOut];
-#pragma unroll
-    for (int i = 0; i < kOut; ++i) {
-        const int idx = tid + 256 * i;
-        const int t = min(idx / kDecCh, T - 1), ch = min(g * kDecCh + idx % kDecCh, N - 1);
-        int32_t* pa = part + static_cast<int64_t>(t) * N + ch;
-#pragma unroll
-        for (int q = 0; q < kDecMaxSlices; ++q)
-            pv[i][q] = __hip_atomic_load(pa + static_cast<int64_t>(min(q, ns - 1)) * kSmallMaxT * N,
-                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        cv[i] = early ? __int_as_float(__hip_atomic_load(pa + static_cast<int64_t>(ns) * kSmallMaxT * N,
-                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                      : 0.f;
-        dxv[i] = x_scale[t];
-        dwv[i] = w_scale[ch];
-        mv[i] = cmc ? sane_mod(mod[t], n_mod) : 0;
-        om[i] = only_mod >= 0 ? sane_mod(mod[t], n_mod) : -1;
-    }
-    const int row_bytes = r * static_cast<int>(sizeof(LT));
-    const bool staged = cmc && !early && (n_mod - 1) * kDecCh * row_bytes <= kRStage;
-    const int per_row = row_bytes >> 4;                                // 16-byte pieces per row
-    const int pieces = staged ? (n_mod - 1) * kDecCh * per_row : 0;
-    v4i rpc[kRPieces];
-#pragma unroll
-    for (int k = 0; k < kRPieces; ++k) {
-        const int i = min(tid + 256 * k, max(pieces - 1, 0));
-        const int row = i / max(per_row, 1), pc = i - row * max(per_row, 1);
-        const int mm = row / kDecCh, o = row - mm * kDecCh;
-        const int ch = min(g * kDecCh + o, N - 1);
-        if (tid + 256 * k < pieces)
-            rpc[k] = *reinterpret_cast<const v4i*>(
-                reinterpret_cast<const uint8_t*>(r_up + (static_cast<int64_t>(mm) * N + ch) * r) +
-                16 * pc);
-    }
-    // u rows: one v4f of T x r per thread, the k slices in batches of kUB
-    // (the first issued with the loads above), when the batch is small
-    // enough; else the general loop
-    const bool u_fast = cmc && !early && T * r <= 4 * 256;
-    constexpr int kUB = kUBatch;
-    v4f up[kUB];
-    if (u_fast && 4 * tid < T * r) {
-#pragma unroll
-        for (int q = 0; q < kUB; ++q)
-            if (q < uslices)
-                up[q] = *reinterpret_cast<const v4f*>(usrc + static_cast<int64_t>(q) * T * r + 4 * tid);
-    }
-#pragma unroll
-    for (int k = 0; k < kRPieces; ++k) {
-        const int i = tid + 256 * k;
-        if (i < pieces) {
-            const int row = i / per_row, pc = i - row * per_row;
-            *reinterpret_cast<v4i*>(sq + row * row_bytes + 16 * pc) = rpc[k];
-        }
-    }
-    if (u_fast) {
-        if (4 * tid < T * r) {
-            v4f v = up[0];
-#pragma unroll
-            for (int q = 1; q < kUB; ++q)
-                if (q < uslices) v = v + up[q];                     // slice order
-            for (int q0 = kUB; q0 < uslices; q0 += kUB) {
-#pragma unroll
-                for (int q = 0; q < kUB; ++q)
-                    if (q0 + q < uslices)
-                        up[q] = *reinterpret_cast<const v4f*>(
-                            usrc + static_cast<int64_t>(q0 + q) * T * r + 4 * tid);
-#pragma unroll
-                for (int q = 0; q < kUB; ++q)
-                    if (q0 + q < uslices) v = v + up[q];
-            }
-            const int tt = (4 * tid) / r, c = 4 * tid - tt * r;
-            *reinterpret_cast<v4f*>(&su[tt][c]) = v;
-        }
-    } else if (cmc && !early) {
-        small_u_rows(su, u, u_part, n_kslices, T, r, tid);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kOut; ++i) {
-        const int idx = tid + 256 * i;
-        const int t = idx / kDecCh, o = idx % kDecCh, ch = g * kDecCh + o;
-        if (t >= T || ch >= N || om[i] != only_mod) continue;
-        int a = pv[i][0];
-#pragma unroll
-        for (int q = 1; q < kDecMaxSlices; ++q) a += q < ns ? pv[i][q] : 0;
-        float v = (static_cast<float>(a) * dxv[i]) * dwv[i];
-        const int m = mv[i];
-        if (m > 0 && early) {
-            v += cv[i];
-        } else if (m > 0) {
-            float c = 0.f;
-            if (staged) {
-                const LT* rr = reinterpret_cast<const LT*>(sq + ((m - 1) * kDecCh + o) * row_bytes);
-                for (int k0 = 0; k0 < r; k0 += 8) {
-                    float rv[8];
-                    Elem<LT>::load8(rr + k0, rv);
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) c = fmaf(su[t][k0 + k], rv[k], c);
-                }
-            } else {
-                const LT* rr = r_up + (static_cast<int64_t>(m - 1) * N + ch) * r;
-                for (int k0 = 0; k0 < r; k0 += 8) {
-                    float rv[8];
-                    Elem<LT>::load8(rr + k0, rv);
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) c = fmaf(su[t][k0 + k], rv[k], c);
-                }
-            }
-            v += c;
-        }
-        Elem<YT>::store1(y + static_cast<int64_t>(t) * N + ch, v);
-    }
-}
-
 // ================================================================ MAS-only routing
 // Rows grouped by modality (the MAS-only comparator, whose tiles each take
 // one modality's weight): a stable counting sort of the token ids (ids
@@ -3435,26 +3119,6 @@ hipError_t launch_stage1_small(const void* x, DT x_dt, const int32_t* mod, const
     return hipGetLastError();
 }
 
-template <typename YT, typename LT, bool W4>
-static void launch_gemm_decode_t(const int8_t* q, const float* x_scale, const int8_t* wq,
-                                 const float* w_scale, int64_t T, int64_t K, int64_t N,
-                                 const int32_t* mod, const float* u, const float* u_part,
-                                 int n_kslices, int rank, int n_mod, const void* r_up,
-                                 int32_t* part, int* tickets, void* y, hipStream_t s,
-                                 int only_mod = -1) {
-    int ns, sp, ngroups;
-    plan_decode(K, N, ns, sp, ngroups);
-#define MASQ_DECODE(DS)                                                                            \
-    hipLaunchKernelGGL((k_gemm_decode<YT, LT, W4, DS>), dim3(static_cast<unsigned>(ngroups * ns)), \
-                       dim3(256), 0, s, q, wq, x_scale, w_scale, static_cast<int>(T),              \
-                       static_cast<int>(K), static_cast<int>(N), ns, sp, mod, u, u_part,           \
-                       n_kslices, rank, n_mod, static_cast<const LT*>(r_up), part, tickets,        \
-                       static_cast<YT*>(y), only_mod)
-    if (sp <= kDecShort) MASQ_DECODE(kDecShort);
-    else MASQ_DECODE(kDecSteps);
-#undef MASQ_DECODE
-}
-
 hipError_t launch_gemm_decode_mas(const int8_t* q, const float* x_scale, const int8_t* wq,
                                   const float* w_scale, int64_t T, int64_t K, int64_t N,
                                   const int32_t* mod, int n_mod, int32_t* part, int* tickets,
@@ -3464,17 +3128,9 @@ hipError_t launch_gemm_decode_mas(const int8_t* q, const float* x_scale, const i
     plan_decode(K, N, ns, sp, ng);
     if (ns > kDecMaxSlices) return hipErrorInvalidValue;
     for (int m = 0; m < n_mod; ++m) {
-        const int8_t* wm = wq + static_cast<int64_t>(m) * N * K;
-        const float* sm = w_scale + static_cast<int64_t>(m) * N;
-        if (y_dt == DT::BF16)
-            launch_gemm_decode_t<bf16_t, bf16_t, false>(q, x_scale, wm, sm, T, K, N, mod, nullptr,
-                                                         nullptr, 1, 0, n_mod, nullptr, part,
-                                                         tickets, y, s, m);
-        else
-            launch_gemm_decode_t<float, bf16_t, false>(q, x_scale, wm, sm, T, K, N, mod, nullptr,
-                                                        nullptr, 1, 0, n_mod, nullptr, part,
-                                                        tickets, y, s, m);
-        const hipError_t e = hipGetLastError();
+        const hipError_t e = launch_gemm_stream(StreamGemm{
+            q, x_scale, wq + static_cast<int64_t>(m) * N * K, w_scale + static_cast<int64_t>(m) * N, T, K, N,
+            mod, nullptr, 1, 0, n_mod, nullptr, DT::BF16, y, y_dt, false, part, tickets, m, s});
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -3575,21 +3231,12 @@ hipError_t launch_gemm(const int8_t* q, const float* x_scale, const int8_t* wq,
     if (w4 && K % 64 != 0) return hipErrorInvalidValue;
     // row-paired codes are read by the direct-to-LDS GEMM only
     if (a_pair && !paired_codes(T, K)) return hipErrorInvalidValue;
-    int dns = 0, dsp = 0, dng = 0;
-    if (small_path(T, K)) plan_decode(K, N, dns, dsp, dng);
-    if (small_path(T, K) && dec_part != nullptr && dec_tickets != nullptr && acc == nullptr &&
-        dns <= kDecMaxSlices) {
-        const float* uu = cmc ? u : nullptr;
-#define MASQ_DEC(YT, LT) (w4 ? launch_gemm_decode_t<YT, LT, true> : launch_gemm_decode_t<YT, LT, false>)(q, x_scale, wq, w_scale, T, K, N, mod, uu, u_part, n_kslices, rank, n_mod, r_up, dec_part, dec_tickets, y, s, -1)
-        if (y_dt == DT::BF16) {
-            if (lr_dt == DT::BF16) MASQ_DEC(bf16_t, bf16_t);
-            else MASQ_DEC(bf16_t, float);
-        } else {
-            if (lr_dt == DT::BF16) MASQ_DEC(float, bf16_t);
-            else MASQ_DEC(float, float);
-        }
-#undef MASQ_DEC
-        return hipGetLastError();
+    if (small_path(T, K) && dec_part != nullptr && dec_tickets != nullptr && acc == nullptr) {
+        const bool parts = u_part != nullptr && n_kslices > 1;
+        return launch_gemm_stream(StreamGemm{q, x_scale, wq, w_scale, T, K, N, mod,
+                                             cmc ? (parts ? u_part : u) : nullptr, parts ? n_kslices : 1,
+                                             rank, n_mod, r_up, lr_dt, y, y_dt, w4, dec_part, dec_tickets,
+                                             -1, s});
     }
     if (small_path(T, K)) {
         const float* uu = cmc ? u : nullptr;
@@ -3636,9 +3283,10 @@ template <typename XT, typename LT, typename YT>
 static void launch_comp_t(const void* x, const int32_t* mod, const float* inv_s, const void* ld,
                           const void* ru, int64_t T, int64_t K, int64_t N, int rank, int n_mod,
                           void* y, hipStream_t s) {
-    // channel groups: about 512 workgroups in all, at least a block for each wave
+    // channel groups: about 256 workgroups in all (each reads all of L1: 512 took
+    // 147 us against 135 for 8192 x 3584 -> 3584), at least a block for each wave
     const int64_t tiles = (T + kCompRows - 1) / kCompRows, nb = (N + 31) / 32;
-    int64_t groups = (512 + tiles - 1) / tiles;
+    int64_t groups = (256 + tiles - 1) / tiles;
     if (groups > (nb + kCompWaves - 1) / kCompWaves) groups = (nb + kCompWaves - 1) / kCompWaves;
     const int per = static_cast<int>((nb + groups - 1) / groups);
     const dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>((nb + per - 1) / per));

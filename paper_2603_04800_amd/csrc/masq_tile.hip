@@ -5,8 +5,9 @@
 //   k_gemm_tile      BM x BN output tile per workgroup of WM x WN waves, K in
 //                    128-byte stages DMA'd into a ring of NST LDS buffers,
 //                    optionally split into S slices per tile.
+//   k_gemm_stream    batches of at most 16 tokens (decoding), below.
 //
-// What bounds it: the bytes a compute unit can pull through its DMA path (33
+// What bounds k_gemm_tile: the bytes a compute unit can pull through its DMA path (33
 // to 40 bytes a clock; a 64 x 64 tile needs 16 KB per 64 clocks of MFMA),
 // and at few tokens the weight's stream from HBM.  So the shapes are chosen
 // for bytes in flight: small rings, so that two (128 x 128, 64 KB), three
@@ -427,6 +428,313 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void k_gemm_tile(
     }
 }
 
+// ================================================================ decode GEMM
+// At most 16 tokens: the layer is a stream of Wq from HBM.  A workgroup of
+// four waves owns 64 output channels (16 a wave, v_mfma_i32_16x16x64_i8, the
+// tokens as rows) and one of S k slices; q and Wq come in 128-byte stages
+// through a ring of four LDS buffers filled by DMA (10 KB a stage), three
+// workgroups a CU, so that each CU keeps about 90 KB in flight and a grid of
+// 296 channel groups (18944 channels) is resident at once without a split.
+// With fewer groups the slices hand their int32 partials over through
+// agent-scope stores and an arrival counter per group, as k_gemm_tile does.
+//
+// The compensation of the tokens t with t % S == slice is formed by the
+// workgroup itself while its first stages are in flight: the u slice partials
+// of those tokens are added (thread groups over the slices, then the groups
+// in order), and each thread sums over the rank for its channel.  The terms
+// are handed over beside the partials.
+//
+// only_mod >= 0 (the MAS-only comparator, one launch per modality's weight):
+// only the outputs of tokens of that modality are stored.
+//
+// Measured against the kernel it replaces (each wave's whole slice of Wq in
+// registers, two or three workgroups a CU): 1 token 3584 -> 18944 18.8 ->
+// 14.5 us, 16 tokens 22.7 -> 21.2 us (16.3 without compensation, whose loads
+// hold the ring up for about 4 us; a ring of seven stages, two workgroups a
+// CU, 22.0), 16 tokens 18944 -> 3584 22.7 -> 19.5 us, with packed codes 20.5
+// -> 15.5 us, 4 tokens 8192 -> 28672 62.2 -> 53.7 us.
+constexpr int kStrCh = 64;
+constexpr int kStrStages = 4;
+constexpr int kStrThreads = 256;
+
+template <typename YT, typename LT, bool W4>
+__global__ __launch_bounds__(kStrThreads, 3) void k_gemm_stream(
+    const int8_t* __restrict__ A, const int8_t* __restrict__ B, const float* __restrict__ x_scale,
+    const float* __restrict__ w_scale, int T, int K, int N, int S, const int32_t* __restrict__ mod,
+    const float* __restrict__ u, int u_slices, int r, int n_mod, const LT* __restrict__ r_up,
+    int32_t* __restrict__ part, int* __restrict__ tickets, YT* __restrict__ y, int only_mod) {
+    constexpr int kRowB = W4 ? kTsK / 2 : kTsK;
+    constexpr int kStage = kSmallMaxT * kTsK + kStrCh * kRowB;
+    constexpr int kDmaB = kStrCh * kRowB / 1024 / 4;      // per wave: 2 (W4: 1); q: one for waves 0, 1
+    __shared__ __attribute__((aligned(16))) uint8_t ring[kStrStages * kStage];
+    __shared__ __attribute__((aligned(16))) float terms[kSmallMaxT][kStrCh];
+    __shared__ int s_last;
+    extern __shared__ __attribute__((aligned(16))) float su[];       // [own tokens][r up to whole 64s]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = static_cast<int>(blockIdx.x) / S, sl = static_cast<int>(blockIdx.x) - g * S;
+    const int col0 = g * kStrCh;
+    const int nst_all = (K + kTsK - 1) / kTsK;
+    const int per = (nst_all + S - 1) / S;
+    const int s0 = sl * per;
+    const int ns = min(per, nst_all - s0);                // >= 1 (tile_slices)
+
+    // modalities of this workgroup's tokens (scalar)
+    const bool cmc = u != nullptr;
+    const int own = sl < T ? (T - sl + S - 1) / S : 0;
+    unsigned present = 0;
+    if (cmc)
+        for (int i = 0; i < own; ++i) present |= 1u << sane_mod(mod[sl + i * S], n_mod);
+    present = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(present & ~1u)));
+
+    // u partials: item = 4 columns of one own token, summed over slices
+    // [grp cnt, grp cnt + cnt) by thread group grp (one group when the items
+    // fill the workgroup)
+    const int nit = own * (r >> 2);
+    const int grps = nit > 0 && 2 * nit <= kStrThreads ? min(kStrThreads / nit, 8) : 1;
+    const int cnt = (u_slices + grps - 1) / grps;
+    auto item_sum = [&](int it, int q0, int q1) __attribute__((always_inline)) {
+        const int i = it / (r >> 2), c = it - i * (r >> 2);
+        const float* src = u + static_cast<int64_t>(sl + i * S) * r + 4 * c;
+        const int64_t step = static_cast<int64_t>(T) * r;
+        v4f v = {0.f, 0.f, 0.f, 0.f};
+        for (int q = q0; q < q1; q += 8) {
+            v4f p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] = *reinterpret_cast<const v4f*>(src + min(q + e, q1 - 1) * step);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (q + e < q1) v = v + p[e];              // slice order
+        }
+        return v;
+    };
+
+    // ---- DMA (rows past T or N repeat the last one; pieces past K read the
+    // row's first piece of the stage, their q counts as zeros)
+    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(ring));
+    const int rem = K - (nst_all - 1) * kTsK;
+    const int8_t *srcq, *srcw[kDmaB];
+    int offq, offw[kDmaB];
+    {
+        const int row = (wave & 1) * 8 + (lane >> 3), c = (lane & 7) ^ ts_swz(row);
+        srcq = A + static_cast<int64_t>(min(row, T - 1)) * K + static_cast<int64_t>(s0) * kTsK;
+        offq = 16 * c;
+    }
+#pragma unroll
+    for (int q = 0; q < kDmaB; ++q) {
+        const int row = (wave * kDmaB + q) * (1024 / kRowB) + lane / (kRowB / 16);
+        const int c = W4 ? (lane & 3) ^ ts_swz4(row) : (lane & 7) ^ ts_swz(row);
+        srcw[q] = B + static_cast<int64_t>(min(col0 + row, N - 1)) * (W4 ? K / 2 : K) +
+                  static_cast<int64_t>(s0) * kRowB;
+        offw[q] = 16 * c;
+    }
+    auto issue = [&](int st, int buf) __attribute__((always_inline)) {
+        const bool last = s0 + st == nst_all - 1;
+        const uint32_t base = lds0 + static_cast<uint32_t>(buf * kStage);
+        if (wave < 2)
+            lds_dma16(srcq + static_cast<int64_t>(st) * kTsK + (last && offq >= rem ? 0 : offq),
+                      base + static_cast<uint32_t>(wave * 1024));
+#pragma unroll
+        for (int q = 0; q < kDmaB; ++q)
+            lds_dma16(srcw[q] + static_cast<int64_t>(st) * kRowB +
+                          (last && (W4 ? 2 : 1) * offw[q] >= rem ? 0 : offw[q]),
+                      base + static_cast<uint32_t>(kSmallMaxT * kTsK + (wave * kDmaB + q) * 1024));
+    };
+    auto publish = [&](int younger) __attribute__((always_inline)) {
+        auto wait = [&](auto per_stage) __attribute__((always_inline)) {
+            constexpr int P = decltype(per_stage)::value;
+            static_assert(kStrStages == 4, "counts up to two younger stages");
+            if (younger >= 2) MASQ_WAIT_VMCNT_LGKM0(2 * P);
+            else if (younger == 1) MASQ_WAIT_VMCNT_LGKM0(P);
+            else MASQ_WAIT_VMCNT_LGKM0(0);
+        };
+        if (wave < 2) wait(std::integral_constant<int, kDmaB + 1>{});
+        else wait(std::integral_constant<int, kDmaB>{});
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    for (int st = 0; st < kStrStages - 1 && st < ns; ++st) issue(st, st);
+
+    // ---- compensation terms of the own tokens: one copy of the code for
+    // every token and rank (rows of su padded with zeros to whole chunks of 64
+    // columns)
+    if (present) {
+        const int ch = min(col0 + lane, N - 1);
+        const int rp = (r + 63) & ~63;
+        Raw8<LT> rv[8];                                              // 64 columns of the channel's L2 row
+        int have = -1;                                               // (modality, chunk) they are
+        auto load_row = [&](int m, int k0) __attribute__((always_inline)) {
+            const LT* rr = r_up + (static_cast<int64_t>(m - 1) * N + ch) * r;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) rv[q].load(rr + min(k0 + 8 * q, r - 8));
+            have = m * 64 + (k0 >> 6);
+        };
+        load_row(__builtin_ctz(present), 0);                         // in flight beside the u partials
+        for (int i = tid; i < own * ((rp - r) >> 2); i += kStrThreads) {
+            const int row = i / max((rp - r) >> 2, 1), c = i - row * ((rp - r) >> 2);
+            *reinterpret_cast<v4f*>(su + row * rp + r + 4 * c) = v4f{0.f, 0.f, 0.f, 0.f};
+        }
+        auto put = [&](int it, v4f v) __attribute__((always_inline)) {
+            const int row = it / (r >> 2), c = it - row * (r >> 2);
+            *reinterpret_cast<v4f*>(su + row * rp + 4 * c) = v;
+        };
+        v4f* tmp = reinterpret_cast<v4f*>(&terms[0][0]);             // grps nit <= 256 items
+        for (int it0 = tid; it0 < grps * nit; it0 += kStrThreads) {
+            const int grp = it0 / nit, it = it0 - grp * nit;
+            const v4f v = item_sum(it, min(grp * cnt, u_slices), min((grp + 1) * cnt, u_slices));
+            if (grps > 1) tmp[it0] = v;
+            else put(it, v);
+        }
+        __syncthreads();
+        if (grps > 1) {
+            if (tid < nit) {
+                v4f v = tmp[tid];
+                for (int q = 1; q < grps; ++q)
+                    if (q * cnt < u_slices) v = v + tmp[q * nit + tid];
+                put(tid, v);
+            }
+            __syncthreads();
+        }
+#pragma unroll 1
+        for (int i = wave; i < own; i += 4) {                        // wave-uniform
+            const int m = __builtin_amdgcn_readfirstlane(sane_mod(mod[sl + i * S], n_mod));
+            float term = 0.f;
+            if (m > 0) {
+#pragma unroll 1
+                for (int k0 = 0; k0 < r; k0 += 64) {
+                    if (have != m * 64 + (k0 >> 6)) load_row(m, k0);
+                    const float* ur = su + i * rp + k0;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        float f[8], uv[8];
+                        rv[q].to_f32(f);
+                        load8_f32(ur + 8 * q, uv);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) term = fmaf(uv[e], f[e], term);
+                    }
+                }
+                if (S > 1 && col0 + lane < N)
+                    __hip_atomic_store(part + static_cast<int64_t>(S) * kSmallMaxT * N +
+                                           static_cast<int64_t>(sl + i * S) * N + col0 + lane,
+                                       __float_as_int(term), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (S == 1) terms[i][lane] = term;
+        }
+        // every load of this block is complete, so that none of its registers
+        // is waited for in the main loop (which would drain the DMA ring)
+        MASQ_WAIT_VMCNT_LGKM0(0);
+    }
+
+    // ---- main loop
+    v4i acc = {0, 0, 0, 0};
+    auto compute = [&](int buf, int valid) __attribute__((always_inline)) {
+        const uint8_t* sa = ring + buf * kStage;
+        const uint8_t* sb = sa + kSmallMaxT * kTsK;
+        const int rw = lane & 15, cg = lane >> 4, brow = 16 * wave + rw;
+        const v4i zero = {0, 0, 0, 0};
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const int c = 4 * ks + cg;
+            v4i fa = *reinterpret_cast<const v4i*>(sa + rw * kTsK + ((c ^ ts_swz(rw)) << 4));
+            if (valid < 8) fa = c < valid ? fa : zero;
+            v4i fb;
+            if constexpr (W4)
+                fb = w4_operand(*reinterpret_cast<const v2i*>(
+                    sb + brow * kRowB + (((c >> 1) ^ ts_swz4(brow)) << 4) + 8 * (c & 1)));
+            else
+                fb = *reinterpret_cast<const v4i*>(sb + brow * kRowB + ((c ^ ts_swz(brow)) << 4));
+            acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, fb, acc, 0, 0, 0);
+        }
+    };
+    int st = 0, cur = 0, nxt = kStrStages - 1;
+    for (; st + kStrStages - 1 < ns; ++st) {
+        publish(kStrStages - 2);
+        issue(st + kStrStages - 1, nxt);
+        compute(cur, 8);
+        cur = (cur + 1) & (kStrStages - 1);
+        nxt = (nxt + 1) & (kStrStages - 1);
+    }
+    for (; st < ns; ++st) {
+        publish(min(ns - 1 - st, kStrStages - 2));
+        compute(cur, s0 + st == nst_all - 1 ? rem >> 4 : 8);
+        cur = (cur + 1) & (kStrStages - 1);
+    }
+    if constexpr (W4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] >>= 4;                    // exact: 16 x the sum
+    }
+    // acc[e]: token 4 (lane / 16) + e, channel col0 + 16 wave + lane % 16
+    const int ch = col0 + 16 * wave + (lane & 15);
+    if (S == 1) {
+        __syncthreads();                                             // terms (written before the loop)
+        if (ch >= N) return;
+        const float dw = w_scale[ch];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int t = 4 * (lane >> 4) + e;
+            if (t >= T) continue;
+            const int m = (cmc || only_mod >= 0) ? sane_mod(mod[t], n_mod) : 0;
+            if (only_mod >= 0 && m != only_mod) continue;
+            float v = (static_cast<float>(acc[e]) * x_scale[t]) * dw;
+            if (cmc && m > 0) v += terms[t][16 * wave + (lane & 15)];
+            Elem<YT>::store1(y + static_cast<int64_t>(t) * N + ch, v);
+        }
+        return;
+    }
+    // Hand-over without cache maintenance: agent-scope accesses, every store
+    // complete (vmcnt 0) before the workgroup's arrival is counted.
+    if (ch < N) {
+        int32_t* pp = part + static_cast<int64_t>(sl) * kSmallMaxT * N + ch;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int t = 4 * (lane >> 4) + e;
+            if (t < T)
+                __hip_atomic_store(pp + static_cast<int64_t>(t) * N, acc[e], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    MASQ_WAIT_VMCNT_LGKM0(0);
+    __syncthreads();
+    if (tid == 0)
+        s_last = __hip_atomic_fetch_add(&tickets[g], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == S - 1;
+    __syncthreads();
+    if (!s_last) return;
+    if (tid == 0)                       // ready for the next launch
+        __hip_atomic_store(&tickets[g], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // each thread finishes channel tid % 64 of tokens tid / 64 + 4 j
+    constexpr int kOut = kSmallMaxT / 4;
+    const int o = min(col0 + lane, N - 1);
+    int pv[kOut][kDecMaxSlices], mv[kOut];
+    float dxv[kOut], cv[kOut];
+    const float dw = w_scale[o];
+#pragma unroll
+    for (int j = 0; j < kOut; ++j) {
+        const int t = min(wave + 4 * j, T - 1);
+        const int32_t* pa = part + static_cast<int64_t>(t) * N + o;
+#pragma unroll
+        for (int q = 0; q < kDecMaxSlices; ++q)
+            pv[j][q] = __hip_atomic_load(pa + static_cast<int64_t>(min(q, S - 1)) * kSmallMaxT * N,
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        cv[j] = cmc ? __int_as_float(__hip_atomic_load(pa + static_cast<int64_t>(S) * kSmallMaxT * N,
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    : 0.f;
+        dxv[j] = x_scale[t];
+        mv[j] = (cmc || only_mod >= 0) ? sane_mod(mod[t], n_mod) : 0;
+    }
+    if (col0 + lane >= N) return;
+#pragma unroll
+    for (int j = 0; j < kOut; ++j) {
+        const int t = wave + 4 * j;
+        if (t >= T || (only_mod >= 0 && mv[j] != only_mod)) continue;
+        int a = pv[j][0];
+#pragma unroll
+        for (int q = 1; q < kDecMaxSlices; ++q) a += q < S ? pv[j][q] : 0;
+        float v = (static_cast<float>(a) * dxv[j]) * dw;
+        if (cmc && mv[j] > 0) v += cv[j];
+        Elem<YT>::store1(y + static_cast<int64_t>(t) * N + col0 + lane, v);
+    }
+}
+
 template <typename YT, typename LT, bool CMC, bool ACC, bool W4>
 hipError_t launch_tile_t(const TileGemm& g) {
     const int bm = kTileShapes[g.plan.shape].bm, bn = kTileShapes[g.plan.shape].bn;
@@ -455,7 +763,31 @@ hipError_t launch_tile_w(const TileGemm& g) {
     return g.w4 ? launch_tile_t<YT, LT, CMC, ACC, true>(g) : launch_tile_t<YT, LT, CMC, ACC, false>(g);
 }
 
+template <typename YT, typename LT, bool W4>
+hipError_t launch_stream_t(const StreamGemm& g) {
+    int ns = 0, sp = 0, groups = 0;
+    plan_decode(g.K, g.N, ns, sp, groups);
+    const int S = stream_slices(g.K, groups, ns);
+    const size_t lds = g.u != nullptr ? static_cast<size_t>((g.T + S - 1) / S) * ((g.rank + 63) / 64 * 64) * sizeof(float)
+                                      : 0;
+    hipLaunchKernelGGL((k_gemm_stream<YT, LT, W4>), dim3(static_cast<unsigned>(groups * S)),
+                       dim3(kStrThreads), lds, g.stream, g.q, g.wq, g.x_scale, g.w_scale,
+                       static_cast<int>(g.T), static_cast<int>(g.K), static_cast<int>(g.N), S, g.mod, g.u,
+                       g.u_slices, g.rank, g.n_mod, static_cast<const LT*>(g.r_up), g.part, g.tickets,
+                       static_cast<YT*>(g.y), g.only_mod);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_gemm_stream(const StreamGemm& g) {
+    if (!small_path(g.T, g.K) || g.N % 16 != 0 || g.part == nullptr || g.tickets == nullptr)
+        return hipErrorInvalidValue;
+#define MASQ_STREAM(YT, LT) (g.w4 ? launch_stream_t<YT, LT, true>(g) : launch_stream_t<YT, LT, false>(g))
+    if (g.y_dt == DT::BF16) return g.lr_dt == DT::BF16 ? MASQ_STREAM(bf16_t, bf16_t) : MASQ_STREAM(bf16_t, float);
+    return g.lr_dt == DT::BF16 ? MASQ_STREAM(float, bf16_t) : MASQ_STREAM(float, float);
+#undef MASQ_STREAM
+}
 
 hipError_t launch_gemm_tile(const TileGemm& g) {
     if (g.K % 16 != 0 || g.N % 16 != 0 || g.plan.S < 1 || (g.w4 && g.K % 64 != 0) ||

@@ -658,11 +658,14 @@ def test_standalone_compensation_edges(ops, T, K, N, r, M, act, lr, y_dtype):
 
 
 @pytest.mark.parametrize("T,K,N,r,M,lr,bits", [
-    # slices of 28 steps and fewer (three workgroups a CU), 29 and more
+    # one stage of 128 codes or part of one, a few, ring wrap-around; channel
+    # groups of 64 with remainders
     (1, 64, 16, 16, 2, "bf16", 8), (16, 1792, 144, 64, 2, "bf16", 8), (7, 1856, 80, 32, 3, "bf16", 4),
     (16, 3584, 208, 64, 4, "f32", 8), (1, 3584, 1040, 64, 2, "bf16", 4), (13, 2688, 64, 128, 2, "bf16", 8),
-    # operands past the smaller compensation buffer: u added by the last slice
-    (16, 3584, 96, 256, 2, "f32", 8), (16, 14336, 80, 64, 4, "bf16", 8),
+    # no slices (256 groups and more), every slice count up to 8, rows past
+    # 20480 columns; ranks up to 256, fewer tokens than slices
+    (16, 192, 16400, 80, 3, "bf16", 8), (9, 128, 16400, 48, 2, "f32", 4), (16, 3584, 96, 256, 2, "f32", 8),
+    (16, 14336, 80, 64, 4, "bf16", 8), (3, 18944, 64, 16, 2, "bf16", 4), (16, 20544, 48, 64, 2, "bf16", 8),
 ])
 def test_decode_gemm_step_counts(ops, T, K, N, r, M, lr, bits):
     L = _random_layer(T, K, N, r, M, "bf16", lr, weight_bits=bits, seed=T + K)
