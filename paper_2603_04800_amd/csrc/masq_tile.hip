@@ -469,7 +469,7 @@ __global__ __launch_bounds__(kStrThreads, 3) void k_gemm_stream(
     __shared__ __attribute__((aligned(16))) uint8_t ring[kStrStages * kStage];
     __shared__ __attribute__((aligned(16))) float terms[kSmallMaxT][kStrCh];
     __shared__ int s_last;
-    extern __shared__ __attribute__((aligned(16))) float su[];       // [own tokens][r up to whole 64s]
+    extern __shared__ __attribute__((aligned(16))) float su[];       // [own tokens][r]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = static_cast<int>(blockIdx.x) / S, sl = static_cast<int>(blockIdx.x) - g * S;
@@ -556,11 +556,9 @@ __global__ __launch_bounds__(kStrThreads, 3) void k_gemm_stream(
     for (int st = 0; st < kStrStages - 1 && st < ns; ++st) issue(st, st);
 
     // ---- compensation terms of the own tokens: one copy of the code for
-    // every token and rank (rows of su padded with zeros to whole chunks of 64
-    // columns)
+    // every token and rank
     if (present) {
         const int ch = min(col0 + lane, N - 1);
-        const int rp = (r + 63) & ~63;
         Raw8<LT> rv[8];                                              // 64 columns of the channel's L2 row
         int have = -1;                                               // (modality, chunk) they are
         auto load_row = [&](int m, int k0) __attribute__((always_inline)) {
@@ -570,13 +568,9 @@ __global__ __launch_bounds__(kStrThreads, 3) void k_gemm_stream(
             have = m * 64 + (k0 >> 6);
         };
         load_row(__builtin_ctz(present), 0);                         // in flight beside the u partials
-        for (int i = tid; i < own * ((rp - r) >> 2); i += kStrThreads) {
-            const int row = i / max((rp - r) >> 2, 1), c = i - row * ((rp - r) >> 2);
-            *reinterpret_cast<v4f*>(su + row * rp + r + 4 * c) = v4f{0.f, 0.f, 0.f, 0.f};
-        }
         auto put = [&](int it, v4f v) __attribute__((always_inline)) {
             const int row = it / (r >> 2), c = it - row * (r >> 2);
-            *reinterpret_cast<v4f*>(su + row * rp + 4 * c) = v;
+            *reinterpret_cast<v4f*>(su + row * r + 4 * c) = v;
         };
         v4f* tmp = reinterpret_cast<v4f*>(&terms[0][0]);             // grps nit <= 256 items
         for (int it0 = tid; it0 < grps * nit; it0 += kStrThreads) {
@@ -603,9 +597,10 @@ __global__ __launch_bounds__(kStrThreads, 3) void k_gemm_stream(
 #pragma unroll 1
                 for (int k0 = 0; k0 < r; k0 += 64) {
                     if (have != m * 64 + (k0 >> 6)) load_row(m, k0);
-                    const float* ur = su + i * rp + k0;
+                    const float* ur = su + i * r + k0;
 #pragma unroll
                     for (int q = 0; q < 8; ++q) {
+                        if (k0 + 8 * q >= r) break;                  // uniform; no product past r (0 x inf)
                         float f[8], uv[8];
                         rv[q].to_f32(f);
                         load8_f32(ur + 8 * q, uv);
@@ -768,7 +763,7 @@ hipError_t launch_stream_t(const StreamGemm& g) {
     int ns = 0, sp = 0, groups = 0;
     plan_decode(g.K, g.N, ns, sp, groups);
     const int S = stream_slices(g.K, groups, ns);
-    const size_t lds = g.u != nullptr ? static_cast<size_t>((g.T + S - 1) / S) * ((g.rank + 63) / 64 * 64) * sizeof(float)
+    const size_t lds = g.u != nullptr ? static_cast<size_t>((g.T + S - 1) / S) * g.rank * sizeof(float)
                                       : 0;
     hipLaunchKernelGGL((k_gemm_stream<YT, LT, W4>), dim3(static_cast<unsigned>(groups * S)),
                        dim3(kStrThreads), lds, g.stream, g.q, g.wq, g.x_scale, g.w_scale,

@@ -681,3 +681,22 @@ def test_decode_gemm_step_counts(ops, T, K, N, r, M, lr, bits):
 def test_quantisation_and_down_projection_in_one_launch(ops, T, K, N, r, M, act, lr):
     L = _random_layer(T, K, N, r, M, act, lr, zero_rows=(T // 2,), seed=T + K)
     _check_layer(ops, L, name="one launch")
+
+
+@pytest.mark.parametrize("T,K,N,r,lr", [(5, 128, 16400, 16, "bf16"), (16, 3584, 208, 80, "bf16"), (9, 2688, 64, 48, "f32")])
+def test_decode_keeps_an_infinite_factor_infinite(ops, T, K, N, r, lr):
+    """An infinite entry in the last column of L2: its channel is infinite for
+    the vision tokens (the terms are fp32 sums over r products and no others),
+    every other output keeps its bits."""
+    from paper_2603_04800_amd import workload
+    L = _random_layer(T, K, N, r, 2, "f32", lr, seed=T + r)
+    x, mod, lin = workload.to_device(L)
+    y = _np(lin(x, mod))
+    c = N - 3
+    L["r_up"][0, c, r - 1] = np.inf
+    x, mod, lin = workload.to_device(L)
+    yi = _np(lin(x, mod))
+    vision = L["modality"] == 1
+    assert np.isinf(yi[vision, c]).all()
+    yi[vision, c] = y[vision, c]
+    assert np.array_equal(yi, y)
