@@ -84,7 +84,7 @@ static void plan_kslices(int64_t T, int64_t K, int& n_kslices, int& kslice) {
 
 // The layout for a given tile plan of the GEMM.
 static Workspace carve_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, int n_mod,
-                                 TilePlan tile) {
+                                 TilePlan tile, int dl_quarters) {
     Workspace w{};
     w.tile = tile;
     w.kslice = static_cast<int>(K);
@@ -148,13 +148,18 @@ static Workspace carve_workspace(void* base, int64_t T, int64_t K, int64_t N, in
     w.dw_slices = w.dw_kslice = 0;
     w.dw_part = nullptr;
     w.dl_part = nullptr;
+    w.dl_quarters = w.dl_slices = 0;
     const bool cmc64 = rank > 0 && rank <= 64 && n_mod > 1 && !small_path(T, K);
     const bool dw = cmc64 && down_wide(T, K);
     const bool dl = kStage1SplitDown && cmc64 && K % 64 == 0;
     if (dw) plan_down_wide(T, K, w.dw_slices, w.dw_kslice);
+    if (dl) {
+        w.dl_quarters = dl_quarters;
+        w.dl_slices = down_lds_slices(K, dl_quarters);
+    }
     const size_t row_bytes = static_cast<size_t>(T) * static_cast<size_t>(rank) * sizeof(float);
     const size_t part_bytes = std::max(dw ? w.dw_slices * row_bytes : 0,
-                                       dl ? down_lds_slices(T, K) * row_bytes : 0);
+                                       dl ? w.dl_slices * row_bytes : 0);
     if (part_bytes > 0) {
         float* p = reinterpret_cast<float*>(carve(part_bytes));
         if (dw) w.dw_part = p;
@@ -170,18 +175,26 @@ static Workspace carve_workspace(void* base, int64_t T, int64_t K, int64_t N, in
 
 // The size is that of the 256 x 256 tiles' layout whatever the plan, so that
 // it does not depend on which kernel runs; a small-tile plan takes as many
-// slices as that holds (one slice needs no accumulators).
+// slices as that holds (one slice needs no accumulators).  The shorter slices
+// of k_down_lds (down_lds_quarters) are taken where that size has room for
+// their partials, or where no accumulators are held at all (the workspace is
+// then a few MB: at most 128 x 128 rows of 256 columns of codes, and 8 MB of
+// partials, far below the allocation-free call's scratch).
 Workspace plan_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, int n_mod,
                          bool w4) {
-    Workspace w = carve_workspace(base, T, K, N, rank, n_mod, TilePlan{-1, 1});
+    const int long_q = 4 * down_lds_chunks(T, K), dl_q = down_lds_quarters(T, K);
+    Workspace w = carve_workspace(base, T, K, N, rank, n_mod, TilePlan{-1, 1}, long_q);
     TilePlan tile = small_path(T, K) ? TilePlan{-1, 1} : plan_tile(T, K, N, true, w4);
-    if (tile.shape < 0) return w;
     const size_t bytes = w.bytes;
-    for (;; tile.S = tile_slices(K, tile.S - 1)) {
-        w = carve_workspace(base, T, K, N, rank, n_mod, tile);
+    for (; tile.shape >= 0; tile.S = tile_slices(K, tile.S - 1)) {
+        w = carve_workspace(base, T, K, N, rank, n_mod, tile, long_q);
         if (w.bytes <= bytes || tile.S <= 1) break;
     }
-    w.bytes = bytes;
+    if (w.dl_slices > 0 && dl_q < long_q) {
+        const Workspace f = carve_workspace(base, T, K, N, rank, n_mod, tile, dl_q);
+        if (f.gk_splits == 1 || f.bytes <= bytes) w = f;
+    }
+    if (w.bytes < bytes) w.bytes = bytes;
     return w;
 }
 
@@ -347,9 +360,9 @@ masq_status fused_stage(const Fused& a, int stage) {
         // tiles, then the quantisation adding its slice partials into u (and
         // its bf16 hi/lo rows)
         st = from_hip(masq::launch_down_lds(a.x, a.modality, a.inv_smooth, a.l_down, a.T, a.c_in,
-                                            a.rank, a.n_mod, w.dl_part, s));
+                                            a.rank, a.n_mod, w.dl_quarters, w.dl_part, s));
         if (st != MASQ_OK) return st;
-        const masq::UFinish fin{w.dl_part, masq::down_lds_slices(a.T, a.c_in), a.rank, w.u, w.u_hl};
+        const masq::UFinish fin{w.dl_part, w.dl_slices, a.rank, w.u, w.u_hl};
         st = from_hip(masq::launch_smooth_quant(a.x, to_dt(a.x_dt), a.modality, a.inv_smooth,
                                                 a.T, a.c_in, a.n_mod, w.q, w.x_scale,
                                                 w.zero_base, w.n_zero, s, &fin, w.pair));

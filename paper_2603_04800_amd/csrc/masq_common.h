@@ -159,7 +159,8 @@ struct Workspace {
     int* zero_base;
     int dw_slices, dw_kslice;   // plan_down_wide (dw_part != nullptr)
     float* dw_part;    // [dw_slices][T][rank] fp32 partials of the wide down-projection
-    float* dl_part;    // [down_lds_slices(T, K)][T][rank] fp32 partials of k_down_lds
+    int dl_quarters, dl_slices;   // k slices of k_down_lds (dl_part != nullptr)
+    float* dl_part;    // [dl_slices][T][rank] fp32 partials of k_down_lds
     int n_kslices;
     int kslice;
     size_t bytes;
@@ -225,7 +226,7 @@ inline bool stage1_fr_ok(DT x_dt, int64_t K, int n_mod) {
 }
 // Down-projection with the L1 fragments staged in LDS (k_down_lds): bf16
 // activations and factors, rank <= 64, K % 64 == 0; slice partials
-// [down_lds_slices(T, K)][T][rank] for the quantisation kernel to add.
+// [slices][T][rank] for the quantisation kernel to add.
 constexpr int64_t kDownLdsCols = 256;    // columns staged in LDS at a time (a chunk)
 constexpr int64_t kDownLdsRows = 128;    // rows of a workgroup's tile
 // Chunks per k slice: the workgroups (two per CU: 66 KB of LDS each) stream
@@ -239,10 +240,20 @@ inline int down_lds_chunks(int64_t T, int64_t K) {
     const int64_t n = (tiles * chunks + kDownLdsWgs - 1) / kDownLdsWgs;
     return static_cast<int>(n < 1 ? 1 : (n > chunks ? chunks : n));
 }
-inline int down_lds_slices(int64_t T, int64_t K) {
+// Quarters (64 columns) per k slice.  Batches whose chunks are at most half
+// as many workgroups as compute units take slices of two: a workgroup's time
+// is its quarters' latency, one after the other, and the chip has room for
+// twice the workgroups.  Layers, with the u partials added beside the codes:
+// 64 tokens 3584 -> 18944 28.6 -> 25.8 us, 333 x 3584 -> 3584 (two non-text
+// modalities) 27.7 -> 25.8 us, 1000 x 3584 -> 18944 W4A8 105.2 -> 101.9 us;
+// slices of one quarter up to 64 chunks were no faster (25.8, 25.9 us).
+inline int down_lds_quarters(int64_t T, int64_t K) {
     const int64_t chunks = (K + kDownLdsCols - 1) / kDownLdsCols;
-    const int n = down_lds_chunks(T, K);
-    return static_cast<int>((chunks + n - 1) / n);
+    const int64_t tiles = (T + kDownLdsRows - 1) / kDownLdsRows;
+    return tiles * chunks <= 128 ? 2 : 4 * down_lds_chunks(T, K);
+}
+inline int down_lds_slices(int64_t K, int quarters) {
+    return static_cast<int>(((K + 63) / 64 + quarters - 1) / quarters);
 }
 inline bool down_lds_ok(DT x_dt, int64_t K) { return x_dt == DT::BF16 && K % 64 == 0; }
 // Stage 1 of the fused layer for rows that k_stage1_fr cannot hold: k_down_lds,
@@ -261,7 +272,7 @@ constexpr bool kStage1SplitDown = true;
 inline bool stage1_fr_first(int64_t T, int n_mod) { return T >= kFusedFullT && n_mod <= 2; }
 hipError_t launch_down_lds(const void* x, const int32_t* mod, const float* inv_s,
                            const void* l_down, int64_t T, int64_t K, int rank, int n_mod,
-                           float* part, hipStream_t s);
+                           int quarters, float* part, hipStream_t s);
 
 hipError_t launch_stage1_fused(const void* x, DT x_dt, const int32_t* mod, const float* inv_s,
                                const void* l_down, int64_t T, int64_t K, int rank, int n_mod,

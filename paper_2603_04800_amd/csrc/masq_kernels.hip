@@ -161,9 +161,13 @@ __global__ __launch_bounds__(256) void k_smooth_quant(const XT* __restrict__ x,
                                                       int64_t T, UFinish fin, bool pair) {
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < n_zero; i += 256) zero_ints[i] = 0;
-    if (fin.part != nullptr && threadIdx.x < 64)
-        finish_u_row(blockIdx.x, T, sane_mod(mod[blockIdx.x], n_mod) == 0, fin.part, fin.slices,
-                     fin.r, fin.u, fin.u_hl, threadIdx.x);
+    if (blockIdx.x >= T) {              // u of four rows, beside the rows' codes
+        const int64_t t = (static_cast<int64_t>(blockIdx.x) - T) * 4 + (threadIdx.x >> 6);
+        if (t < T)
+            finish_u_row(t, T, sane_mod(mod[t], n_mod) == 0, fin.part, fin.slices, fin.r, fin.u,
+                         fin.u_hl, threadIdx.x & 63);
+        return;
+    }
     sq_row<XT, 256, kSqChunks>(x, mod, inv_s, K, n_mod, q, x_scale, blockIdx.x, pair);
 }
 
@@ -1056,8 +1060,8 @@ __global__ __launch_bounds__(64 * kFuseWaves) void k_stage1_fused(
 
 // ---------------------------------------------------------------- down-projection, operands in LDS
 // u = xs L1^m for bf16 activations and factors (rank <= 64), as slice
-// partials part[s][t][0 .. r) over k slices of nchunk chunks of kDlCols
-// columns; grid (ceil(T / 128), S).  A workgroup of 8 waves owns 128 rows
+// partials part[s][t][0 .. r) over k slices of nquart 64-column quarters;
+// grid (ceil(T / 128), S).  A workgroup of 8 waves owns 128 rows
 // and one slice, which it streams in 64-column quarters through a ring of
 // kDlBufs LDS buffers filled by DMA, kDlAhead quarters ahead of the one
 // being multiplied (one barrier a quarter).  A quarter's buffer holds the
@@ -1074,8 +1078,6 @@ __global__ __launch_bounds__(64 * kFuseWaves) void k_stage1_fused(
 // the same 128 rows read their operands from global memory afterwards.
 // Tiles without non-text rows return at once: text rows' partials are never
 // read (finish_u_row).
-constexpr int kDlCols = 256;                        // chunk width of the slice plan
-static_assert(kDlCols == kDownLdsCols, "chunk width of the workspace plan");
 constexpr int kDlRows = 128;
 static_assert(kDlRows == kDownLdsRows, "row tile of the workspace plan");
 constexpr int kDlWaves = kDlRows / 16;
@@ -1109,7 +1111,7 @@ __device__ __forceinline__ void dl_wait(int n) {
 
 __device__ __forceinline__ void down_lds_tile(
     const bf16_t* __restrict__ x, const int32_t* __restrict__ mod, const float* __restrict__ inv_s,
-    const bf16_t* __restrict__ l_down, int64_t T, int K, int r, int n_mod, int nchunk,
+    const bf16_t* __restrict__ l_down, int64_t T, int K, int r, int n_mod, int nquart,
     float* __restrict__ part, int tile, int s) {
     __shared__ __attribute__((aligned(16))) DlQuarter sb[kDlBufs];          // 132 KB
     __shared__ int smod[kDlRows];
@@ -1141,8 +1143,8 @@ __device__ __forceinline__ void down_lds_tile(
     const int64_t trow = row0 + 16 * wave + ar;
     const bool valid = trow < T;
     const int mrow = smod[16 * wave + ar];
-    const int qb = s * nchunk * (kDlCols / 64);     // first quarter of the slice
-    const int nq = min(nchunk * (kDlCols / 64), npairs - qb);   // its quarters, >= 1
+    const int qb = s * nquart;                      // first quarter of the slice
+    const int nq = min(nquart, npairs - qb);        // its quarters, >= 1
     const int g = 2 + kDlFragOps * nsl + (wave == 0 ? 1 : 0);   // DMA instructions per quarter, this wave
 
     // quarter h into buffer h % kDlBufs: (wave 0) the factors, lane i those
@@ -1273,9 +1275,9 @@ __device__ __forceinline__ void down_lds_tile(
 
 __global__ __launch_bounds__(64 * kDlWaves) void k_down_lds(
     const bf16_t* __restrict__ x, const int32_t* __restrict__ mod, const float* __restrict__ inv_s,
-    const bf16_t* __restrict__ l_down, int64_t T, int K, int r, int n_mod, int nchunk,
+    const bf16_t* __restrict__ l_down, int64_t T, int K, int r, int n_mod, int nquart,
     float* __restrict__ part) {
-    down_lds_tile(x, mod, inv_s, l_down, T, K, r, n_mod, nchunk, part, blockIdx.x, blockIdx.y);
+    down_lds_tile(x, mod, inv_s, l_down, T, K, r, n_mod, nquart, part, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------- fused stage 1, rows in registers
@@ -2972,7 +2974,7 @@ hipError_t launch_smooth_quant(const void* x, DT x_dt, const int32_t* mod, const
                                n_mod, q, x_scale, zero_ints, n_zero, fin, pair);
         return hipGetLastError();
     }
-    const dim3 grid(static_cast<unsigned>(T)), block(256);
+    const dim3 grid(static_cast<unsigned>(T + (fin.part != nullptr ? (T + 3) / 4 : 0))), block(256);
     if (x_dt == DT::BF16)
         hipLaunchKernelGGL(k_smooth_quant<bf16_t>, grid, block, 0, s,
                            static_cast<const bf16_t*>(x), mod, inv_s, static_cast<int>(K), n_mod,
@@ -3084,13 +3086,13 @@ hipError_t launch_stage1_fused(const void* x, DT x_dt, const int32_t* mod, const
 
 hipError_t launch_down_lds(const void* x, const int32_t* mod, const float* inv_s,
                            const void* l_down, int64_t T, int64_t K, int rank, int n_mod,
-                           float* part, hipStream_t s) {
+                           int quarters, float* part, hipStream_t s) {
     const dim3 grid(static_cast<unsigned>((T + kDlRows - 1) / kDlRows),
-                    static_cast<unsigned>(down_lds_slices(T, K))),
+                    static_cast<unsigned>(down_lds_slices(K, quarters))),
         block(64 * kDlWaves);
     hipLaunchKernelGGL(k_down_lds, grid, block, 0, s, static_cast<const bf16_t*>(x), mod, inv_s,
                        static_cast<const bf16_t*>(l_down), T, static_cast<int>(K), rank, n_mod,
-                       down_lds_chunks(T, K), part);
+                       quarters, part);
     return hipGetLastError();
 }
 
