@@ -700,3 +700,14 @@ def test_decode_keeps_an_infinite_factor_infinite(ops, T, K, N, r, lr):
     assert np.isinf(yi[vision, c]).all()
     yi[vision, c] = y[vision, c]
     assert np.array_equal(yi, y)
+
+
+@pytest.mark.parametrize("T,K,N,r,M", [
+    # slices of two quarters (an odd count leaves one), around the 128-row
+    # tiles and up to 128 workgroups of chunks; one past it: whole chunks
+    (17, 2048, 80, 64, 2), (128, 2112, 48, 48, 3), (129, 4160, 64, 64, 4), (255, 2240, 320, 16, 2),
+    (256, 8128, 64, 64, 3), (512, 8192, 32, 32, 2), (513, 8192, 32, 64, 3), (1100, 2112, 4128, 64, 2),
+])
+def test_down_projection_slices_of_two_quarters(ops, T, K, N, r, M):
+    L = _random_layer(T, K, N, r, M, "bf16", "bf16", zero_rows=(T // 2,), seed=T + K)
+    _check_layer(ops, L, name="two quarters")
