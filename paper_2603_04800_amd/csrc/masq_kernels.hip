@@ -262,10 +262,17 @@ __global__ __launch_bounds__(256) void k_smooth_quant_rows(const XT* __restrict_
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < n_zero; i += 256) zero_ints[i] = 0;
     const int lane = threadIdx.x & 63;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    const int64_t nb = (T + 3) / 4;
+    const bool apart = gridDim.x > nb;  // u by workgroups of its own, past the rows' (launch_smooth_quant)
+    const bool sum = blockIdx.x >= nb;
+    const int64_t t = (blockIdx.x - (sum ? nb : 0)) * 4 + (threadIdx.x >> 6);
     if (t >= T) return;
+    if (sum) {
+        finish_u_row(t, T, sane_mod(mod[t], n_mod) == 0, fin.part, fin.slices, fin.r, fin.u, fin.u_hl, lane);
+        return;
+    }
     quant_row_wave<XT, NC>(x, mod, inv_s, K, n_mod, q, x_scale, t, pair, lane, [&](int m) {
-        if (fin.part != nullptr)
+        if (fin.part != nullptr && !apart)
             finish_u_row(t, T, m == 0, fin.part, fin.slices, fin.r, fin.u, fin.u_hl, lane);
     });
 }
@@ -2963,7 +2970,12 @@ hipError_t launch_smooth_quant(const void* x, DT x_dt, const int32_t* mod, const
                                 nullptr, zero_ints, n_zero, s, pair, fin);
     // a wave per row for large batches whose rows fit its register cache
     if (T >= kRowsPerWaveMinT && K <= 64 * 8 * 8) {
-        const dim3 grid(static_cast<unsigned>((T + 3) / 4)), block(256);
+        // u by workgroups of its own where the rows' waves are fewer than 16 a
+        // compute unit (333 x 3584: 6.5 -> 5.1 us, 1000 x 3584 8.8 -> 7.8 us);
+        // with more, each row's wave adds its partials while its row is in
+        // flight (8192 x 3584: 20.9 us, apart 22.1 us)
+        const bool apart = fin.part != nullptr && T < kFusedFullT;
+        const dim3 grid(static_cast<unsigned>((T + 3) / 4 * (apart ? 2 : 1))), block(256);
         if (x_dt == DT::BF16)
             hipLaunchKernelGGL((k_smooth_quant_rows<bf16_t, 8>), grid, block, 0, s,
                                static_cast<const bf16_t*>(x), mod, inv_s, T, static_cast<int>(K),
