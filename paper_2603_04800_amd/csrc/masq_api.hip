@@ -384,7 +384,7 @@ masq_status fused_stage(const Fused& a, int stage) {
                                                 w.x_scale, w.u, w.u_hl, w.zero_base, w.n_zero, s,
                                                 w.pair));
         if (st != MASQ_OK) return st;
-    } else if ((stage & 1) && cmc && masq::quant_down_ok(w, a.c_in)) {
+    } else if ((stage & 1) && cmc && masq::quant_down_ok(w, a.T, a.c_in)) {
         st = from_hip(masq::launch_quant_down(a.x, to_dt(a.x_dt), a.modality, a.inv_smooth, a.l_down,
                                               to_dt(a.lr_dt), a.T, a.c_in, a.rank, a.n_mod, w, s));
         if (st != MASQ_OK) return st;

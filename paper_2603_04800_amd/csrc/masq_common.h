@@ -195,9 +195,13 @@ hipError_t launch_lowrank_down(const void* x, DT x_dt, const int32_t* mod, const
 
 // Quantisation and the down-projection in one launch: one k slice of u a
 // tile (no arrival counters, which the launch itself would have to clear).
+// Batches whose tiles and rows together pass a launch's 2^32 threads (512
+// for every 16 rows of u and every 8 of codes: 44.7 million tokens) take the
+// two launches, each of which reaches further.
 constexpr int64_t kQuantDownMaxK = 4096;
-inline bool quant_down_ok(const Workspace& w, int64_t K) {
-    return w.n_kslices == 1 && K <= kQuantDownMaxK;
+inline bool quant_down_ok(const Workspace& w, int64_t T, int64_t K) {
+    return w.n_kslices == 1 && K <= kQuantDownMaxK &&
+           ((T + kDownRows - 1) / kDownRows + (T + 7) / 8) * 512 < (int64_t{1} << 32);
 }
 hipError_t launch_quant_down(const void* x, DT x_dt, const int32_t* mod, const float* inv_s,
                              const void* l_down, DT lr_dt, int64_t T, int64_t K, int rank, int n_mod,

@@ -3037,7 +3037,8 @@ hipError_t launch_quant_down(const void* x, DT x_dt, const int32_t* mod, const f
                              const void* l_down, DT lr_dt, int64_t T, int64_t K, int rank, int n_mod,
                              const Workspace& w, hipStream_t s) {
     static_assert(kQuantDownMaxK == 64 * 8 * 8, "a row in the registers of quant_row_wave<XT, 8>");
-    if (!quant_down_ok(w, K)) return hipErrorInvalidValue;
+    static_assert(kDownWaves == 8, "threads of a workgroup in quant_down_ok");
+    if (!quant_down_ok(w, T, K)) return hipErrorInvalidValue;
     if (x_dt == DT::BF16) {
         if (lr_dt == DT::BF16) launch_quant_down_t<bf16_t, bf16_t>(x, mod, inv_s, l_down, T, K, rank, n_mod, w, s);
         else launch_quant_down_t<bf16_t, float>(x, mod, inv_s, l_down, T, K, rank, n_mod, w, s);

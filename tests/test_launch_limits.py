@@ -1,0 +1,48 @@
+"""The launches of the library's calls, recorded on the CPU (see
+launch_recorder.c): batches and widths at the far end of what the calls
+accept, where a grid of one workgroup per tile, row or group would pass the
+2^32 threads of a launch."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+F32, BF16 = 0, 1
+
+
+@pytest.fixture(scope="module")
+def record(tmp_path_factory):
+    """record(lines) -> [(status, [(grid x, y, z, threads of a workgroup)])]"""
+    gcc = shutil.which("gcc")
+    if gcc is None:
+        pytest.skip("gcc not available")
+    from paper_2603_04800_amd import _libpath
+    libdir = os.path.dirname(_libpath.LIB)
+    exe = str(tmp_path_factory.mktemp("rec") / "launch_recorder")
+    r = subprocess.run([gcc, "-std=gnu99", "-Wall", "-Werror", "-rdynamic", "-I", os.path.join(ROOT, "include"),
+                        os.path.join(ROOT, "tests", "launch_recorder.c"), "-o", exe, "-L", libdir, "-lmasq",
+                        f"-Wl,-rpath,{libdir}", "-Wl,--allow-shlib-undefined"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def run(lines):
+        r = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        out = []
+        for line in r.stdout.splitlines():
+            st, *la = line.split()
+            out.append((int(st), [tuple(int(v) for v in e.split(",")) for e in la]))
+        assert len(out) == len(lines)
+        return out
+    return run
+
+
+@pytest.mark.parametrize("call", [
+    # codes and u in one launch: up to where (T / 16 + T / 8) x 512 threads fit, past it two
+    f"fused 44739200 16 16 16 2 {F32} {F32} {F32} 0", f"fused 44739300 16 16 16 2 {F32} {F32} {F32} 0",
+    f"fused 67000000 16 16 128 2 {BF16} {BF16} {BF16} 0",
+])
+def test_launches_stay_within_the_thread_limit(record, call):
+    status, launches = record([call])[0]
+    assert status == 0 and launches, (call, status, launches)
