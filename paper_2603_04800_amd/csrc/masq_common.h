@@ -7,6 +7,20 @@
 
 namespace masq {
 
+// A grid of n workgroups of `threads`, in one dimension where its threads stay
+// below the 2^32 that the runtime takes in one, else in rows of a multiple of
+// 8 workgroups (the XCDs are dealt in turn as before); the kernel counts them
+// with linear_block() and those past n find no work.
+inline dim3 grid_of(int64_t n, int threads) {
+    const int64_t most = ((int64_t{1} << 32) / threads - 1) / 8 * 8;
+    if (n <= most) return dim3(static_cast<unsigned>(n));
+    const int64_t rows = (n + most - 1) / most, x = ((n + rows - 1) / rows + 7) / 8 * 8;
+    return dim3(static_cast<unsigned>(x), static_cast<unsigned>((n + x - 1) / x));
+}
+__device__ __forceinline__ int64_t linear_block() {
+    return static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+}
+
 // Tile shape of the int8 GEMM: 256 x 256 output tile per workgroup of four
 // wave64s (2 x 2, each wave 128 x 128), 128-byte K stages, double-buffered.
 constexpr int kTileM = 256;

@@ -159,16 +159,17 @@ __global__ __launch_bounds__(256) void k_smooth_quant(const XT* __restrict__ x,
                                                       float* __restrict__ x_scale,
                                                       int* __restrict__ zero_ints, int n_zero,
                                                       int64_t T, UFinish fin, bool pair) {
-    if (blockIdx.x == 0)
+    const int64_t b = linear_block();
+    if (b == 0)
         for (int i = threadIdx.x; i < n_zero; i += 256) zero_ints[i] = 0;
-    if (blockIdx.x >= T) {              // u of four rows, beside the rows' codes
-        const int64_t t = (static_cast<int64_t>(blockIdx.x) - T) * 4 + (threadIdx.x >> 6);
+    if (b >= T) {                       // u of four rows, beside the rows' codes
+        const int64_t t = (b - T) * 4 + (threadIdx.x >> 6);
         if (t < T)
             finish_u_row(t, T, sane_mod(mod[t], n_mod) == 0, fin.part, fin.slices, fin.r, fin.u,
                          fin.u_hl, threadIdx.x & 63);
         return;
     }
-    sq_row<XT, 256, kSqChunks>(x, mod, inv_s, K, n_mod, q, x_scale, blockIdx.x, pair);
+    sq_row<XT, 256, kSqChunks>(x, mod, inv_s, K, n_mod, q, x_scale, b, pair);
 }
 
 // One row t quantised by one wave (lane = this lane), its smoothed values
@@ -2986,7 +2987,10 @@ hipError_t launch_smooth_quant(const void* x, DT x_dt, const int32_t* mod, const
                                n_mod, q, x_scale, zero_ints, n_zero, fin, pair);
         return hipGetLastError();
     }
-    const dim3 grid(static_cast<unsigned>(T + (fin.part != nullptr ? (T + 3) / 4 : 0))), block(256);
+    // a workgroup per row, and past them those that add u (together they may
+    // pass one launch dimension where the rows do not)
+    if (T * 256 >= (int64_t{1} << 32)) return hipErrorInvalidConfiguration;
+    const dim3 grid = grid_of(T + (fin.part != nullptr ? (T + 3) / 4 : 0), 256), block(256);
     if (x_dt == DT::BF16)
         hipLaunchKernelGGL(k_smooth_quant<bf16_t>, grid, block, 0, s,
                            static_cast<const bf16_t*>(x), mod, inv_s, static_cast<int>(K), n_mod,

@@ -42,6 +42,9 @@ def record(tmp_path_factory):
     # codes and u in one launch: up to where (T / 16 + T / 8) x 512 threads fit, past it two
     f"fused 44739200 16 16 16 2 {F32} {F32} {F32} 0", f"fused 44739300 16 16 16 2 {F32} {F32} {F32} 0",
     f"fused 67000000 16 16 128 2 {BF16} {BF16} {BF16} 0",
+    # a row and a quarter of u rows a workgroup, after the split down-projection
+    f"fused 13421772 4160 16 16 2 {BF16} {BF16} {BF16} 0", f"fused 13421773 4160 16 16 2 {BF16} {BF16} {BF16} 0",
+    f"fused 16777215 8192 16 64 3 {F32} {BF16} {F32} 0",
 ])
 def test_launches_stay_within_the_thread_limit(record, call):
     status, launches = record([call])[0]
