@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "masq.h"
+#include "masq_common.h"
 
 namespace {
 
@@ -400,9 +401,9 @@ __global__ __launch_bounds__(64 * WI * WJ, 2) void k_dgemm(int64_t M, int64_t N,
     const int wi = (wave / WJ) * (TI / WI), wj = (wave % WJ) * (TJ / WJ);
     const int lr = lane & 15, lk = lane >> 4;
     const int64_t tiles_j = (N + TJ - 1) / TJ;
-    const int64_t i0 = static_cast<int64_t>(blockIdx.x) / tiles_j * TI;
-    const int64_t j0 = static_cast<int64_t>(blockIdx.x) % tiles_j * TJ;
-    if (lower && j0 > i0 + TI - 1) return;                   // block-uniform
+    const int64_t i0 = masq::linear_block() / tiles_j * TI;
+    const int64_t j0 = masq::linear_block() % tiles_j * TJ;
+    if (i0 >= M || (lower && j0 > i0 + TI - 1)) return;      // block-uniform
     // staging: element e = tid + NT q of each operand block;
     // the fastest-moving index follows the operand's unit-stride direction.
     // Rows past M (columns past N) repeat the last one: their results are
@@ -717,8 +718,8 @@ hipError_t launch_dgemm(int64_t m, int64_t n, int64_t k, const double* a, int64_
                         hipStream_t s) {
     if (m <= 0 || n <= 0) return hipSuccess;
     const int64_t tiles = ((n + kDgCols - 1) / kDgCols) * ((m + kDgRows - 1) / kDgRows);
-    if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;       // (C alone would hold 32 TB)
-    hipLaunchKernelGGL((k_dgemm<kDgRows, kDgCols, kDgStep, 2, 2>), dim3(static_cast<unsigned>(tiles)),
+    if ((n + 127) / 128 > 0xFFFFFF) return hipErrorInvalidConfiguration;   // (never accepted: C of 17 GB a row)
+    hipLaunchKernelGGL((k_dgemm<kDgRows, kDgCols, kDgStep, 2, 2>), grid_of(tiles, 256),
                        dim3(256), 0, s, m, n, k, a, ars, acs, b, brs, bcs, alpha, beta, c, crs, ccs,
                        lower ? 1 : 0);
     return hipGetLastError();

@@ -195,6 +195,17 @@ def test_dgemm_degenerate_sizes(ops):
     assert e.shape == (0, 2)
 
 
+def test_dgemm_of_one_row_past_2_24_tiles(ops):
+    """537 million columns: the tiles go over two grid dimensions; every
+    element exact (small whole numbers)."""
+    n = 2 ** 29 + 37
+    i = torch.arange(n, device="cuda:0")
+    b = torch.stack([(i % 1021).double(), (i % 4093).double()])
+    del i
+    c = ops.dgemm(torch.tensor([[3.0, 5.0]], dtype=torch.float64, device="cuda:0"), b)
+    assert torch.equal(c[0], 3.0 * b[0] + 5.0 * b[1])
+
+
 @pytest.mark.parametrize("act", ["f32", "bf16"])
 def test_gather_smoothed_is_exact(ops, act):
     """Z_m = X_m S_m^-1 (Sec. 4.3) in fp64, bit for bit; indices outside

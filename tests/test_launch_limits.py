@@ -45,6 +45,8 @@ def record(tmp_path_factory):
     # a row and a quarter of u rows a workgroup, after the split down-projection
     f"fused 13421772 4160 16 16 2 {BF16} {BF16} {BF16} 0", f"fused 13421773 4160 16 16 2 {BF16} {BF16} {BF16} 0",
     f"fused 16777215 8192 16 64 3 {F32} {BF16} {F32} 0",
+    # fp64 products whose 64 x 32 tiles pass 2^24 workgroups: one row, and a C of many rows
+    "dgemm 1 536870880 4", "dgemm 1 536870881 4", f"dgemm 1 {128 * (2 ** 24 - 1)} 1", "dgemm 8388480 4096 1",
 ])
 def test_launches_stay_within_the_thread_limit(record, call):
     status, launches = record([call])[0]
