@@ -158,7 +158,7 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void k_gemm_tile(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     int tm, tn;
-    if (!tile_coords_at(static_cast<int>(blockIdx.x), tiles_m, tiles_n * S, tm, tn)) return;
+    if (!tile_coords_at(static_cast<int>(linear_block()), tiles_m, tiles_n * S, tm, tn)) return;
     const int sl = tn % S;                                  // k slice
     tn /= S;
     const int64_t row0 = static_cast<int64_t>(tm) * BM;
@@ -736,13 +736,13 @@ hipError_t launch_tile_t(const TileGemm& g) {
     const int tiles_m = static_cast<int>((g.T + bm - 1) / bm);
     const int tiles_n = static_cast<int>((g.N + bn - 1) / bn);
     const int64_t nt = static_cast<int64_t>(tiles_m) * tiles_n * g.plan.S;
-    const dim3 grid(static_cast<unsigned>(8 * ((nt + 7) / 8)));
 #define MASQ_TILE(BM, BN, WM, WN, NST, WPE)                                                         \
-    hipLaunchKernelGGL((k_gemm_tile<YT, LT, CMC, ACC, W4, BM, BN, WM, WN, NST, WPE>), grid,         \
-                       dim3(64 * WM * WN), 0, g.stream, g.q, g.wq, g.x_scale, g.w_scale, g.T,       \
-                       static_cast<int>(g.K), static_cast<int>(g.N), tiles_m, tiles_n, g.mod, g.u,  \
-                       g.u_hl, g.rank, g.n_mod, static_cast<const LT*>(g.r_up), g.acc,              \
-                       static_cast<YT*>(g.y), g.plan.S, g.part, g.tickets, g.a_pair)
+    hipLaunchKernelGGL((k_gemm_tile<YT, LT, CMC, ACC, W4, BM, BN, WM, WN, NST, WPE>),               \
+                       grid_of(8 * ((nt + 7) / 8), 64 * WM * WN), dim3(64 * WM * WN), 0, g.stream,  \
+                       g.q, g.wq, g.x_scale, g.w_scale, g.T, static_cast<int>(g.K),                 \
+                       static_cast<int>(g.N), tiles_m, tiles_n, g.mod, g.u, g.u_hl, g.rank,         \
+                       g.n_mod, static_cast<const LT*>(g.r_up), g.acc, static_cast<YT*>(g.y),       \
+                       g.plan.S, g.part, g.tickets, g.a_pair)
     switch (g.plan.shape) {
         case 0: MASQ_TILE(32, 64, 1, 2, 3, 2); break;
         case 1: MASQ_TILE(64, 64, 2, 2, 3, 3); break;

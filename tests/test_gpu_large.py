@@ -56,3 +56,29 @@ def test_layer_past_2_31_bytes_of_codes(T, K, r, M):
     assert oinf.relerr(got, ref) <= 1e-2
     text = mr == 0
     assert text.any() and np.array_equal(got[text], ref[text])
+
+
+def test_small_tile_gemm_past_2_24_tiles():
+    """2^30 + 200 rows of 16 channels: 64 x 64 tiles over two grid dimensions.
+    The rows repeat with a period that is no multiple of a tile; the first
+    period is the oracle's, every later one equals it."""
+    assert torch.cuda.is_available()
+    from paper_2603_04800_amd import ops
+    dev = torch.device("cuda")
+    T, K, N, P = 2 ** 30 + 200, 16, 16, 1048573
+    print(f"[large] gemm T={T} K={K} N={N}", flush=True)
+    rng = np.random.default_rng(3)
+    q = rng.integers(-127, 128, (P, K)).astype(np.int8)
+    xs = rng.uniform(1e-3, 1e-1, P).astype(np.float32)
+    wq = rng.integers(-127, 128, (N, K)).astype(np.int8)
+    ws = rng.uniform(1e-4, 1e-2, N).astype(np.float32)
+    n = -(-T // P)
+    qd = torch.from_numpy(q).to(dev).repeat(n, 1)[:T]
+    xd = torch.from_numpy(xs).to(dev).repeat(n)[:T]
+    _, y = ops.w8a8_gemm(qd, xd, torch.from_numpy(wq).to(dev), torch.from_numpy(ws).to(dev), want_acc=False,
+                         out_dtype=torch.bfloat16)
+    ref = oinf.to_output((q.astype(np.int32) @ wq.astype(np.int32).T).astype(np.float32) * xs[:, None] * ws, "bf16")
+    first = y[:P]
+    assert np.array_equal(first.float().cpu().numpy(), ref)
+    for i in range(P, T, P):
+        assert torch.equal(y[i:i + P], first[:min(P, T - i)]), i

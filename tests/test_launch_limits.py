@@ -47,6 +47,9 @@ def record(tmp_path_factory):
     f"fused 16777215 8192 16 64 3 {F32} {BF16} {F32} 0",
     # fp64 products whose 64 x 32 tiles pass 2^24 workgroups: one row, and a C of many rows
     "dgemm 1 536870880 4", "dgemm 1 536870881 4", f"dgemm 1 {128 * (2 ** 24 - 1)} 1", "dgemm 8388480 4096 1",
+    # small GEMM tiles past 2^24 workgroups: many rows of few channels, and few rows of many
+    f"gemm 1073741824 16 16 {BF16} 0", f"gemm 1100000000 64 16 {BF16} 1", f"gemm 2147483647 16 16 {BF16} 0",
+    f"gemm 33 16 1073741824 {BF16} 0", f"fused 33 16 1073741824 0 1 {BF16} {BF16} {BF16} 0",
 ])
 def test_launches_stay_within_the_thread_limit(record, call):
     status, launches = record([call])[0]
