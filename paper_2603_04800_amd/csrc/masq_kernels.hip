@@ -1648,7 +1648,8 @@ __global__ __launch_bounds__(64 * kCompWaves) void k_lowrank_comp(const XT* __re
     __shared__ __attribute__((aligned(16))) float su[kCompRows * (kMaxRank + kCompPad)];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kCompRows;
+    const int64_t row0 = (static_cast<int64_t>(blockIdx.z) * gridDim.x + blockIdx.x) * kCompRows;
+    if (row0 >= T) return;
     if (tid < kCompRows) smod[tid] = row0 + tid < T ? sane_mod(mod[row0 + tid], n_mod) : 0;
     __syncthreads();
     const unsigned present = tile_presence<kCompRows>(smod);
@@ -3308,7 +3309,8 @@ static void launch_comp_t(const void* x, const int32_t* mod, const float* inv_s,
     int64_t groups = (256 + tiles - 1) / tiles;
     if (groups > (nb + kCompWaves - 1) / kCompWaves) groups = (nb + kCompWaves - 1) / kCompWaves;
     const int per = static_cast<int>((nb + groups - 1) / groups);
-    const dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>((nb + per - 1) / per));
+    const dim3 rows = grid_of(tiles, 64 * kCompWaves);
+    const dim3 grid(rows.x, static_cast<unsigned>((nb + per - 1) / per), rows.y);
     hipLaunchKernelGGL((k_lowrank_comp<XT, LT, YT>), grid, dim3(64 * kCompWaves), 0, s,
                        static_cast<const XT*>(x), mod, inv_s, static_cast<const LT*>(ld),
                        static_cast<const LT*>(ru), T, static_cast<int>(K), static_cast<int>(N),
@@ -3319,6 +3321,7 @@ hipError_t launch_lowrank_comp(const void* x, DT x_dt, const int32_t* mod, const
                                const void* l_down, const void* r_up, DT lr_dt, int64_t T,
                                int64_t K, int64_t N, int rank, int n_mod, void* y, DT y_dt,
                                hipStream_t s) {
+    if ((T + 15) / 16 > 0xFFFFFF) return hipErrorInvalidConfiguration;   // (never accepted: 2^28 tokens)
 #define MASQ_COMP(XT, LT, YT) launch_comp_t<XT, LT, YT>(x, mod, inv_s, l_down, r_up, T, K, N, rank, n_mod, y, s)
     const int key = (x_dt == DT::BF16 ? 4 : 0) | (lr_dt == DT::BF16 ? 2 : 0) | (y_dt == DT::BF16 ? 1 : 0);
     switch (key) {

@@ -50,6 +50,8 @@ def record(tmp_path_factory):
     # small GEMM tiles past 2^24 workgroups: many rows of few channels, and few rows of many
     f"gemm 1073741824 16 16 {BF16} 0", f"gemm 1100000000 64 16 {BF16} 1", f"gemm 2147483647 16 16 {BF16} 0",
     f"gemm 33 16 1073741824 {BF16} 0", f"fused 33 16 1073741824 0 1 {BF16} {BF16} {BF16} 0",
+    # the standalone compensation's last 32-row tile
+    f"comp {16 * (2 ** 24 - 1)} 16 16 16 2 {BF16} {BF16} {BF16}",
 ])
 def test_launches_stay_within_the_thread_limit(record, call):
     status, launches = record([call])[0]
