@@ -1626,7 +1626,10 @@ __global__ __launch_bounds__(64 * kFrWaves) void k_stage1_fr(
 // where T / 32 tiles would leave most of it idle.  One lane a channel and
 // scalar fma, 16 rows a workgroup: 2081 us for 1000 x 1040 -> 2000, rank 128
 // in fp32, and 4.6 ms for 8192 x 3584 -> 3584, rank 64 in bf16; in this form
-// 43 and 135 us (16-row tiles, twice the L1 reads: 68 and 224 us).
+// 43 and 135 us (16-row tiles, twice the L1 reads: 68 and 224 us).  A token's
+// sums hold the r products of its own modality and no others, so that a
+// factor that is not finite stays in its own outputs; the selections for
+// that cost 0 to 4 % (8192 x 3584 -> 3584, three modalities 129.6 -> 134.9 us).
 constexpr int kCompRows = 32;
 constexpr int kCompWaves = 8;
 constexpr int kCompPad = 4;             // floats after a u row: rows start on different banks
@@ -1669,23 +1672,29 @@ __global__ __launch_bounds__(64 * kCompWaves) void k_lowrank_comp(const XT* __re
         v16f acc = v16f{0.f};
         for (int m = 1; m < n_mod; ++m) {
             if (!__builtin_amdgcn_readfirstlane(static_cast<int>(present >> m) & 1)) continue;
-            const bool live = md == m;
             const LT* rr = r_up + (static_cast<int64_t>(m - 1) * N + chan) * r + 8 * kg;
             const float* ur = su + tl * pitch + 8 * kg;
+            v16f am = v16f{0.f};                            // every token's products with modality m's L2
             for (int k0 = 0; k0 < r; k0 += 64) {            // r % 16 == 0
                 float rv[4][8];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) load8_any(rr + min(k0 + 16 * q, r - 16), rv[q]);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const bool use = live && k0 + 16 * q < r;     // (no branch: see DownK)
+                    // past r both operands are zero (0 x inf); selected, so
+                    // that the four loads stay in flight together
+                    const bool in = k0 + 16 * q < r;
                     float uv[8];
                     load8_f32(ur + min(k0 + 16 * q, r - 16), uv);
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
-                        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(rv[q][e], use ? uv[e] : 0.f, acc, 0, 0, 0);
+                        am = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? rv[q][e] : 0.f, in ? uv[e] : 0.f,
+                                                                  am, 0, 0, 0);
                 }
             }
+            // a token takes its own modality's sum and nothing of another's
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[e] = md == m ? am[e] : acc[e];
         }
         // lane: token tl, channels 32 b + 8 g + 4 kg + e in acc[4 g + e]
         if (t < T && md > 0) {

@@ -711,3 +711,29 @@ def test_decode_keeps_an_infinite_factor_infinite(ops, T, K, N, r, lr):
 def test_down_projection_slices_of_two_quarters(ops, T, K, N, r, M):
     L = _random_layer(T, K, N, r, M, "bf16", "bf16", zero_rows=(T // 2,), seed=T + K)
     _check_layer(ops, L, name="two quarters")
+
+
+@pytest.mark.parametrize("T,K,N,r,M,act,lr", [(70, 112, 80, 16, 3, "bf16", "bf16"), (70, 112, 80, 80, 3, "bf16", "bf16"),
+                                              (129, 1040, 304, 16, 4, "f32", "f32"), (64, 272, 48, 144, 3, "bf16", "f32")])
+def test_standalone_compensation_keeps_an_infinite_factor_to_its_products(ops, T, K, N, r, M, act, lr):
+    """An infinite entry in the last column of one modality's L2: its channel
+    is infinite for that modality's tokens (exactly r products a token), and
+    every other output, of the same tile's other modalities too, keeps its bits."""
+    L = _random_layer(T, K, N, r, M, act, lr, layout="alternating", seed=T + r)
+    dev = torch.device("cuda")
+    lt = torch.bfloat16 if lr == "bf16" else torch.float32
+    x = torch.from_numpy(L["x"]).to(dev, torch.bfloat16 if act == "bf16" else torch.float32)
+    mod, inv = torch.from_numpy(L["modality"]).to(dev), torch.from_numpy(L["inv_smooth"]).to(dev)
+    ld = torch.from_numpy(L["l_down"]).to(dev, lt)
+
+    def comp():
+        ru = torch.from_numpy(L["r_up"]).to(dev, lt)
+        return _np(ops.lowrank_comp(x, mod, inv, ld, ru, torch.zeros((T, N), device=dev)))
+    y = comp()
+    c = N - 3
+    L["r_up"][1, c, r - 1] = np.inf
+    yi = comp()
+    own = L["modality"] == 2
+    assert np.isinf(yi[own, c]).all()
+    yi[own, c] = y[own, c]
+    assert np.array_equal(yi, y)
