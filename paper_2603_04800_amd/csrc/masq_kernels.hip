@@ -393,7 +393,9 @@ template <typename XT> struct DownK<XT, float> {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             lrow[j] = ld_m + static_cast<int64_t>(c0 + 16 * min(j, ncb - 1) + ar) * K;
-        for (int k0 = kb; k0 < ke; k0 += kStep * kUnroll) {       // kb, ke: multiples of 16
+        // kUnroll steps from k0 on (kb, ke: multiples of 16); in the last
+        // round both operands of the steps past ke are zero (0 x inf)
+        auto round = [&](int k0, auto whole) __attribute__((always_inline)) {
             v4f xv[kUnroll][RG], sv[kUnroll], bv[kUnroll][4];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {                   // all loads first
@@ -406,7 +408,7 @@ template <typename XT> struct DownK<XT, float> {
             }
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
-                const bool in = k0 + kStep * u < ke;
+                const bool in = decltype(whole)::value || k0 + kStep * u < ke;
 #pragma unroll
                 for (int g = 0; g < RG; ++g)
 #pragma unroll
@@ -415,10 +417,14 @@ template <typename XT> struct DownK<XT, float> {
                         const float a = live[g] && in ? xs : 0.f;
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
-                            acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[u][j][e], acc[g][j], 0, 0, 0);
+                            acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, in ? bv[u][j][e] : 0.f,
+                                                                             acc[g][j], 0, 0, 0);
                     }
             }
-        }
+        };
+        int k0 = kb;
+        for (; k0 + kStep * kUnroll <= ke; k0 += kStep * kUnroll) round(k0, std::true_type{});
+        if (k0 < ke) round(k0, std::false_type{});
     }
 };
 

@@ -737,3 +737,26 @@ def test_standalone_compensation_keeps_an_infinite_factor_to_its_products(ops, T
     assert np.isinf(yi[own, c]).all()
     yi[own, c] = y[own, c]
     assert np.array_equal(yi, y)
+
+
+@pytest.mark.parametrize("T,K,N,act", [(300, 1040, 48, "f32"), (257, 16, 32, "bf16"), (33, 4112, 64, "f32"), (7, 1072, 32, "f32")])
+def test_down_projection_keeps_an_infinite_factor_infinite(ops, T, K, N, act):
+    """fp32 factors, an infinite entry in the last column of one row of L1:
+    that rank's u is infinite (no product with the column a second time), so
+    the outputs of the tokens of that modality are, through an L2 of ones;
+    text rows keep their bits."""
+    from paper_2603_04800_amd import workload
+    L = _random_layer(T, K, N, 16, 2, act, "f32", seed=T + K)
+    L["x"][:, K - 1] = np.abs(L["x"][:, K - 1]) + 1
+    x, mod, lin = workload.to_device(L)
+    y = _np(lin(x, mod, out_dtype=torch.float32))
+    L["l_down"][0, 5, K - 1] = np.inf
+    L["r_up"][0, :, 5] = 1.0
+    x, mod, lin = workload.to_device(L)
+    yi = _np(lin(x, mod, out_dtype=torch.float32))
+    own = L["modality"] == 1
+    assert np.isposinf(yi[own]).all()
+    assert np.array_equal(yi[~own], y[~own])
+    dev = torch.device("cuda")
+    yc = _np(ops.lowrank_comp(x, mod, lin.inv_smooth, lin.l_down, lin.r_up, torch.zeros((T, N), device=dev)))
+    assert np.isposinf(yc[own]).all()
