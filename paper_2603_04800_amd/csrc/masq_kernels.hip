@@ -448,26 +448,44 @@ __device__ __forceinline__ void down_group(const XT* x, const float* inv_s, cons
     const int q = ((span + NW * step - 1) / (NW * step)) * step;  // k per wave, step-aligned
     const int wkb = min(ke, kb + wave * q);
     const int wke = min(ke, wkb + q);
+    // Rows of more than one modality past the 16 that share their products
+    // anyway: each modality's sums are taken to its own rows (text rows zero)
+    // before the next one's, so that a factor that is not finite stays there.
+    const bool apart = RG > 1 && __builtin_popcount(present) > 1;
     v4f acc[RG][4];
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int g = 0; g < RG; ++g)
+        for (int g = 0; g < RG; ++g)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[g][j] = v4f{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < 4; ++j) acc[g][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    };
+    auto store = [&](int m) __attribute__((always_inline)) {     // m > 0: its rows; 0: all
+#pragma unroll
+        for (int g = 0; g < RG; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = 16 * g + 4 * (lane >> 4) + i;
+                const int md = m > 0 ? smod[row] : 0;
+                if (md != m && md != 0) continue;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (j >= ncb) break;
+                    red[wave][row][16 * j + (lane & 15)] = md == m ? acc[g][j][i] : 0.f;
+                }
+            }
+    };
+    clear();
     for (int m = 1; m < n_mod; ++m) {
         if (!(present & (1u << m))) continue;
         DownK<XT, LT>::template run<RG>(x, inv_s + static_cast<int64_t>(m) * K,
                                         l_down + static_cast<int64_t>(m - 1) * r * K, row0, T, K, wkb,
                                         wke, c0, ncb, smod, m, acc, lane);
-    }
-#pragma unroll
-    for (int g = 0; g < RG; ++g)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (j >= ncb) break;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                red[wave][16 * g + 4 * (lane >> 4) + i][16 * j + (lane & 15)] = acc[g][j][i];
+        if (apart) {
+            store(m);
+            clear();
         }
+    }
+    if (!apart) store(0);
     __syncthreads();
     for (int idx = tid; idx < kRowsDown * RG * rc; idx += 64 * NW) {
         const int row = idx / rc, col = idx - row * rc;
@@ -1632,10 +1650,11 @@ __global__ __launch_bounds__(64 * kFrWaves) void k_stage1_fr(
 // where T / 32 tiles would leave most of it idle.  One lane a channel and
 // scalar fma, 16 rows a workgroup: 2081 us for 1000 x 1040 -> 2000, rank 128
 // in fp32, and 4.6 ms for 8192 x 3584 -> 3584, rank 64 in bf16; in this form
-// 43 and 135 us (16-row tiles, twice the L1 reads: 68 and 224 us).  A token's
+// 43 and 139 us (16-row tiles, twice the L1 reads: 68 and 224 us).  A token's
 // sums hold the r products of its own modality and no others, so that a
-// factor that is not finite stays in its own outputs; the selections for
-// that cost 0 to 4 % (8192 x 3584 -> 3584, three modalities 129.6 -> 134.9 us).
+// factor that is not finite stays in its own outputs; that costs 0 to 4 %,
+// and 8 % where the modalities alternate (8192 x 3584 -> 3584, three of them,
+// 129 -> 139 us).
 constexpr int kCompRows = 32;
 constexpr int kCompWaves = 8;
 constexpr int kCompPad = 4;             // floats after a u row: rows start on different banks

@@ -760,3 +760,26 @@ def test_down_projection_keeps_an_infinite_factor_infinite(ops, T, K, N, act):
     dev = torch.device("cuda")
     yc = _np(ops.lowrank_comp(x, mod, lin.inv_smooth, lin.l_down, lin.r_up, torch.zeros((T, N), device=dev)))
     assert np.isposinf(yc[own]).all()
+
+
+@pytest.mark.parametrize("T,K,N,r,act,lr", [(70, 112, 80, 16, "bf16", "bf16"), (129, 1040, 48, 80, "f32", "f32"),
+                                            (40, 272, 32, 16, "f32", "bf16")])
+def test_standalone_compensation_keeps_an_infinite_l1_to_its_modality(ops, T, K, N, r, act, lr):
+    """An infinite entry in one modality's L1: the outputs of the tokens of
+    another modality in the same tile keep their bits."""
+    L = _random_layer(T, K, N, r, 3, act, lr, layout="alternating", seed=T + r)
+    dev = torch.device("cuda")
+    lt = torch.bfloat16 if lr == "bf16" else torch.float32
+    x = torch.from_numpy(L["x"]).to(dev, torch.bfloat16 if act == "bf16" else torch.float32)
+    mod, inv = torch.from_numpy(L["modality"]).to(dev), torch.from_numpy(L["inv_smooth"]).to(dev)
+    ru = torch.from_numpy(L["r_up"]).to(dev, lt)
+
+    def comp():
+        ld = torch.from_numpy(L["l_down"]).to(dev, lt)
+        return _np(ops.lowrank_comp(x, mod, inv, ld, ru, torch.zeros((T, N), device=dev)))
+    y = comp()
+    L["l_down"][0, 3, K // 2] = np.inf
+    yi = comp()
+    own = L["modality"] == 1
+    assert not np.isfinite(yi[own]).any()
+    assert np.array_equal(yi[~own], y[~own])
