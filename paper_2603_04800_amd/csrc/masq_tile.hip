@@ -41,8 +41,8 @@ template <> struct CompBlocks<bf16_t> {
                                                const bool (&live)[MI], const int (&chan)[NJ], int lane) {
         const int kg = lane >> 5;
         const v4i zero = {0, 0, 0, 0};
-        // (in: the step lies within r; a step past it multiplies zeros, without
-        // a branch between the MFMAs)
+        // (in: the step lies within r; a step past it multiplies zeros, both
+        // operands, by selection, so that the loads of all steps stay in flight)
         auto mac = [&](const v4i (&hi)[MI], const v4i (&lo)[MI], const v4i (&b)[NJ], bool in)
                        __attribute__((always_inline)) {
 #pragma unroll
@@ -51,7 +51,7 @@ template <> struct CompBlocks<bf16_t> {
                 const v8bf l = __builtin_bit_cast(v8bf, live[i] && in ? lo[i] : zero);
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
-                    const v8bf bj = __builtin_bit_cast(v8bf, b[j]);
+                    const v8bf bj = __builtin_bit_cast(v8bf, in ? b[j] : zero);
                     yb[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bj, h, yb[i][j], 0, 0, 0);
                     yb[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bj, l, yb[i][j], 0, 0, 0);
                 }

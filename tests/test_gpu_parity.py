@@ -783,3 +783,23 @@ def test_standalone_compensation_keeps_an_infinite_l1_to_its_modality(ops, T, K,
     own = L["modality"] == 1
     assert not np.isfinite(yi[own]).any()
     assert np.array_equal(yi[~own], y[~own])
+
+
+@pytest.mark.parametrize("T,K,N,r", [(20, 144, 48, 16), (65, 320, 208, 48), (200, 1040, 336, 32), (129, 512, 80, 80),
+                                     (1100, 144, 3104, 16)])
+def test_small_tile_compensation_has_no_products_past_the_rank(ops, T, K, N, r):
+    """An infinite entry in the last column of L2 (bf16 factors): the layer
+    equals, bit for bit and not-a-number for not-a-number, the one whose rank
+    is filled up to the next whole 64 with zero columns."""
+    from paper_2603_04800_amd import workload
+    L = _random_layer(T, K, N, r, 2, "bf16", "bf16", seed=T + r)
+    L["r_up"][0, N - 3, r - 1] = np.inf
+    x, mod, lin = workload.to_device(L)
+    y = _np(lin(x, mod, out_dtype=torch.float32))
+    full = (r + 63) // 64 * 64
+    wide = dict(L, rank=full, l_down=np.zeros((1, full, K), np.float32), r_up=np.zeros((1, N, full), np.float32))
+    wide["l_down"][:, :r], wide["r_up"][:, :, :r] = L["l_down"], L["r_up"]
+    x, mod, lin = workload.to_device(wide)
+    yw = _np(lin(x, mod, out_dtype=torch.float32))
+    assert np.isinf(y).any()
+    assert np.array_equal(y, yw, equal_nan=True)
