@@ -175,11 +175,9 @@ static Workspace carve_workspace(void* base, int64_t T, int64_t K, int64_t N, in
 
 // The size is that of the 256 x 256 tiles' layout whatever the plan, so that
 // it does not depend on which kernel runs; a small-tile plan takes as many
-// slices as that holds (one slice needs no accumulators).  The shorter slices
-// of k_down_lds (down_lds_quarters) are taken where that size has room for
-// their partials, or where no accumulators are held at all (the workspace is
-// then a few MB: at most 128 x 128 rows of 256 columns of codes, and 8 MB of
-// partials, far below the allocation-free call's scratch).
+// slices as that holds (one slice needs no accumulators), and the shorter
+// slices of k_down_lds (down_lds_quarters) are taken where it has room for
+// their partials.
 Workspace plan_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, int n_mod,
                          bool w4) {
     const int long_q = 4 * down_lds_chunks(T, K), dl_q = down_lds_quarters(T, K);
@@ -192,9 +190,9 @@ Workspace plan_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, 
     }
     if (w.dl_slices > 0 && dl_q < long_q) {
         const Workspace f = carve_workspace(base, T, K, N, rank, n_mod, tile, dl_q);
-        if (f.gk_splits == 1 || f.bytes <= bytes) w = f;
+        if (f.bytes <= bytes) w = f;
     }
-    if (w.bytes < bytes) w.bytes = bytes;
+    w.bytes = bytes;
     return w;
 }
 

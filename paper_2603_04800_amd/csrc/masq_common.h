@@ -259,12 +259,13 @@ inline int down_lds_chunks(int64_t T, int64_t K) {
     return static_cast<int>(n < 1 ? 1 : (n > chunks ? chunks : n));
 }
 // Quarters (64 columns) per k slice.  Batches whose chunks are at most half
-// as many workgroups as compute units take slices of two: a workgroup's time
-// is its quarters' latency, one after the other, and the chip has room for
-// twice the workgroups.  Layers, with the u partials added beside the codes:
-// 64 tokens 3584 -> 18944 28.6 -> 25.8 us, 333 x 3584 -> 3584 (two non-text
-// modalities) 27.7 -> 25.8 us, 1000 x 3584 -> 18944 W4A8 105.2 -> 101.9 us;
-// slices of one quarter up to 64 chunks were no faster (25.8, 25.9 us).
+// as many workgroups as compute units take slices of two where the workspace
+// of the longer slices has room for their partials (plan_workspace): a
+// workgroup's time is its quarters' latency, one after the other, and the
+// chip has room for twice the workgroups.  Stage 1 in slices of four / of two:
+// 300 x 512 10.0 / 8.2 us, 512 x 3584 (two non-text modalities) 13.0 / 10.5,
+// 1000 x 3584 12.3 / 11.4.  Layers without that room, those whose GEMM is not
+// split, keep the longer slices: the size asked for is one that callers keep.
 inline int down_lds_quarters(int64_t T, int64_t K) {
     const int64_t chunks = (K + kDownLdsCols - 1) / kDownLdsCols;
     const int64_t tiles = (T + kDownLdsRows - 1) / kDownLdsRows;

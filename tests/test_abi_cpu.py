@@ -402,3 +402,57 @@ def test_dgemm_binding_refuses_an_output_aliasing_an_input():
     b = torch.zeros((4, 4), dtype=torch.float64)
     with pytest.raises(ValueError, match="share memory"):
         ops.dgemm(b.T, a, c=b)
+
+
+def _workspace_of_long_slices(T, K, N, r, M):
+    """Bytes of a layer past the small batches: codes (whole row pairs where
+    K % 64 == 0), scales, u, its bf16 rows, the down-projection's partials of
+    256-column chunks (or of the wide form's slices, whichever is more) and
+    the accumulators of the 256 x 256 tiles' slices."""
+    def up(v):
+        return (v + 255) // 256 * 256
+
+    def div(a, b):
+        return -(-a // b)
+    total = up((T + 1) // 2 * 2 * K if K % 64 == 0 else T * K) + up(4 * T)
+    tiles = div(T, 256) * div(N, 256)
+    S = 1 if tiles >= 128 or K % 64 else max(1, min(256 // tiles, 4, K // 64 // 8))
+    counters = tiles if S > 1 else 0
+    if r > 0 and M > 1:
+        total += up(4 * T * r) + (up(256 * T) if r <= 64 else 0)
+        steps, row_tiles = div(K, 512), div(T, 16)
+        want = min(div(512, row_tiles) if row_tiles <= 16 else 1, steps)
+        slices = div(K, div(steps, want) * 512)
+        if slices > 1:
+            total += up(4 * T * r * slices)
+            counters += row_tiles
+    total += up(4 * counters)
+    if 0 < r <= 64 and M > 1:
+        parts = 0
+        if K >= 2048 and (T < 4096 or K >= 8192):
+            want = max(1, min(div(512, div(T, 128)), div(K, 256)))
+            parts = div(K, div(div(K, want), 64) * 64)
+        if K % 64 == 0:
+            chunks = div(K, 256)
+            per = max(1, min(div(div(T, 128) * chunks, 512), chunks))
+            parts = max(parts, div(K // 64, 4 * per))
+        total += up(4 * T * r * parts)
+    if S > 1:
+        total += up(4 * tiles * S * 65536)
+    return total
+
+
+def test_workspace_sizes_are_those_of_the_long_slices(lib):
+    """The size asked for depends on the sizes alone, not on the kernels that
+    run in it: callers keep it."""
+    import random
+    rng = random.Random(5)
+    shapes = [(1000, 3584, 18944, 64, 2), (333, 3584, 18944, 64, 3), (300, 512, 512, 64, 2), (17, 2624, 80, 16, 2),
+              (2048, 18944, 3584, 64, 2), (333, 3584, 3584, 64, 3), (1152, 3584, 32768, 16, 4), (600, 1040, 2000, 32, 2)]
+    for _ in range(400):
+        shapes.append((rng.randint(17, 6000), 16 * rng.randint(1, 1200), 16 * rng.randint(1, 1200),
+                       16 * rng.randint(0, 8), rng.randint(1, 4)))
+        T, K, N, r, M = shapes[-1]
+        shapes.append((T, (K + 63) // 64 * 64, N, r, M))
+    for s in shapes:
+        assert lib.masq_linear_fused_workspace_bytes(*s) == _workspace_of_long_slices(*s), s
