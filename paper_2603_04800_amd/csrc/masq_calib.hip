@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "masq.h"
@@ -32,7 +33,7 @@ using bf16_t = unsigned short;
 typedef int32_t v4i __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
-typedef double v4d16 __attribute__((ext_vector_type(4), aligned(16)));   // at any 16-byte address
+typedef double v2d __attribute__((ext_vector_type(2)));
 
 // 16 bytes of a row as magnitudes: 4 fp32 or 8 bf16 columns.
 template <typename XT> struct Abs16;
@@ -66,7 +67,8 @@ __global__ __launch_bounds__(256) void k_zero_f32(float* __restrict__ p, int64_t
 // registers; the waves combine in LDS, then one atomic max per column and
 // modality, consecutive lanes on consecutive columns (a lane on its own C
 // columns made every atomic instruction touch C times the lines: 16384 x 512
-// bf16 took 123 us where this takes 17).  Tokens whose id is outside [0, n_mod) belong to no modality.
+// bf16 took 123 us where this takes 17).  Tokens whose id is outside
+// [0, n_mod) belong to no modality.
 constexpr int kRangeRows = 8;
 template <typename XT>
 __global__ __launch_bounds__(256) void k_channel_range(const XT* __restrict__ x,
@@ -524,32 +526,26 @@ __global__ __launch_bounds__(64 * WI * WJ, 2) void k_dgemm(int64_t M, int64_t N,
 // pass (formed with k_dgemm).
 
 // out [R][C] fp64 = codes [R][C] * scale[r] (exact: 8 x 24 significant bits).
-// With C % 4 == 0 each thread takes 4 codes of a row (VEC: one 4-byte load,
-// two 16-byte stores); grid (chunks of a row's pieces, rows).
-template <bool VEC>
+// P codes of a row a thread and round (2 where C is even: one 16-byte store a
+// lane, a wave's side by side), over the whole matrix in order whatever its
+// shape.  Bound by the writes.  (4 codes a thread in two stores, workgroups on
+// rows of their own: 3584 x 3584 21.9 us, here 18.0; 100000 x 4 13.8, here
+// 3.1; 18944 x 3584 171, here 125 and 138 on a grid of 8192 workgroups.)
+template <int P>
 __global__ __launch_bounds__(256) void k_dequantize_rows(const int8_t* __restrict__ codes,
                                                          const float* __restrict__ scale,
                                                          int64_t R, int64_t C,
                                                          double* __restrict__ out) {
-    if constexpr (VEC) {
-        const int64_t nv = C >> 2;
-        for (int64_t r = blockIdx.y; r < R; r += gridDim.y) {
-            const double sc = static_cast<double>(scale[r]);
-            const uint32_t* src = reinterpret_cast<const uint32_t*>(codes + r * C);
-            double* dst = out + r * C;
-            for (int64_t v = blockIdx.x * 256ll + threadIdx.x; v < nv; v += gridDim.x * 256ll) {
-                const uint32_t w = src[v];
-                v4d d;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    d[j] = static_cast<double>(static_cast<int8_t>(w >> (8 * j))) * sc;
-                *reinterpret_cast<v4d16*>(dst + 4 * v) = d;
-            }
+    const int64_t n = R * C;
+    for (int64_t e = P * (blockIdx.x * 256ll + threadIdx.x); e < n; e += P * 256ll * gridDim.x) {
+        const double sc = static_cast<double>(scale[e / C]);
+        if constexpr (P == 2) {
+            const uint16_t w = *reinterpret_cast<const uint16_t*>(codes + e);
+            *reinterpret_cast<v2d*>(out + e) = v2d{static_cast<double>(static_cast<int8_t>(w)) * sc,
+                                                   static_cast<double>(static_cast<int8_t>(w >> 8)) * sc};
+        } else {
+            out[e] = static_cast<double>(codes[e]) * sc;
         }
-    } else {
-        const int64_t n = R * C;
-        for (int64_t e = blockIdx.x * 256ll + threadIdx.x; e < n; e += gridDim.x * 256ll)
-            out[e] = static_cast<double>(codes[e]) * static_cast<double>(scale[e / C]);
     }
 }
 
@@ -877,18 +873,10 @@ masq_status masq_dequantize_rows(const int8_t* codes, const float* scale, int64_
     if (!aligned16(codes) || !aligned16(scale) || !aligned16(out)) return MASQ_ERR_ALIGN;
     (void)hipGetLastError();
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (cols % 4 == 0) {
-        const int64_t bx = (cols / 4 + 255) / 256;
-        const dim3 grid(static_cast<unsigned>(bx < 64 ? bx : 64),
-                        static_cast<unsigned>(rows < 8192 ? rows : 8192));
-        hipLaunchKernelGGL(k_dequantize_rows<true>, grid, dim3(256), 0, st, codes, scale, rows, cols,
-                           out);
-    } else {
-        const int64_t n = rows * cols;
-        const int64_t blocks = (n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192;
-        hipLaunchKernelGGL(k_dequantize_rows<false>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0,
-                           st, codes, scale, rows, cols, out);
-    }
+    const int per = cols % 2 == 0 ? 2 : 1;
+    const int64_t blocks = std::min<int64_t>((rows * cols + 256 * per - 1) / (256 * per), 1 << 20);
+    hipLaunchKernelGGL(per == 2 ? k_dequantize_rows<2> : k_dequantize_rows<1>,
+                       dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, codes, scale, rows, cols, out);
     return hipGetLastError() == hipSuccess ? MASQ_OK : MASQ_ERR_HIP;
 }
 

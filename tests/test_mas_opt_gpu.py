@@ -29,6 +29,21 @@ def test_dequantize_rows_is_exact(ops, R, C):
     assert np.array_equal(got.cpu().numpy().view(np.uint64), want.view(np.uint64))
 
 
+@pytest.mark.parametrize("R,C", [(1, 1), (3, 2), (7, 33), (513, 1), (100001, 4), (5, 1000003), (3, 2 ** 28 + 2),
+                                 (3, 2 ** 27 + 1)])
+def test_dequantize_rows_of_any_shape(ops, R, C):
+    """Pairs and single codes, rows shorter than a pair and longer than a
+    workgroup's share, and matrices past the largest grid (2^20 workgroups):
+    bit for bit the fp64 product."""
+    g = torch.Generator(device=DEV).manual_seed(R + C)
+    codes = torch.randint(-128, 128, (R, C), generator=g, device=DEV, dtype=torch.int8)
+    scale = torch.rand((R,), generator=g, device=DEV) * 3 + 1e-4
+    got = ops.dequantize_rows(codes, scale)
+    for r in range(0, R, 4096):
+        want = codes[r:r + 4096].double() * scale[r:r + 4096].double()[:, None]
+        assert torch.equal(got[r:r + 4096].view(torch.int64), want.view(torch.int64))
+
+
 @pytest.mark.parametrize("n", [1, 4095, 4097, 70000])
 def test_mae_sign(ops, n):
     rng = np.random.default_rng(n)
