@@ -141,13 +141,19 @@ __global__ __launch_bounds__(256) void k_smoothing_factors(const float* __restri
     const v4f* row = reinterpret_cast<const v4f*>(w + static_cast<int64_t>(i) * N);
     const int nv = N >> 2;                            // N % 16 == 0
     float a = 0.f;
-    for (int j = lane; j < nv; j += 4 * 64) {
-        v4f v[4];
+    if (nv <= 64) {                 // narrow rows: one load (100000 x 16 26.9 us in the loop, 21.3 here)
+        const v4f v = row[min(lane, nv - 1)];
+        a = fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)));
+    } else {
+        for (int j = lane; j < nv; j += 4 * 64) {
+            v4f v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = row[j + 64 * q < nv ? j + 64 * q : j];
+            for (int q = 0; q < 4; ++q) v[q] = row[j + 64 * q < nv ? j + 64 * q : j];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            a = fmaxf(fmaxf(a, fmaxf(fabsf(v[q].x), fabsf(v[q].y))), fmaxf(fabsf(v[q].z), fabsf(v[q].w)));
+            for (int q = 0; q < 4; ++q)
+                a = fmaxf(fmaxf(a, fmaxf(fabsf(v[q].x), fabsf(v[q].y))),
+                          fmaxf(fabsf(v[q].z), fabsf(v[q].w)));
+        }
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) a = fmaxf(a, __shfl_xor(a, o));
