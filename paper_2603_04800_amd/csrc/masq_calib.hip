@@ -181,20 +181,20 @@ __global__ __launch_bounds__(256) void k_smoothing_factors(const float* __restri
 //   k_quantize_codes (head) the first kQwHead columns, once every other
 //                     column is written: a workgroup reads the maxima of its
 //                     64 channels, then overwrites them.
+// Weights of at most kQwHead rows take one launch, whose workgroups form their
+// channels' maxima themselves.
 constexpr int kQwChunks = 16;
 constexpr int kQwHead = 128;                          // 8 kQwChunks bytes, whole 64-column blocks
 static_assert(8 * kQwChunks <= kQwHead && kQwHead % 64 == 0, "maxima lie in the head columns");
 constexpr int kQwBlocks = 4;                          // 64-column blocks per workgroup, at least
 
-__global__ __launch_bounds__(256) void k_weight_absmax(const float* __restrict__ w,
-                                                       const float* __restrict__ s_text, int K,
-                                                       int N, int rows_per_chunk,
-                                                       int8_t* __restrict__ wq) {
-    __shared__ double red[16][64];
+// The fp64 maximum of channel o0 + tid (tid < 64) over rows i0 .. i1 - 1, by
+// the 256 threads of a workgroup.
+__device__ __forceinline__ double weight_absmax(const float* __restrict__ w,
+                                                const float* __restrict__ s_text, int N, int o0, int i0,
+                                                int i1, double (*red)[64]) {
     const int tid = threadIdx.x, cl = tid & 15, rl = tid >> 4;
-    const int o = blockIdx.x * 64 + 4 * cl;           // N % 16 == 0: whole groups of 4
-    const int oc = min(o, N - 4);
-    const int i0 = blockIdx.y * rows_per_chunk, i1 = min(K, i0 + rows_per_chunk);
+    const int oc = min(o0 + 4 * cl, N - 4);           // N % 16 == 0: whole groups of 4
     double a[4] = {0.0, 0.0, 0.0, 0.0};
     constexpr int U = 4;
     for (int i = i0 + rl; i < i1; i += 16 * U) {
@@ -215,12 +215,22 @@ __global__ __launch_bounds__(256) void k_weight_absmax(const float* __restrict__
 #pragma unroll
     for (int e = 0; e < 4; ++e) red[rl][4 * cl + e] = a[e];
     __syncthreads();
-    if (tid < 64 && blockIdx.x * 64 + tid < N) {
-        double m = red[0][tid];
+    double m = red[0][tid & 63];
 #pragma unroll
-        for (int q = 1; q < 16; ++q) m = fmax(m, red[q][tid]);
-        *reinterpret_cast<double*>(wq + static_cast<int64_t>(blockIdx.x * 64 + tid) * K + 8 * blockIdx.y) = m;
-    }
+    for (int q = 1; q < 16; ++q) m = fmax(m, red[q][tid & 63]);
+    return m;
+}
+
+__global__ __launch_bounds__(256) void k_weight_absmax(const float* __restrict__ w,
+                                                       const float* __restrict__ s_text, int K,
+                                                       int N, int rows_per_chunk,
+                                                       int8_t* __restrict__ wq) {
+    __shared__ double red[16][64];
+    const int o0 = blockIdx.x * 64, i0 = blockIdx.y * rows_per_chunk;
+    const double m = weight_absmax(w, s_text, N, o0, i0, min(K, i0 + rows_per_chunk), red);
+    const int o = o0 + static_cast<int>(threadIdx.x);
+    if (threadIdx.x < 64 && o < N)
+        *reinterpret_cast<double*>(wq + static_cast<int64_t>(o) * K + 8 * blockIdx.y) = m;
 }
 
 // One code: rint(v / d) clamped to [-qmax, qmax], d > 0, rd = 1 / d.  v rd
@@ -236,7 +246,9 @@ __device__ __forceinline__ int weight_code(double v, double d, double rd, double
 
 // Codes of 64 channels (blockIdx.x) and the `per` 64-column blocks from
 // b0 + per blockIdx.y on, below b1, transposed through LDS so that
-// both the reads (along o) and the writes (along i) are contiguous.
+// both the reads (along o) and the writes (along i) are contiguous.  OWN: the
+// workgroup forms its channels' maxima itself (K <= kQwHead: one launch).
+template <bool OWN>
 __global__ __launch_bounds__(256) void k_quantize_codes(const float* __restrict__ w,
                                                         const float* __restrict__ s_text, int K,
                                                         int N, int qmax, int chunks, int b0, int b1,
@@ -248,11 +260,17 @@ __global__ __launch_bounds__(256) void k_quantize_codes(const float* __restrict_
     __shared__ __attribute__((aligned(16))) int8_t tile[64 * kPitch];
     const int tid = threadIdx.x, cl = tid & 15, rl = tid >> 4;
     const int o0 = blockIdx.x * 64;
-    if (tid < 64) {
+    double m = 0.0;
+    if constexpr (OWN) {
+        __shared__ double red[16][64];
+        m = weight_absmax(w, s_text, N, o0, 0, K, red);
+    } else if (tid < 64) {
         const int o = min(o0 + tid, N - 1);
         const double* mp = reinterpret_cast<const double*>(wq + static_cast<int64_t>(o) * K);
-        double m = mp[0];
+        m = mp[0];
         for (int c = 1; c < chunks; ++c) m = fmax(m, mp[c]);
+    }
+    if (tid < 64) {
         const double d = m / qmax;
         sdelta[tid] = d;
         if (w_scale != nullptr && o0 + tid < N) w_scale[o0 + tid] = static_cast<float>(d);
@@ -792,19 +810,24 @@ masq_status masq_quantize_weight(const float* w, const float* smooth_text, int64
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int K = static_cast<int>(c_in), N = static_cast<int>(c_out), qmax = (1 << (bits - 1)) - 1;
     const unsigned groups = static_cast<unsigned>((N + 63) / 64);
-    int chunks = K / 64 < kQwChunks ? (K / 64 < 1 ? 1 : K / 64) : kQwChunks;
+    const int blocks = (K + 63) / 64;
+    if (K <= kQwHead) {     // few rows: one launch (16 x 512 5.7 -> 3.5 us, 128 x 3584 6.7 -> 5.1 us)
+        hipLaunchKernelGGL(k_quantize_codes<true>, dim3(groups, 1), dim3(256), 0, s, w, smooth_text, K, N,
+                           qmax, 0, 0, blocks, blocks, wq, w_scale);
+        return hipGetLastError() == hipSuccess ? MASQ_OK : MASQ_ERR_HIP;
+    }
+    int chunks = std::min(K / 64, kQwChunks);
     const int rows = (K + chunks - 1) / chunks;
     chunks = (K + rows - 1) / rows;
-    const int blocks = (K + 63) / 64, head = blocks < kQwHead / 64 ? blocks : kQwHead / 64;
     hipLaunchKernelGGL(k_weight_absmax, dim3(groups, static_cast<unsigned>(chunks)), dim3(256), 0, s,
                        w, smooth_text, K, N, rows, wq);
+    constexpr int head = kQwHead / 64;
     const int rest = blocks - head;
     const int per = rest > kQwBlocks * 65535 ? (rest + 65534) / 65535 : kQwBlocks;
-    if (rest > 0)
-        hipLaunchKernelGGL(k_quantize_codes, dim3(groups, static_cast<unsigned>((rest + per - 1) / per)),
-                           dim3(256), 0, s, w, smooth_text, K, N, qmax, chunks, head, blocks, per, wq,
-                           static_cast<float*>(nullptr));
-    hipLaunchKernelGGL(k_quantize_codes, dim3(groups, 1), dim3(256), 0, s, w, smooth_text, K, N, qmax,
+    hipLaunchKernelGGL(k_quantize_codes<false>, dim3(groups, static_cast<unsigned>((rest + per - 1) / per)),
+                       dim3(256), 0, s, w, smooth_text, K, N, qmax, chunks, head, blocks, per, wq,
+                       static_cast<float*>(nullptr));
+    hipLaunchKernelGGL(k_quantize_codes<false>, dim3(groups, 1), dim3(256), 0, s, w, smooth_text, K, N, qmax,
                        chunks, 0, head, head, wq, w_scale);
     return hipGetLastError() == hipSuccess ? MASQ_OK : MASQ_ERR_HIP;
 }
