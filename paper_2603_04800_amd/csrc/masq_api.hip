@@ -28,6 +28,13 @@ namespace masq {
 //              packed weight 0.62 (fewer bytes)
 //   256 x 256  1 for each round of 256, or for fewer than kSplitMaxTiles
 //              tiles 1 / S with S slices, and 17 us for their hand-over
+// Past two rounds of 128 x 128 tiles the rounds overlap and a tile's fixed
+// part counts, so those are compared in ns: 19 + 0.0161 K a tile with the
+// packed weight (0.0195 with int8 codes), 9000 + 10.75 K a round of 256 x 256
+// (1036-1924 tiles, 512-18944 columns; packed, 3584 columns: 1036 tiles 82.8
+// us where 256 x 256 take 93.3, 1184 90-93 / 94, 1316 103.6 / 96, 1536 108 /
+// 98; 1184 of 512 columns 30.7 / 30.3; int8, 1924 tiles 147.8 / 138.6, 1120
+// of 3008 columns 85.5 / 78.8).
 // At 3584 columns this gives 64 x 64 tiles for 333 x 3584 (15.0 us; 128 x 128
 // 23.3, 256 x 256 30.5), 128 x 128 for 2048 x 3584 (38.8; 51, 45.0) and 256 x
 // 256 for 512 x 18944 (49.8; 72, 64).  Rows that are not a multiple of 64
@@ -50,9 +57,14 @@ TilePlan plan_tile(int64_t T, int64_t K, int64_t N, bool split, bool w4) {
             p.shape = 2;
         }
         if (K % 64 == 0) {
+            const double k = static_cast<double>(K);
             const int s256 = split ? plan_gemm_splits(T, K, N) : 1;
-            const double t256 = s256 > 1 ? 1.0 / s256 + 17.0 / (50.0 * static_cast<double>(K) / 3584.0)
-                                         : static_cast<double>((n256 + 255) / 256);
+            const double rounds = static_cast<double>((n256 + 255) / 256);
+            double t256 = s256 > 1 ? 1.0 / s256 + 17.0 / (50.0 * k / 3584.0) : rounds;
+            if (p.shape == 2 && n128 > 1024) {         // both in ns
+                best = static_cast<double>(n128) * (19.0 + (w4 ? 0.0161 : 0.0195) * k);
+                t256 = rounds * (9000.0 + 10.75 * k);
+            }
             if (t256 < best) return TilePlan{-1, 1};
         }
     }

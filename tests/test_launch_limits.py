@@ -56,3 +56,17 @@ def record(tmp_path_factory):
 def test_launches_stay_within_the_thread_limit(record, call):
     status, launches = record([call])[0]
     assert status == 0 and launches, (call, status, launches)
+
+
+@pytest.mark.parametrize("T,K,N,w4,large", [
+    # several rounds of 128 x 128 tiles against those of 256 x 256 (a persistent grid of 256 workgroups of 512
+    # threads): packed weights of long rows and a short last round keep the smaller tiles
+    (1000, 3584, 18944, 1, False), (800, 512, 18944, 1, False), (2300, 8192, 8192, 1, False),
+    (2300, 512, 8192, 1, True), (6000, 3584, 3584, 1, True), (1280, 3584, 18944, 1, True),
+    (3000, 18944, 8192, 1, True), (1600, 512, 18944, 0, True), (1600, 3584, 18944, 0, True),
+    (2048, 3584, 3584, 0, False), (700, 3584, 8192, 0, False), (8192, 3584, 18944, 0, True),
+])
+def test_tile_shapes_of_several_rounds(record, T, K, N, w4, large):
+    for status, launches in record([f"fused {T} {K} {N} 32 2 {BF16} {BF16} {BF16} {w4}", f"gemm {T} {K} {N} {BF16} {w4}"]):
+        assert status == 0
+        assert launches[-1] == (256, 1, 1, 512) if large else launches[-1][3] == 256, launches
