@@ -172,6 +172,14 @@ __global__ __launch_bounds__(256) void k_smooth_quant(const XT* __restrict__ x,
     sq_row<XT, 256, kSqChunks>(x, mod, inv_s, K, n_mod, q, x_scale, b, pair);
 }
 
+// Chunks of 512 columns a wave holds of a row of K columns, of the instances
+// there are.  A chunk past the row's end costs its loads and arithmetic all
+// the same: with 8 for every row, 16384 x 256 fp32 took 17.2 us, 65536 x 512
+// 63 us, where fitting chunks take 8 and 33.
+inline __host__ __device__ int quant_row_chunks(int64_t K) {
+    return K <= 512 ? 1 : (K <= 1024 ? 2 : (K <= 2048 ? 4 : (K <= 3072 ? 6 : 8)));
+}
+
 // One row t quantised by one wave (lane = this lane), its smoothed values
 // kept in registers between the absmax and the codes for rows of up to
 // 64 * 8 * NC elements; longer rows stream their remainder twice.  The row's
@@ -607,7 +615,7 @@ __global__ __launch_bounds__(64 * kDownWaves) void k_lowrank_down(const XT* __re
 // 512 fp32, rank 16, 9.7 / 7.2 us; 1000 x 3584 bf16, rank 128, 54.4 / 46.5;
 // 8192 x 2048 bf16, rank 128, 82.5 / 68.1.  Workgroups below
 // down_tiles take a 16-row tile of u, the others 8 rows of codes, a wave each.
-template <typename XT, typename LT>
+template <typename XT, typename LT, int NC>
 __global__ __launch_bounds__(64 * kDownWaves) void k_quant_down(
     const XT* __restrict__ x, const int32_t* __restrict__ mod, const float* __restrict__ inv_s,
     const LT* __restrict__ l_down, int64_t T, int K, int r, int n_mod, float* __restrict__ u,
@@ -622,7 +630,7 @@ __global__ __launch_bounds__(64 * kDownWaves) void k_quant_down(
         for (int i = threadIdx.x; i < n_zero; i += 64 * kDownWaves) zero_ints[i] = 0;
     const int64_t t = b * kDownWaves + (threadIdx.x >> 6);
     if (t < T)
-        quant_row_wave<XT, 8>(x, mod, inv_s, K, n_mod, q, x_scale, t, pair, threadIdx.x & 63, [](int) {});
+        quant_row_wave<XT, NC>(x, mod, inv_s, K, n_mod, q, x_scale, t, pair, threadIdx.x & 63, [](int) {});
 }
 
 // Down-projection of large batches (bf16 factors, rank <= 64): u = (x S_m^-1)
@@ -3012,14 +3020,20 @@ hipError_t launch_smooth_quant(const void* x, DT x_dt, const int32_t* mod, const
         // flight (8192 x 3584: 20.9 us, apart 22.1 us)
         const bool apart = fin.part != nullptr && T < kFusedFullT;
         const dim3 grid(static_cast<unsigned>((T + 3) / 4 * (apart ? 2 : 1))), block(256);
-        if (x_dt == DT::BF16)
-            hipLaunchKernelGGL((k_smooth_quant_rows<bf16_t, 8>), grid, block, 0, s,
-                               static_cast<const bf16_t*>(x), mod, inv_s, T, static_cast<int>(K),
-                               n_mod, q, x_scale, zero_ints, n_zero, fin, pair);
-        else
-            hipLaunchKernelGGL((k_smooth_quant_rows<float, 8>), grid, block, 0, s,
-                               static_cast<const float*>(x), mod, inv_s, T, static_cast<int>(K),
-                               n_mod, q, x_scale, zero_ints, n_zero, fin, pair);
+#define MASQ_SQR(XT, NC)                                                                            \
+    case NC:                                                                                        \
+        hipLaunchKernelGGL((k_smooth_quant_rows<XT, NC>), grid, block, 0, s, static_cast<const XT*>(x), \
+                           mod, inv_s, T, static_cast<int>(K), n_mod, q, x_scale, zero_ints, n_zero, \
+                           fin, pair);                                                              \
+        break;
+#define MASQ_SQR_ALL(XT) MASQ_SQR(XT, 1) MASQ_SQR(XT, 2) MASQ_SQR(XT, 4) MASQ_SQR(XT, 6) MASQ_SQR(XT, 8)
+        if (x_dt == DT::BF16) {
+            switch (quant_row_chunks(K)) { MASQ_SQR_ALL(bf16_t) }
+        } else {
+            switch (quant_row_chunks(K)) { MASQ_SQR_ALL(float) }
+        }
+#undef MASQ_SQR_ALL
+#undef MASQ_SQR
         return hipGetLastError();
     }
     // a workgroup per row, and past them those that add u (together they may
@@ -3066,10 +3080,18 @@ static void launch_quant_down_t(const void* x, const int32_t* mod, const float* 
                                 int64_t T, int64_t K, int rank, int n_mod, const Workspace& w,
                                 hipStream_t s) {
     const int64_t tiles = (T + kDownRows - 1) / kDownRows, rows = (T + kDownWaves - 1) / kDownWaves;
-    hipLaunchKernelGGL((k_quant_down<XT, LT>), dim3(static_cast<unsigned>(tiles + rows)),
-                       dim3(64 * kDownWaves), 0, s, static_cast<const XT*>(x), mod, inv_s,
-                       static_cast<const LT*>(ld), T, static_cast<int>(K), rank, n_mod, w.u, w.q,
-                       w.x_scale, w.zero_base, w.n_zero, static_cast<int>(tiles), w.pair);
+#define MASQ_QD(NC)                                                                                 \
+    hipLaunchKernelGGL((k_quant_down<XT, LT, NC>), dim3(static_cast<unsigned>(tiles + rows)),       \
+                       dim3(64 * kDownWaves), 0, s, static_cast<const XT*>(x), mod, inv_s,          \
+                       static_cast<const LT*>(ld), T, static_cast<int>(K), rank, n_mod, w.u, w.q,   \
+                       w.x_scale, w.zero_base, w.n_zero, static_cast<int>(tiles), w.pair)
+    switch (quant_row_chunks(K)) {
+        case 1: MASQ_QD(1); break;
+        case 2: MASQ_QD(2); break;
+        case 4: MASQ_QD(4); break;
+        default: MASQ_QD(8);
+    }
+#undef MASQ_QD
 }
 
 hipError_t launch_quant_down(const void* x, DT x_dt, const int32_t* mod, const float* inv_s,

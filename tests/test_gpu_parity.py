@@ -803,3 +803,11 @@ def test_small_tile_compensation_has_no_products_past_the_rank(ops, T, K, N, r):
     yw = _np(lin(x, mod, out_dtype=torch.float32))
     assert np.isinf(y).any()
     assert np.array_equal(y, yw, equal_nan=True)
+
+
+@pytest.mark.parametrize("K", [16, 64, 496, 512, 528, 1024, 1040, 2048, 2064, 3072, 3088, 4096])
+def test_row_quantiser_instances(ops, K):
+    """Rows around the 512-column chunks of every instance of the wave-per-row
+    quantiser, alone (fp32) and beside the fp32 down-projection."""
+    L = _random_layer(259, K, 32, 16, 3, "f32", "f32", zero_rows=(5, 258), seed=K)
+    _check_layer(ops, L, name=f"row quantiser K={K}")
