@@ -401,13 +401,14 @@ template <typename XT> struct DownK<XT, float> {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             lrow[j] = ld_m + static_cast<int64_t>(c0 + 16 * min(j, ncb - 1) + ar) * K;
-        // kUnroll steps from k0 on (kb, ke: multiples of 16); in the last
-        // round both operands of the steps past ke are zero (0 x inf)
-        auto round = [&](int k0, auto whole) __attribute__((always_inline)) {
-            v4f xv[kUnroll][RG], sv[kUnroll], bv[kUnroll][4];
+        // U steps from k0 on, all within the range (kb, ke: multiples of 16):
+        // none multiplies a column past it (0 x inf)
+        auto round = [&](int k0, auto steps) __attribute__((always_inline)) {
+            constexpr int U = decltype(steps)::value;
+            v4f xv[U][RG], sv[U], bv[U][4];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {                   // all loads first
-                const int k = min(k0 + kStep * u, ke - kStep) + 4 * kg;
+            for (int u = 0; u < U; ++u) {                         // all loads first
+                const int k = k0 + kStep * u + 4 * kg;
                 sv[u] = load4(inv_s_m + k);
 #pragma unroll
                 for (int g = 0; g < RG; ++g) xv[u][g] = load4(xrow[g] + k);
@@ -415,24 +416,26 @@ template <typename XT> struct DownK<XT, float> {
                 for (int j = 0; j < 4; ++j) bv[u][j] = load4(lrow[j] + k);
             }
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                const bool in = decltype(whole)::value || k0 + kStep * u < ke;
+            for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int g = 0; g < RG; ++g)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float xs = xv[u][g][e] * sv[u][e];
-                        const float a = live[g] && in ? xs : 0.f;
+                        const float a = live[g] ? xs : 0.f;
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
-                            acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, in ? bv[u][j][e] : 0.f,
-                                                                             acc[g][j], 0, 0, 0);
+                            acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[u][j][e], acc[g][j], 0, 0, 0);
                     }
-            }
         };
         int k0 = kb;
-        for (; k0 + kStep * kUnroll <= ke; k0 += kStep * kUnroll) round(k0, std::true_type{});
-        if (k0 < ke) round(k0, std::false_type{});
+        for (; k0 + kStep * kUnroll <= ke; k0 += kStep * kUnroll)
+            round(k0, std::integral_constant<int, kUnroll>{});
+        if (k0 + kStep * 2 <= ke) {                               // uniform
+            round(k0, std::integral_constant<int, 2>{});
+            k0 += kStep * 2;
+        }
+        if (k0 < ke) round(k0, std::integral_constant<int, 1>{});
     }
 };
 
