@@ -85,9 +85,10 @@ def test_weight_codes_half_way_between_two_integers(ops, bits):
     """Steps of exactly 1 and 3 with values exactly half-way (rounded to
     even) and one part in 2^23 to either side of it."""
     top = 127 if bits == 8 else 7
-    K, N = 272, 32
+    K, N = 784 if bits == 8 else 272, 32
     half = np.arange(-top, top) + 0.5
-    v = np.concatenate([half, half * (1 + 2.0 ** -23), half * (1 - 2.0 ** -23)])[:K - 1]
+    v = np.concatenate([half, half * (1 + 2.0 ** -23), half * (1 - 2.0 ** -23)])
+    assert v.size <= K - 1
     w = np.zeros((K, N), np.float32)
     w[:v.size] = np.resize(v, v.size)[:, None]
     w[-1] = top
@@ -98,6 +99,35 @@ def test_weight_codes_half_way_between_two_integers(ops, bits):
     wq_ref, ws_ref, _ = cal.quantize_weight(w, one, bits)
     assert np.array_equal(wq.cpu().numpy(), wq_ref)
     assert np.array_equal(ws.cpu().numpy(), ws_ref)
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+def test_weight_codes_beside_half_way_points(ops, bits):
+    """A step of 1 and products s w (exact in fp64) within 1e-9 of every
+    half-way point, below it and above, found among random factors: closer
+    than the reciprocal's shortcut decides."""
+    top = 127 if bits == 8 else 7
+    rng = np.random.default_rng(bits)
+    sv, wv = [], []
+    for half in np.arange(-top, top) + 0.5:
+        s = rng.uniform(0.5, 2.0, 200000).astype(np.float32)
+        w = (half / s.astype(np.float64)).astype(np.float32)
+        d = s.astype(np.float64) * w.astype(np.float64) - half
+        for side in (d < 0, d > 0):
+            i = np.flatnonzero(side)[np.argmin(np.abs(d[side]))]
+            assert abs(d[i]) < 1e-9
+            sv.append(s[i])
+            wv.append(w[i])
+    K = (len(sv) + 1 + 15) // 16 * 16
+    s = np.ones(K, np.float32)
+    w = np.zeros((K, 16), np.float32)
+    s[:len(sv)], w[:len(wv)] = sv, np.array(wv, np.float32)[:, None]
+    w[-1] = top
+    dev = torch.device("cuda:0")
+    wq, ws = ops.quantize_weight(torch.from_numpy(w).to(dev), torch.from_numpy(s).to(dev), bits=bits)
+    wq_ref, ws_ref, _ = cal.quantize_weight(w, s, bits)
+    assert np.array_equal(ws.cpu().numpy(), ws_ref) and np.all(ws_ref == 1)
+    assert np.array_equal(wq.cpu().numpy(), wq_ref)
 
 
 def test_prefill_workload_calibration(ops):
@@ -160,12 +190,14 @@ def test_dgemm_within_the_fp64_bound(ops, m, n, k, ta, tb):
 
 
 @pytest.mark.parametrize("m,n,k", [(64, 64, 32), (65, 63, 33), (63, 65, 31), (192, 320, 4), (16, 2064, 100),
-                                   (1100, 1040, 48), (2049, 2050, 18)])
+                                   (1100, 1040, 48), (2049, 2050, 18), (1, 31, 15), (129, 33, 16), (128, 97, 17),
+                                   (63, 32, 47), (64, 31, 64), (65, 1, 80)])
 @pytest.mark.parametrize("ta,tb", [(False, False), (True, True)])
 def test_dgemm_is_the_increasing_k_chain(ops, m, n, k, ta, tb):
-    """Both tile sizes around their edges and k steps: with operands of few
-    bits every order is exact, and a term that only survives when the sum
-    runs in increasing k (2^60, then -2^60 beside small terms) pins the order."""
+    """The 64 x 32 tiles around their edges and the 16-wide k steps: with
+    operands of few bits every order is exact, and a term that only survives
+    when the sum runs in increasing k (2^60, then -2^60 beside small terms)
+    pins the order."""
     rng = np.random.default_rng(m + n + k)
     a = rng.integers(-8, 9, (m, k)).astype(np.float64)
     b = rng.integers(-8, 9, (k, n)).astype(np.float64)
