@@ -21,18 +21,17 @@ __device__ __forceinline__ int64_t linear_block() {
     return static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
 }
 
-// Tile shape of the int8 GEMM: 256 x 256 output tile per workgroup of four
-// wave64s (2 x 2, each wave 128 x 128), 128-byte K stages, double-buffered.
+// Tile shape of the int8 GEMM: 256 x 256 output tile per workgroup of eight
+// wave64s (2 x 4, each wave 128 x 64), 64-byte K stages in a ring of four LDS
+// buffers.
 constexpr int kTileM = 256;
 constexpr int kTileN = 256;
-constexpr int kTileK = 128;
 constexpr int kRowsDown = 16;     // rows per down-projection tile
 constexpr int kDownRows = kRowsDown;
 constexpr int kDownStep = 512;    // k granularity of a down-projection slice (128 per wave)
 constexpr int kMaxRank = 256;
 constexpr int kSmallMaxT = 16;    // batches this small use the Wq-streaming GEMM
 constexpr int kSmallSlices = 64;  // down-projection k slices (at most; >= 512 columns each) summed by that GEMM
-constexpr int kUBatch = 16;        // slice partials of u a thread keeps in flight when adding them
 
 // The small-batch path: the Wq-streaming GEMM, which also adds the
 // down-projection's k-slice partials itself.
@@ -164,7 +163,7 @@ struct Workspace {
     int32_t* dec_part; // small-batch path: [ns][kSmallMaxT][N] int32 partial sums per k slice,
                        // then [kSmallMaxT][N] fp32 compensation terms
     int* dec_tickets;  // small-batch path: [ngroups] arrival counters (zeroed by stage 1)
-    int dec_ns, dec_sp, dec_groups;   // plan_decode of the small-batch path
+    int dec_groups;    // plan_decode's channel groups (small-batch path)
     TilePlan tile;     // plan_tile: the small-tile GEMM's shape and slices (shape < 0: 256 x 256)
     int gk_splits;     // plan_gemm_splits (256 x 256 tiles)
     int32_t* gk_part;  // [tiles][slices][bm * bn] int32 slice accumulators (slices > 1)
@@ -307,11 +306,12 @@ hipError_t launch_stage1_small(const void* x, DT x_dt, const int32_t* mod, const
 // u: the down-projection; on the small-batch path (small_path) with
 // n_kslices > 1 the GEMM adds the slice partials u_part itself.  u_hl
 // (optional): u as bf16 hi/lo rows, written by the fused stage 1.  dec_part /
-// dec_tickets (optional, small-batch path): workspace of the k-sliced decode
-// GEMM; without them the single-pass small-batch GEMM runs.  w4: wq holds
-// packed 4-bit codes ([N][K / 2] bytes, K % 64 == 0).  a_pair: q is
-// row-paired (code_row / code_col), which only the LDS-DMA GEMM reads
-// (K % 64 == 0, batches past the small path).
+// dec_tickets (optional, small-batch path): workspace of the decode GEMM;
+// without them (the standalone product, no compensation) the single-pass
+// small-batch GEMM runs.  w4: wq holds packed 4-bit codes ([N][K / 2] bytes,
+// K % 64 == 0).  a_pair: q is row-paired (code_row / code_col), which the
+// 256 x 256 and the small-tile kernel read (K % 64 == 0, batches past the
+// small path).
 hipError_t launch_gemm(const int8_t* q, const float* x_scale, const int8_t* wq,
                        const float* w_scale, int64_t T, int64_t K, int64_t N,
                        const int32_t* mod, const float* u, const uint8_t* u_hl,

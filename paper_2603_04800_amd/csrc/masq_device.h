@@ -38,7 +38,6 @@ template <> struct Elem<float> {
         v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
         v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
     }
-    static __device__ __forceinline__ float load1(const float* p) { return *p; }
     static __device__ __forceinline__ void store1(float* p, float v) { *p = v; }
 };
 template <> struct Elem<bf16_t> {
@@ -50,7 +49,6 @@ template <> struct Elem<bf16_t> {
             v[2 * j + 1] = __uint_as_float(static_cast<uint32_t>(a[j]) & 0xFFFF0000u);
         }
     }
-    static __device__ __forceinline__ float load1(const bf16_t* p) { return bf16_to_f32(*p); }
     static __device__ __forceinline__ void store1(bf16_t* p, float v) {
         *p = static_cast<bf16_t>(f32_to_bf16(v));
     }

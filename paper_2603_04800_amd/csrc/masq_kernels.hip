@@ -2768,76 +2768,21 @@ __global__ __launch_bounds__(128 * NWN, 1) void k_gemm_dma(
 }
 
 // ================================================================ small-batch GEMM
-// For batches of at most 16 tokens (decoding) the layer is bound by
-// streaming Wq from HBM.  A workgroup owns 16 output channels; its four
-// waves split K and keep kSmallDepth 64-byte k steps of Wq and q loads in
-// flight, feeding v_mfma_i32_16x16x64_i8 (tokens as the 16 rows).  The
-// per-wave int32 partials are added in a fixed order in LDS (exact), then
-// each thread finishes one (token, channel): dequantisation, the rank-r
-// compensation u L2^m in fp32 for non-text tokens, and the store.
+// The standalone product of at most 16 tokens (the layer's own is
+// k_gemm_stream), bound by streaming Wq from HBM.  A workgroup owns 16 output
+// channels; its four waves split K and keep kSmallDepth 64-byte k steps of Wq
+// and q loads in flight, feeding v_mfma_i32_16x16x64_i8 (tokens as the 16
+// rows).  The per-wave int32 partials are added in a fixed order in LDS
+// (exact), then each thread finishes one (token, channel): dequantisation and
+// the store.
 constexpr int kSmallDepth = 16;
 
-// u of a small batch's rows into LDS (256 threads), adding the k-slice
-// partials in slice order when the down-projection left them separate.
-__device__ __forceinline__ void small_u_rows(float (&su)[kSmallMaxT][kMaxRank],
-                                             const float* __restrict__ u,
-                                             const float* __restrict__ u_part, int n_kslices,
-                                             int T, int r, int tid) {
-    const bool parts = u_part != nullptr && n_kslices > 1;
-    const float* src = parts ? u_part : u;
-    const int slices = parts ? n_kslices : 1;
-    for (int idx = 4 * tid; idx < T * r; idx += 4 * 256) {       // T r % 16 == 0
-        v4f v = {0.f, 0.f, 0.f, 0.f};
-        for (int q0 = 0; q0 < slices; q0 += kUBatch) {
-            v4f p[kUBatch];
-#pragma unroll
-            for (int q = 0; q < kUBatch; ++q)                        // a batch in flight
-                p[q] = *reinterpret_cast<const v4f*>(
-                    src + static_cast<int64_t>(min(q0 + q, slices - 1)) * T * r + idx);
-#pragma unroll
-            for (int q = 0; q < kUBatch; ++q)
-                if (q0 + q < slices) v = (q0 + q == 0) ? p[q] : v + p[q];   // slice order
-        }
-        const int tt = idx / r, c = idx - tt * r;
-        *reinterpret_cast<v4f*>(&su[tt][c]) = v;
-    }
-}
-
-// Dequantisation, compensation (u rows in su) and store of one output of a
-// small batch: token t, channel ch, int32 accumulator a.
-template <typename YT, typename LT>
-__device__ __forceinline__ void small_output(const float (&su)[kSmallMaxT][kMaxRank], int a, int t,
-                                             int ch, int N, const float* __restrict__ x_scale,
-                                             const float* __restrict__ w_scale,
-                                             const int32_t* __restrict__ mod, bool cmc, int r,
-                                             int n_mod, const LT* __restrict__ r_up,
-                                             YT* __restrict__ y) {
-    float v = (static_cast<float>(a) * x_scale[t]) * w_scale[ch];
-    const int m = cmc ? sane_mod(mod[t], n_mod) : 0;
-    if (m > 0) {
-        const LT* rr = r_up + (static_cast<int64_t>(m - 1) * N + ch) * r;
-        float c = 0.f;
-        for (int k0 = 0; k0 < r; k0 += 8) {
-            float uv[8], rv[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) uv[k] = su[t][k0 + k];
-            Elem<LT>::load8(rr + k0, rv);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) c = fmaf(uv[k], rv[k], c);
-        }
-        v += c;
-    }
-    Elem<YT>::store1(y + static_cast<int64_t>(t) * N + ch, v);
-}
-
-template <typename YT, typename LT, bool W4>
+template <typename YT, bool W4>
 __global__ __launch_bounds__(256) void k_gemm_small(
     const int8_t* __restrict__ A, const int8_t* __restrict__ B, const float* __restrict__ x_scale,
-    const float* __restrict__ w_scale, int T, int K, int N, const int32_t* __restrict__ mod,
-    const float* __restrict__ u, const float* __restrict__ u_part, int n_kslices, int r,
-    int n_mod, const LT* __restrict__ r_up, int32_t* __restrict__ acc_out, YT* __restrict__ y) {
+    const float* __restrict__ w_scale, int T, int K, int N, int32_t* __restrict__ acc_out,
+    YT* __restrict__ y) {
     __shared__ int part[4][16][16];
-    __shared__ float su[kSmallMaxT][kMaxRank];     // u rows of the batch
     const int tid = threadIdx.x, lane = tid & 63;
     // wave-uniform k range (scalar registers), so the loop below branches on
     // it: MFMA instructions ignore EXEC and must not sit under a lane mask
@@ -2885,7 +2830,6 @@ __global__ __launch_bounds__(256) void k_gemm_small(
     // acc[e]: token 4 (lane / 16) + e, channel col0 + lane % 16
 #pragma unroll
     for (int e = 0; e < 4; ++e) part[wave][4 * (lane >> 4) + e][lane & 15] = acc[e];
-    if (u != nullptr) small_u_rows(su, u, u_part, n_kslices, T, r, tid);
     __syncthreads();
     const int t = tid >> 4, o = tid & 15;
     if (t >= T) return;
@@ -2893,7 +2837,7 @@ __global__ __launch_bounds__(256) void k_gemm_small(
     const int ch = col0 + o;
     if (acc_out != nullptr) acc_out[static_cast<int64_t>(t) * N + ch] = a;
     if (y == nullptr) return;
-    small_output<YT, LT>(su, a, t, ch, N, x_scale, w_scale, mod, u != nullptr, r, n_mod, r_up, y);
+    Elem<YT>::store1(y + static_cast<int64_t>(t) * N + ch, (static_cast<float>(a) * x_scale[t]) * w_scale[ch]);
 }
 
 // ================================================================ MAS-only routing
@@ -3215,16 +3159,13 @@ hipError_t launch_gemm_decode_mas(const int8_t* q, const float* x_scale, const i
     return hipSuccess;
 }
 
-template <typename YT, typename LT, bool W4>
+template <typename YT, bool W4>
 static void launch_gemm_small_t(const int8_t* q, const float* x_scale, const int8_t* wq,
-                                const float* w_scale, int64_t T, int64_t K, int64_t N,
-                                const int32_t* mod, const float* u, const float* u_part,
-                                int n_kslices, int rank, int n_mod, const void* r_up, int32_t* acc,
+                                const float* w_scale, int64_t T, int64_t K, int64_t N, int32_t* acc,
                                 void* y, hipStream_t s) {
-    hipLaunchKernelGGL((k_gemm_small<YT, LT, W4>), dim3(static_cast<unsigned>(N / 16)), dim3(256), 0, s,
-                       q, wq, x_scale, w_scale, static_cast<int>(T), static_cast<int>(K),
-                       static_cast<int>(N), mod, u, u_part, n_kslices, rank, n_mod,
-                       static_cast<const LT*>(r_up), acc, static_cast<YT*>(y));
+    hipLaunchKernelGGL((k_gemm_small<YT, W4>), dim3(static_cast<unsigned>(N / 16)), dim3(256), 0, s, q,
+                       wq, x_scale, w_scale, static_cast<int>(T), static_cast<int>(K),
+                       static_cast<int>(N), acc, static_cast<YT*>(y));
 }
 
 template <typename YT, typename LT, bool CMC, bool ACC, bool W4>
@@ -3305,10 +3246,9 @@ hipError_t launch_gemm(const int8_t* q, const float* x_scale, const int8_t* wq,
                        int* gk_tickets, const float* u_part, int n_kslices,
                        int rank, int n_mod, const void* r_up, DT lr_dt, bool cmc, int32_t* acc,
                        void* y, DT y_dt, hipStream_t s, TilePlan tile, bool w4, bool a_pair) {
-    // packed 4-bit Wq: K % 64 == 0 (checked by the caller), so every batch
-    // takes the decode, small-batch or direct-to-LDS kernel
+    // packed 4-bit Wq: K % 64 == 0 (checked by the caller)
     if (w4 && K % 64 != 0) return hipErrorInvalidValue;
-    // row-paired codes are read by the direct-to-LDS GEMM only
+    // row-paired codes are read by the kernels past the small batches only
     if (a_pair && !paired_codes(T, K)) return hipErrorInvalidValue;
     if (small_path(T, K) && dec_part != nullptr && dec_tickets != nullptr && acc == nullptr) {
         const bool parts = u_part != nullptr && n_kslices > 1;
@@ -3317,16 +3257,11 @@ hipError_t launch_gemm(const int8_t* q, const float* x_scale, const int8_t* wq,
                                              rank, n_mod, r_up, lr_dt, y, y_dt, w4, dec_part, dec_tickets,
                                              -1, s});
     }
-    if (small_path(T, K)) {
-        const float* uu = cmc ? u : nullptr;
-#define MASQ_SMALL(YT, LT) (w4 ? launch_gemm_small_t<YT, LT, true> : launch_gemm_small_t<YT, LT, false>)(q, x_scale, wq, w_scale, T, K, N, mod, uu, u_part, n_kslices, rank, n_mod, r_up, acc, y, s)
-        if (y_dt == DT::BF16) {
-            if (lr_dt == DT::BF16) MASQ_SMALL(bf16_t, bf16_t);
-            else MASQ_SMALL(bf16_t, float);
-        } else {
-            if (lr_dt == DT::BF16) MASQ_SMALL(float, bf16_t);
-            else MASQ_SMALL(float, float);
-        }
+    if (small_path(T, K)) {                   // the standalone product: no workspace, no compensation
+        if (cmc) return hipErrorInvalidValue;
+#define MASQ_SMALL(YT) (w4 ? launch_gemm_small_t<YT, true> : launch_gemm_small_t<YT, false>)(q, x_scale, wq, w_scale, T, K, N, acc, y, s)
+        if (y_dt == DT::BF16) MASQ_SMALL(bf16_t);
+        else MASQ_SMALL(float);
 #undef MASQ_SMALL
         return hipGetLastError();
     }
