@@ -293,10 +293,13 @@ __global__ __launch_bounds__(256) void k_smooth_quant_rows(const XT* __restrict_
 // sums are added across waves in LDS in a fixed order.  Rows whose modality
 // is not m contribute zeros.  MFMA operand layout: lane l holds row/column
 // (l % 16) and the k group (l / 16); A and B use the same k assignment.
-// The instructions of a round stand in one block of code: column blocks past
-// the group's and steps past the range multiply zeros (or repeat a column
-// block whose result is dropped).  A branch between an MFMA and the next
-// read of its result has been compiled without the wait that the read needs.
+// A round's loads and MFMAs stand in one block of code: column blocks past the
+// group's repeat the last (their results are dropped), and steps past the
+// range multiply zeros (bf16) or are rounds of their own (fp32), because a
+// branch between the steps sinks their loads behind it, one wait each.  The k
+// range is in scalar registers (down_group): MFMA ignores EXEC, so that under
+// a lane mask it would add the masked lanes' operands too.  (The compiler
+// counts the wait between an MFMA and a read of its result across branches.)
 template <typename XT, typename LT> struct DownK;
 
 // bf16 factors: the smoothed row enters as two bf16 terms, hi = bf16(xs) and
