@@ -618,7 +618,7 @@ __global__ __launch_bounds__(64 * kDownWaves) void k_lowrank_down(const XT* __re
 // rows of up to kQuantDownMaxK columns, which a wave's registers hold):
 // neither needs the other, and on small batches each is a few microseconds of
 // launch and dependent loads.  Stage 1 one after the other / together: 256 x
-// 512 fp32, rank 16, 9.7 / 7.2 us; 1000 x 3584 bf16, rank 128, 54.4 / 46.5;
+// 512 fp32, rank 16, 9.7 / 7.6 us; 1000 x 3584 bf16, rank 128, 54.4 / 46.5;
 // 8192 x 2048 bf16, rank 128, 82.5 / 68.1.  Workgroups below
 // down_tiles take a 16-row tile of u, the others 8 rows of codes, a wave each.
 template <typename XT, typename LT, int NC>
@@ -1664,11 +1664,11 @@ __global__ __launch_bounds__(64 * kFrWaves) void k_stage1_fr(
 // where T / 32 tiles would leave most of it idle.  One lane a channel and
 // scalar fma, 16 rows a workgroup: 2081 us for 1000 x 1040 -> 2000, rank 128
 // in fp32, and 4.6 ms for 8192 x 3584 -> 3584, rank 64 in bf16; in this form
-// 43 and 139 us (16-row tiles, twice the L1 reads: 68 and 224 us).  A token's
-// sums hold the r products of its own modality and no others, so that a
-// factor that is not finite stays in its own outputs; that costs 0 to 4 %,
-// and 8 % where the modalities alternate (8192 x 3584 -> 3584, three of them,
-// 129 -> 139 us).
+// 34 and 139 us (16-row tiles, twice the L1 reads, took 1.6 times as long).
+// A token's sums hold the r products of its own modality and no others, so
+// that a factor that is not finite stays in its own outputs; that costs 0 to
+// 4 %, and 8 % where the modalities alternate (8192 x 3584 -> 3584, three of
+// them, 129 -> 139 us).
 constexpr int kCompRows = 32;
 constexpr int kCompWaves = 8;
 constexpr int kCompPad = 4;             // floats after a u row: rows start on different banks

@@ -7,17 +7,19 @@
 //                    optionally split into S slices per tile.
 //   k_gemm_stream    batches of at most 16 tokens (decoding), below.
 //
-// What bounds k_gemm_tile: the bytes a compute unit can pull through its DMA path (33
-// to 40 bytes a clock; a 64 x 64 tile needs 16 KB per 64 clocks of MFMA),
-// and at few tokens the weight's stream from HBM.  So the shapes are chosen
-// for bytes in flight: small rings, so that two (128 x 128, 64 KB), three
-// (64 x 64, 48 KB) or four (32 x 64, 36 KB) workgroups share a CU and hide
-// each other's barriers and epilogues; a 64 x 64 ring of 5 stages, one
-// workgroup per CU, took 25.2 us where 3 stages take 17.3 (64 tokens, 3584
-// -> 18944), and one of 2 stages 20.1.  Measured per GEMM launch against the
-// 256 x 256 kernel: 64 tokens 3584 -> 18944 42.1 -> 17.3 us, 64 tokens 18944
-// -> 3584 60 -> 19.1 us, 333 tokens 3584 -> 3584 30.5 -> 15.0 us, 256 tokens
-// 512 -> 512 (fp32) 28.4 -> 5.8 us.
+// What bounds k_gemm_tile: at few tokens the weight's stream from HBM and the
+// latency of each workgroup's chain of stages (64 tokens 3584 -> 18944: 71 MB
+// fetched in 17.1 us, 4.2 TB/s; 13 bytes a clock and compute unit through the
+// DMA path, matrix cores 8 % busy), and with several tiles a unit the DMA path
+// itself (1184 tiles of 64 x 64: 23 bytes a clock; a probe of it alone reaches
+// 33).  So the shapes are chosen for bytes in flight: small rings, so that two
+// (128 x 128, 64 KB), three (64 x 64, 48 KB) or four (32 x 64, 36 KB)
+// workgroups share a CU and hide each other's barriers and epilogues; a 64 x 64
+// ring of 5 stages, one workgroup per CU, took 25.2 us where 3 stages take 17.3
+// (64 tokens, 3584 -> 18944), and one of 2 stages 20.1.  Measured per GEMM
+// launch against the 256 x 256 kernel: 64 tokens 3584 -> 18944 42.1 -> 17.3 us,
+// 64 tokens 18944 -> 3584 60 -> 19.1 us, 333 tokens 3584 -> 3584 30.5 -> 15.0
+// us, 256 tokens 512 -> 512 (fp32) 28.4 -> 5.8 us.
 
 #include "masq_device.h"
 
@@ -432,11 +434,12 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void k_gemm_tile(
 // At most 16 tokens: the layer is a stream of Wq from HBM.  A workgroup of
 // four waves owns 64 output channels (16 a wave, v_mfma_i32_16x16x64_i8, the
 // tokens as rows) and one of S k slices; q and Wq come in 128-byte stages
-// through a ring of four LDS buffers filled by DMA (10 KB a stage), three
-// workgroups a CU, so that each CU keeps about 90 KB in flight and a grid of
-// 296 channel groups (18944 channels) is resident at once without a split.
-// With fewer groups the slices hand their int32 partials over through
-// agent-scope stores and an arrival counter per group, as k_gemm_tile does.
+// through a ring of four LDS buffers filled by DMA (10 KB a stage, three of
+// them in flight), up to three workgroups a CU, so that a grid of 296 channel
+// groups (18944 channels) is resident at once without a split (1 token: 68 MB
+// in 14.0 us, 4.9 TB/s).  With fewer groups the slices hand their int32
+// partials over through agent-scope stores and an arrival counter per group,
+// as k_gemm_tile does.
 //
 // The compensation of the tokens t with t % S == slice is formed by the
 // workgroup itself while its first stages are in flight: the u slice partials
