@@ -34,7 +34,10 @@ namespace masq {
 // (1036-1924 tiles, 512-18944 columns; packed, 3584 columns: 1036 tiles 82.8
 // us where 256 x 256 take 93.3, 1184 90-93 / 94, 1316 103.6 / 96, 1536 108 /
 // 98; 1184 of 512 columns 30.7 / 30.3; int8, 1924 tiles 147.8 / 138.6, 1120
-// of 3008 columns 85.5 / 78.8).
+// of 3008 columns 85.5 / 78.8).  With fp32 factors or ranks past 64 the 256 x
+// 256 kernel's compensation costs far more than a round, and the estimate
+// above stands (layers of 2343 x 768 -> 13248, fp32, rank 64, 102.5 us / 300.8;
+// 2600 x 3584 -> 8192, bf16, rank 128, packed, 212.6 / 302.0).
 // At 3584 columns this gives 64 x 64 tiles for 333 x 3584 (15.0 us; 128 x 128
 // 23.3, 256 x 256 30.5), 128 x 128 for 2048 x 3584 (38.8; 51, 45.0) and 256 x
 // 256 for 512 x 18944 (49.8; 72, 64).  Rows that are not a multiple of 64
@@ -42,7 +45,7 @@ namespace masq {
 // every unit has a workgroup, in slices of at least 10 stages, 8 at most (64
 // tokens, 18944 -> 3584: 40.3 us in one slice, 24.8 in 2, 19.1 in 4, 22.8 in
 // 8, which pay the hand-over again).
-TilePlan plan_tile(int64_t T, int64_t K, int64_t N, bool split, bool w4) {
+TilePlan plan_tile(int64_t T, int64_t K, int64_t N, bool split, bool w4, bool slow_comp) {
     if (T <= 0 || N <= 0) return TilePlan{-1, 1};
     auto tiles = [&](int64_t bm, int64_t bn) { return ((T + bm - 1) / bm) * ((N + bn - 1) / bn); };
     TilePlan p{T <= 32 ? 0 : 1, 1};
@@ -61,7 +64,7 @@ TilePlan plan_tile(int64_t T, int64_t K, int64_t N, bool split, bool w4) {
             const int s256 = split ? plan_gemm_splits(T, K, N) : 1;
             const double rounds = static_cast<double>((n256 + 255) / 256);
             double t256 = s256 > 1 ? 1.0 / s256 + 17.0 / (50.0 * k / 3584.0) : rounds;
-            if (p.shape == 2 && n128 > 1024) {         // both in ns
+            if (p.shape == 2 && n128 > 1024 && !slow_comp) {      // both in ns
                 best = static_cast<double>(n128) * (19.0 + (w4 ? 0.0161 : 0.0195) * k);
                 t256 = rounds * (9000.0 + 10.75 * k);
             }
@@ -192,10 +195,10 @@ static Workspace carve_workspace(void* base, int64_t T, int64_t K, int64_t N, in
 // slices of k_down_lds (down_lds_quarters) are taken where it has room for
 // their partials.
 Workspace plan_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, int n_mod,
-                         bool w4) {
+                         bool w4, bool slow_comp) {
     const int long_q = 4 * down_lds_chunks(T, K), dl_q = down_lds_quarters(T, K);
     Workspace w = carve_workspace(base, T, K, N, rank, n_mod, TilePlan{-1, 1}, long_q);
-    TilePlan tile = small_path(T, K) ? TilePlan{-1, 1} : plan_tile(T, K, N, true, w4);
+    TilePlan tile = small_path(T, K) ? TilePlan{-1, 1} : plan_tile(T, K, N, true, w4, slow_comp);
     const size_t bytes = w.bytes;
     for (; tile.shape >= 0; tile.S = tile_slices(K, tile.S - 1)) {
         w = carve_workspace(base, T, K, N, rank, n_mod, tile, long_q);
@@ -338,7 +341,7 @@ masq_status validate_fused(const Fused& a) {
         return MASQ_ERR_ALIGN;
     if (cmc && (!aligned16(a.l_down) || !aligned16(a.r_up))) return MASQ_ERR_ALIGN;
     if (a.workspace && (reinterpret_cast<uintptr_t>(a.workspace) & 255u) != 0) return MASQ_ERR_ALIGN;
-    const masq::Workspace w = masq::plan_workspace(nullptr, a.T, a.c_in, a.c_out, a.rank, a.n_mod, a.w4);
+    const masq::Workspace w = masq::plan_workspace(nullptr, a.T, a.c_in, a.c_out, a.rank, a.n_mod);
     if (a.T > 0 && a.workspace_bytes < w.bytes) return MASQ_ERR_WORKSPACE;
     return MASQ_OK;
 }
@@ -348,7 +351,8 @@ masq_status fused_stage(const Fused& a, int stage) {
     if (st != MASQ_OK || a.T == 0) return st;
     const bool cmc = a.rank > 0 && a.n_mod > 1;
     const masq::Workspace w =
-        masq::plan_workspace(a.workspace, a.T, a.c_in, a.c_out, a.rank, a.n_mod, a.w4);
+        masq::plan_workspace(a.workspace, a.T, a.c_in, a.c_out, a.rank, a.n_mod, a.w4,
+                             cmc && (a.lr_dt == MASQ_F32 || a.rank > 64));
     hipStream_t s = static_cast<hipStream_t>(a.stream);
     (void)hipGetLastError();
     if ((stage & 1) && masq::small_path(a.T, a.c_in)) {

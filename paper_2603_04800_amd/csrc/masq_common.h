@@ -98,8 +98,9 @@ inline int plan_gemm_splits(int64_t T, int64_t K, int64_t N) {
 struct TileShape { int bm, bn; };
 constexpr TileShape kTileShapes[] = {{32, 64}, {64, 64}, {128, 128}};
 struct TilePlan { int shape, S; };
-// split: slices are possible (the caller has room for their accumulators).
-TilePlan plan_tile(int64_t T, int64_t K, int64_t N, bool split, bool w4);
+// split: slices are possible (the caller has room for their accumulators);
+// slow_comp: compensation with fp32 factors or a rank past 64.
+TilePlan plan_tile(int64_t T, int64_t K, int64_t N, bool split, bool w4, bool slow_comp = false);
 constexpr int kTileStageK = 128;      // codes per stage of the small-tile GEMM
 // At most S slices of whole stages, none of them empty.
 inline int tile_slices(int64_t K, int S) {
@@ -180,7 +181,7 @@ struct Workspace {
 };
 
 Workspace plan_workspace(void* base, int64_t T, int64_t K, int64_t N, int rank, int n_mod,
-                         bool w4 = false);
+                         bool w4 = false, bool slow_comp = false);
 
 // zero_ints / n_zero: optional array the kernel clears on the way (the
 // down-projection's tickets, which must start at zero).

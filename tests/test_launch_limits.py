@@ -70,3 +70,13 @@ def test_tile_shapes_of_several_rounds(record, T, K, N, w4, large):
     for status, launches in record([f"fused {T} {K} {N} 32 2 {BF16} {BF16} {BF16} {w4}", f"gemm {T} {K} {N} {BF16} {w4}"]):
         assert status == 0
         assert launches[-1] == (256, 1, 1, 512) if large else launches[-1][3] == 256, launches
+
+
+def test_slow_compensation_keeps_the_small_tiles(record):
+    """With fp32 factors or a rank past 64 the 256 x 256 kernel's compensation
+    costs more than its rounds save."""
+    (st, f32), (sb, bf16), (sr, r128) = record([f"fused 2343 768 13248 64 2 {F32} {F32} {F32} 0",
+                                                f"fused 2343 768 13248 64 2 {F32} {BF16} {F32} 0",
+                                                f"fused 2343 768 13248 128 2 {BF16} {BF16} {BF16} 0"])
+    assert st == sb == sr == 0 and bf16[-1] == (256, 1, 1, 512)
+    assert f32[-1] == r128[-1] == (1976, 1, 1, 256)
